@@ -137,15 +137,13 @@ def bench_next_rows(ctx, patch, orb, w, snr, dev, reps=3):
         return float(np.median(ts))
 
     res = {}
-    # f-2: iterated MAD over the 200 flux images (one full read per digit pass)
+    # f-2: iterated MAD over the 200 flux images
     out = {}
     t_noise = timed(lambda: out.update(r=dt.image_noise(ctx, w.D)))
     sig, used, it = (x.cpu().numpy() for x in out["r"])
     npix = np.array([x.numel() for x in w.D], dtype=np.float64)
-    # count pass + first median digit, then per step two median digits, three
-    # deviation digits (the third also compacts the last digits' keys) and the clip
-    passes = 2 + 6 * it.astype(np.float64)
-    nbytes = float((passes * npix * 4).sum())
+    # the images are read twice: the histogram, then the values of its marked bins
+    nbytes = float((2 * npix * 4).sum())
     res["noise"] = dict(images=len(w.D), ms=t_noise, steps_mean=float(it.mean()), steps_max=int(it.max()),
                         sigma_mean=float(sig.mean()), bytes_read=nbytes,
                         achieved_GBs=nbytes / (t_noise * 1e-3) / 1e9, peak_GBs=HBM_PEAK_GBS)

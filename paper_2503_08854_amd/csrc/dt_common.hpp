@@ -254,19 +254,7 @@ hipError_t launch_record_gathers(const StackArgs& a, int64_t* cnt, const int64_t
 hipError_t launch_gather_replay(const float2* planes, const int64_t* gstart, const int64_t* list, int64_t n,
                                 float* snr, hipStream_t s);
 
-// Per-image iterated-MAD noise: per-image selection state.
-struct NoiseState {
-  double m_cur, thr_cur;  // current set: finite x with |x - m_cur| <= thr_cur
-  double m_new, thr_new;  // median of the set and the next clip half-width
-  double sigma;
-  double val[2];          // the two selected middle values
-  uint64_t prefix[2];     // key bits chosen so far
-  int64_t rank[2];        // target ranks among keys sharing the prefix
-  int64_t n, n_new, n_used;
-  int64_t n_list;         // deviation keys compacted for the last digits (> NOISE_LIST_CAP: not used)
-  int32_t iter, done, changed, pad;
-};
-constexpr int64_t NOISE_LIST_CAP = 65536;  // compacted deviation keys per image
+// Per-image iterated-MAD noise.
 constexpr double NOISE_KAPPA = 3.0;   // clip half-width in sigma (patches without variance planes)
 constexpr int NOISE_MAX_ITER = 10;
 size_t noise_scratch_bytes(int n_img);

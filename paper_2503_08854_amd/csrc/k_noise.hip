@@ -4,369 +4,858 @@
 // kappa sigma}; repeat until S' == S or max_iter steps.  The median of an
 // even count is the mean of the two middle values.
 //
-// Exact selection by radix select: the two middle ranks are found digit by
-// digit (11-bit digits) over an order-preserving integer key -- the float
-// bits for x, the double bits of |x - m| (non-negative, so the raw bits
-// order) for the deviations.  Every pass re-reads the image and builds an
-// LDS histogram of the digit among the pixels that match the prefix chosen so
-// far; a one-block pick kernel per image scans it.  The set S is never
-// stored: membership is the predicate |x - m_cur| <= thr_cur evaluated in
-// FP64, the same arithmetic for every pass, so selection, clipping and the
-// change test are exact and the result equals the FP64 definition.
+// Every set S is an interval of the sorted finite pixels (the FP64 predicate
+// |x - m| <= thr is monotone on each side of m), so a step needs order
+// statistics at five places only: the middle of S, m -+ the deviation median
+// and the two cuts.  The image is therefore read twice, not once per digit
+// and step:
+//   sample   a sorted sample of each image runs the iteration and says where
+//            those places are; it sets a monotone map of values to
+//            NZ_BINS bins, fine around the median and around m -+ the
+//            deviation median (~5e-5 sigma), coarse (~1e-3 sigma) elsewhere;
+//   bins     one read of the images: the histogram of that map;
+//   plan     the iteration on the interpolated histogram; the bins around
+//            every place it visits are marked;
+//   collect  a second read: the values of the marked bins are listed (a few
+//            thousand per image); of bins that are too full because one value
+//            repeats (integer or zero-filled images) only the other values;
+//   solve    the exact iteration on ranks: number of pixels below a bin (the
+//            histogram) + position in the sorted list.  Each rank it uses is
+//            checked to fall in a marked bin (or a gap without pixels); if
+//            one does not, the image is solved by radix selection over its
+//            pixels in the same workgroup.
+// All comparisons that decide the result are the FP64 ones of the definition,
+// so the result is exact on either route.
 //
-// Passes per step: the median's second and third digits (its first is
-// histogrammed by the previous step's clip pass, which already knows the
-// next set), the deviation key's first two digits, then one pass that both
-// histograms its third digit and compacts the few keys that share the
-// chosen 22-bit prefix into a per-image list; its last three digits come
-// from that list (or from the image again if the list overflows), and one
-// clip pass: six image reads per step instead of ten.
+// Two image reads bound it.  200 FP32 2048^2 images (3.36 GB): bins 0.71 ms
+// (4.7 TB/s, the copy rate), collect 0.66 ms, sample + plan + solve 0.43 ms
+// (one workgroup per image, latency); 1.72 ms together, 32.2 ms before, when
+// every 11-bit digit of every median and deviation of every step read the
+// images again (26 reads).  48 FP32 2048 x 1536 images: 0.53 ms, 6.9 before.
 #include <algorithm>
+#include <type_traits>
 
 #include "dt_common.hpp"
 
 namespace dtk {
 
-constexpr int NZ_BITS = 11;
-constexpr int NZ_BINS = 1 << NZ_BITS;
-constexpr int NZ_TX = 256;
+constexpr int NZ_BINS = 16384;        // histogram bins per image (64 KB of LDS in the counting pass)
+constexpr int NZ_COARSE = 5120;       // of which over the whole range
+constexpr int NZ_CENTER = 3072;       // in the window around the median (the rest: 2 x 4094 around m -+ d)
+constexpr int NZ_TX = 1024;           // threads of every workgroup here
+constexpr int NZ_WAVES = NZ_TX / 64;
+constexpr int NZ_SAMPLE = 4096;       // sample size
+constexpr int NZ_SAMPLE_STEPS = 6;    // clip steps followed on the sample
+constexpr int64_t NZ_WHOLE = 16384;   // images up to this size are listed whole
+constexpr int NZ_LIST = 32768;        // listed values per image
+constexpr int NZ_TAB = 512;           // marked bins per image
+constexpr int NZ_STAGE = 2048;        // values a collecting workgroup stages in LDS
+constexpr int NZ_DHAT = 16;           // steps whose planned deviation median is kept
 
-template <typename T>
-__device__ __forceinline__ float nz_load(const void* p, int64_t k);
-template <>
-__device__ __forceinline__ float nz_load<float>(const void* p, int64_t k) {
-  return static_cast<const float*>(p)[k];
+// Monotone map of a value to a bin: the sum of clamped, scaled differences
+// from the sample median (each term is non-decreasing in x, also rounded).
+struct NoiseMap {
+  float mc;          // sample median
+  float T;           // half range
+  float wc;          // half width of the window around the median
+  float q0, q1;      // deviation window
+  float a0, a1, a2;  // bins per unit
+  float off;
+};
+
+struct NoiseImage {
+  NoiseMap map;
+  uint32_t n;       // finite pixels
+  uint32_t n_list;  // values listed
+  int32_t n_tab;    // marked bins; -1: too many, solve from the pixels
+  int32_t whole;    // one bin, every value listed
+  int32_t n_sample; // finite values of the sample
+  float dhat[NZ_DHAT];  // the plan's deviation medians, by step (0: none)
+  uint32_t bin[NZ_TAB], below[NZ_TAB], cnt[NZ_TAB];  // marked bins: index, pixels below, pixels in
+  uint32_t heavy[NZ_TAB];                            // key of the value that is not listed (0: none)
+  uint16_t mode[NZ_BINS];                            // 0 not listed, 0xffff listed, else 1 + table entry (heavy value)
+  uint32_t hist[NZ_BINS];
+  uint32_t sample[NZ_SAMPLE];  // sorted keys
+  uint32_t list[NZ_LIST];      // keys
+};
+
+typedef float nz_f4 __attribute__((ext_vector_type(4)));
+typedef _Float16 nz_h8 __attribute__((ext_vector_type(8)));
+
+// Order-preserving key of a float, one for both zeros (never 0 or 0xffffffff
+// for a finite value).
+__device__ __forceinline__ uint32_t fkey(float x) {
+  const uint32_t u = __float_as_uint(x == 0.f ? 0.f : x);
+  return (u & 0x80000000u) ? ~u : (u | 0x80000000u);
 }
-template <>
-__device__ __forceinline__ float nz_load<_Float16>(const void* p, int64_t k) {
-  return (float)static_cast<const _Float16*>(p)[k];
+__device__ __forceinline__ float fkey_value(uint32_t k) {
+  return __uint_as_float((k & 0x80000000u) ? (k & 0x7fffffffu) : ~k);
 }
 
-__device__ __forceinline__ uint64_t fkey(float x) {
-  const uint32_t u = __float_as_uint(x);
-  return (uint64_t)((u & 0x80000000u) ? ~u : (u | 0x80000000u));
+__device__ __forceinline__ float clampf(float y, float lo, float hi) { return fminf(fmaxf(y, lo), hi); }
+__device__ __forceinline__ float map_pos(const NoiseMap& M, float y) {
+  float g = fmaf(M.a0, clampf(y, -M.T, M.T), M.off);
+  g = fmaf(M.a1, clampf(y, -M.wc, M.wc), g);
+  return fmaf(M.a2, clampf(y, M.q0, M.q1) + clampf(y, -M.q1, -M.q0), g);
 }
-__device__ __forceinline__ double fkey_value(uint64_t k) {
-  const uint32_t u = (uint32_t)k;
-  return (double)__uint_as_float((u & 0x80000000u) ? (u & 0x7fffffffu) : ~u);
-}
+__device__ __forceinline__ int pos_bin(float g) { return (int)fminf(fmaxf(g, 0.f), (float)(NZ_BINS - 1)); }
+__device__ __forceinline__ int map_bin(const NoiseMap& M, float x) { return pos_bin(map_pos(M, x - M.mc)); }
 
-__device__ __forceinline__ bool in_set(float x, const NoiseState& S) {
-  return __builtin_isfinite(x) && fabs((double)x - S.m_cur) <= S.thr_cur;
-}
-
-__global__ void k_noise_init(NoiseState* st, uint32_t* hist, int n_img) {
-  const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  const int64_t nh = (int64_t)n_img * 2 * NZ_BINS;
-  if (i < nh) hist[i] = 0u;
-  if (i < n_img) {
-    NoiseState z{};
-    z.m_cur = 0.0;
-    z.thr_cur = __builtin_inf();
-    z.sigma = __builtin_nan("");
-    st[i] = z;
+// f(x) for every pixel of an image, the pixels shared by `blocks` workgroups
+// of which this is `block`: 16-byte loads, U in flight per thread; the
+// unaligned head and the tail one by one.
+template <typename T, int U = 4, typename F>
+__device__ __forceinline__ void for_pixels(const void* img, int64_t n, int block, int blocks, F&& f) {
+  constexpr int V = 16 / sizeof(T);
+  using Vec = std::conditional_t<sizeof(T) == 4, nz_f4, nz_h8>;
+  const T* p = static_cast<const T*>(img);
+  const int64_t head = std::min<int64_t>(n, (int64_t)((16 - ((uintptr_t)p & 15)) & 15) / (int64_t)sizeof(T));
+  const int64_t nv = (n - head) / V;
+  const int64_t gid = (int64_t)block * NZ_TX + threadIdx.x, stride = (int64_t)blocks * NZ_TX;
+  const auto* pv = (const __attribute__((address_space(1))) Vec*)(p + head);
+  const auto* ps = global_ptr(p);
+  for (int64_t v = gid; v < nv; v += stride * U) {
+    Vec x[U];
+#pragma unroll
+    for (int u = 0; u < U; ++u)
+      if (v + u * stride < nv) x[u] = pv[v + u * stride];
+#pragma unroll
+    for (int u = 0; u < U; ++u)
+      if (v + u * stride < nv) {
+#pragma unroll
+        for (int j = 0; j < V; ++j) f((float)x[u][j]);
+      }
   }
+  const int64_t tail0 = head + nv * V;
+  if (gid < head) f((float)ps[gid]);
+  if (tail0 + gid < n) f((float)ps[tail0 + gid]);  // fewer than V <= 8 pixels
 }
 
+// Exclusive prefix sum over the workgroup; *total is the sum.  tmp: NZ_WAVES
+// words of LDS.
+__device__ __forceinline__ uint32_t block_scan(uint32_t v, uint32_t* tmp, uint32_t* total) {
+  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+  uint32_t inc = v;
+#pragma unroll
+  for (int o = 1; o < 64; o <<= 1) {
+    const uint32_t u = (uint32_t)__shfl_up((int)inc, o, 64);
+    if (lane >= o) inc += u;
+  }
+  __syncthreads();  // earlier readers of tmp
+  if (lane == 63) tmp[w] = inc;
+  __syncthreads();
+  uint32_t base = 0, sum = 0;
+  for (int i = 0; i < NZ_WAVES; ++i) {
+    if (i < w) base += tmp[i];
+    sum += tmp[i];
+  }
+  *total = sum;
+  return base + inc - v;
+}
+
+// Ascending bitonic sort of the NZ_TX * PER keys in s (LDS).  Thread t holds
+// keys PER t .. PER t + PER - 1: a compare-exchange at distance j is in
+// registers for j < PER, between lanes for j < 64 PER, and through LDS, with
+// barriers, only beyond (10 of the 78 stages of 4096 keys).
+template <int PER>
+__device__ __forceinline__ void sort_per(uint32_t* s) {
+  constexpr int S = NZ_TX * PER;
+  const int t = threadIdx.x;
+  uint32_t r[PER];
+  __syncthreads();
+#pragma unroll
+  for (int q = 0; q < PER; ++q) r[q] = s[PER * t + q];
+  __syncthreads();
+#pragma unroll 1
+  for (int k = 2; k <= S; k <<= 1) {
+#pragma unroll 1
+    for (int j = k >> 1; j >= PER; j >>= 1) {
+      const bool low = ((PER * t) & j) == 0, up = ((PER * t) & k) == 0;
+      uint32_t o[PER];
+      if (j >= 64 * PER) {
+        // key PER t + q at q NZ_TX + t: the lanes touch consecutive words
+#pragma unroll
+        for (int q = 0; q < PER; ++q) s[q * NZ_TX + t] = r[q];
+        __syncthreads();
+#pragma unroll
+        for (int q = 0; q < PER; ++q) o[q] = s[q * NZ_TX + (t ^ (j / PER))];
+        __syncthreads();
+      } else {
+#pragma unroll
+        for (int q = 0; q < PER; ++q) o[q] = (uint32_t)__shfl_xor((int)r[q], j / PER, 64);
+      }
+#pragma unroll
+      for (int q = 0; q < PER; ++q) r[q] = low == up ? std::min(r[q], o[q]) : std::max(r[q], o[q]);
+    }
+#pragma unroll
+    for (int j = PER / 2; j > 0; j >>= 1) {
+      if (j > (k >> 1)) continue;
+#pragma unroll
+      for (int q = 0; q < PER; ++q) {
+        if (q & j) continue;
+        const uint32_t a = std::min(r[q], r[q | j]), b = std::max(r[q], r[q | j]);
+        const bool up = ((PER * t + q) & k) == 0;
+        r[q] = up ? a : b;
+        r[q | j] = up ? b : a;
+      }
+    }
+  }
+#pragma unroll
+  for (int q = 0; q < PER; ++q) s[PER * t + q] = r[q];
+  __syncthreads();
+}
+
+// Where the iteration goes on a sample, and the map from it; clears the
+// image's histogram.
 template <typename T>
-__global__ __launch_bounds__(NZ_TX) void k_noise_count(const void* const* imgs, const int64_t* npix, NoiseState* st) {
-  const int img = blockIdx.y;
-  const void* X = imgs[img];
+__global__ __launch_bounds__(NZ_TX) void k_noise_sample(const void* const* imgs, const int64_t* npix, NoiseImage* st,
+                                                        double kappa, int max_iter) {
+  const int img = blockIdx.x;
+  const int tid = threadIdx.x;
   const int64_t n = npix[img];
-  uint64_t c = 0;
-  for (int64_t i = (int64_t)blockIdx.x * NZ_TX + threadIdx.x; i < n; i += (int64_t)gridDim.x * NZ_TX)
-    c += __builtin_isfinite(nz_load<T>(X, i)) ? 1u : 0u;
-  for (int o = 32; o > 0; o >>= 1) c += __shfl_xor(c, o);
-  if ((threadIdx.x & 63) == 0 && c) atomicAdd((unsigned long long*)&st[img].n, (unsigned long long)c);
-}
-
-// Start of a step: ranks of the two middle elements of the current set.
-__device__ __forceinline__ void begin_select(NoiseState& S) {
-  S.rank[0] = (S.n - 1) / 2;
-  S.rank[1] = S.n / 2;
-  S.prefix[0] = S.prefix[1] = 0;
-}
-
-__global__ void k_noise_begin(NoiseState* st, int n_img) {
-  const int i = blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= n_img) return;
-  NoiseState& S = st[i];
-  if (S.n <= 0) {
-    S.done = 1;
+  NoiseImage& S = st[img];
+  __shared__ uint32_t s[NZ_SAMPLE];
+  __shared__ uint32_t tmp[NZ_WAVES];
+  __shared__ unsigned int best[2];
+  for (int b = tid; b < NZ_BINS; b += NZ_TX) S.hist[b] = 0u;
+  if (tid < NZ_DHAT) S.dhat[tid] = 0.f;
+  if (tid == 0) {
+    S.n = 0;
+    S.n_list = 0;
+    S.n_tab = 0;
+    S.whole = n <= NZ_WHOLE;
+    S.n_sample = 0;
+    best[0] = best[1] = 0xffffffffu;
+  }
+  if (n <= NZ_WHOLE) {  // every value is listed: one bin
+    if (tid == 0) S.map = NoiseMap{0.f, 1.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
     return;
   }
-  begin_select(S);
-}
-
-// One digit pass.  KIND 0: key of x; KIND 1: bits of |x - m_new|.
-// SRC 0: the image; SRC 1: the image, and keys sharing the prefix above
-// this digit are also appended to the image's list; SRC 2: the list (or the
-// image when the list overflowed).
-template <typename T, int KIND, int SRC>
-__global__ __launch_bounds__(NZ_TX) void k_noise_hist(const void* const* imgs, const int64_t* npix, NoiseState* st,
-                                                     uint32_t* hist, uint64_t* lists, int lo, int nb) {
-  const int img = blockIdx.y;
-  const NoiseState S = st[img];
-  if (S.done) return;
-  __shared__ uint32_t h[2][NZ_BINS];
-  const bool two = S.prefix[0] != S.prefix[1];
-  for (int b = threadIdx.x; b < 2 * NZ_BINS; b += NZ_TX) (&h[0][0])[b] = 0u;
-  __syncthreads();
-  const int hi = lo + nb;  // <= 63 for both key kinds
-  const uint64_t p0 = S.prefix[0] >> hi, p1 = S.prefix[1] >> hi;
-  const uint32_t mask = (1u << nb) - 1u;
-  uint64_t* list = lists + (int64_t)img * NOISE_LIST_CAP;
-  auto take = [&](uint64_t key) {
-    const uint32_t d = (uint32_t)(key >> lo) & mask;
-    const uint64_t top = key >> hi;
-    if (top == p0) atomicAdd(&h[0][d], 1u);
-    if (two && top == p1) atomicAdd(&h[1][d], 1u);
-    return top == p0 || (two && top == p1);
-  };
-  if (SRC == 2 && S.n_list <= NOISE_LIST_CAP) {
-    for (int64_t i = (int64_t)blockIdx.x * NZ_TX + threadIdx.x; i < S.n_list; i += (int64_t)gridDim.x * NZ_TX)
-      (void)take(list[i]);
-  } else {
-    const void* X = imgs[img];
-    const int64_t n = npix[img];
-    for (int64_t i0 = (int64_t)blockIdx.x * NZ_TX; i0 < n; i0 += (int64_t)gridDim.x * NZ_TX) {
-      const int64_t i = i0 + threadIdx.x;
-      bool keep = false;
-      uint64_t key = 0;
-      if (i < n) {
-        const float x = nz_load<T>(X, i);
-        if (in_set(x, S)) {
-          key = KIND == 0 ? fkey(x) : (uint64_t)__double_as_longlong(fabs((double)x - S.m_new));
-          keep = take(key);
-        }
-      }
-      if (SRC == 1) {
-        // one atomic per wave for the list position of its kept keys
-        const uint64_t ball = __ballot(keep);
-        if (ball) {
-          const int lane = threadIdx.x & 63;
-          int64_t base = 0;
-          if (lane == 0)
-            base = (int64_t)atomicAdd((unsigned long long*)&st[img].n_list, (unsigned long long)__popcll(ball));
-          base = __shfl(base, 0);
-          if (keep) {
-            const int64_t pos = base + __popcll(ball & ((1ull << lane) - 1ull));
-            if (pos < NOISE_LIST_CAP) list[pos] = key;
-          }
-        }
-      }
-    }
+  const auto* p = global_ptr(static_cast<const T*>(imgs[img]));
+  uint32_t mine = 0;
+  for (int i = tid; i < NZ_SAMPLE; i += NZ_TX) {
+    // one pixel of each of NZ_SAMPLE runs, at a place that varies from run to run
+    const double fr = 0.6180339887498949 * i;
+    const int64_t at = (int64_t)(((double)i + (fr - floor(fr))) * ((double)n / NZ_SAMPLE));
+    const float x = (float)p[std::min<int64_t>(at, n - 1)];
+    const bool ok = __builtin_isfinite(x);
+    s[i] = ok ? fkey(x) : 0xffffffffu;
+    mine += ok ? 1u : 0u;
   }
-  __syncthreads();
-  uint32_t* g = hist + (int64_t)img * 2 * NZ_BINS;
-  for (int b = threadIdx.x; b < NZ_BINS; b += NZ_TX) {
-    if (h[0][b]) atomicAdd(&g[b], h[0][b]);
-    if (two && h[1][b]) atomicAdd(&g[NZ_BINS + b], h[1][b]);
-  }
-}
-
-// Choose the digit holding each target rank; one block per image.
-__global__ __launch_bounds__(NZ_TX) void k_noise_pick(NoiseState* st, uint32_t* hist, int lo, int kind) {
-  constexpr int PER = NZ_BINS / NZ_TX;
-  const int img = blockIdx.x;
-  NoiseState& S = st[img];
-  if (S.done) return;
-  __shared__ uint64_t part[NZ_TX];
-  __shared__ int dig[2];
-  __shared__ uint64_t below[2];
-  const bool two = S.prefix[0] != S.prefix[1];
-  uint32_t* g = hist + (int64_t)img * 2 * NZ_BINS;
-  const int tid = threadIdx.x;
-  for (int t = 0; t < 2; ++t) {
-    const uint32_t* H = g + (two ? t : 0) * NZ_BINS;
-    uint64_t loc[PER];
-    uint64_t s = 0;
-    for (int j = 0; j < PER; ++j) {
-      loc[j] = H[tid * PER + j];
-      s += loc[j];
-    }
-    part[tid] = s;
-    __syncthreads();
-    // inclusive scan (Hillis-Steele over 256 entries)
-    for (int o = 1; o < NZ_TX; o <<= 1) {
-      const uint64_t v = tid >= o ? part[tid - o] : 0;
-      __syncthreads();
-      part[tid] += v;
-      __syncthreads();
-    }
-    const uint64_t r = (uint64_t)S.rank[t];
-    const uint64_t start = part[tid] - s;
-    if (r >= start && r < part[tid]) {
-      uint64_t c = start;
-      for (int j = 0; j < PER; ++j) {
-        if (r < c + loc[j]) {
-          dig[t] = tid * PER + j;
-          below[t] = c;
-          break;
-        }
-        c += loc[j];
+  uint32_t ns_u;
+  (void)block_scan(mine, tmp, &ns_u);
+  sort_per<NZ_SAMPLE / NZ_TX>(s);
+  const int ns = (int)ns_u;
+  // all values below are the same in every thread
+  float m = 0.f, m_lo = 0.f, m_hi = 0.f, m0 = 0.f, d_lo = 0.f, d_hi = 0.f, sig = 0.f, sig_max = 0.f;
+  int lo = 0, hi = ns;
+  for (int it = 0; it < min(max_iter, NZ_SAMPLE_STEPS) && hi > lo; ++it) {
+    const int c = hi - lo;
+    m = 0.5f * fkey_value(s[lo + (c - 1) / 2]) + 0.5f * fkey_value(s[lo + c / 2]);
+    // first position in [lo, hi) whose value is >= v (strict: > v)
+    auto pos = [&](float v, bool strict) {
+      int a = lo, b = hi;
+      while (a < b) {
+        const int k = (a + b) >> 1;
+        const float x = fkey_value(s[k]);
+        if (strict ? x <= v : x < v) a = k + 1;
+        else b = k;
       }
+      return a;
+    };
+    // the smallest deviation of a member that covers half of them (every
+    // thread tries its members; the words of `best` take turns)
+    for (int i = lo + tid; i < hi; i += NZ_TX) {
+      const float dd = fabsf(fkey_value(s[i]) - m);
+      if (2 * (pos(m + dd, true) - pos(m - dd, false)) >= c) atomicMin(&best[it & 1], __float_as_uint(dd));
     }
     __syncthreads();
+    const uint32_t db = best[it & 1];
+    if (tid == 0) best[(it + 1) & 1] = 0xffffffffu;
+    const float d = db == 0xffffffffu ? 0.f : __uint_as_float(db);
+    sig = 1.4826f * d;
+    if (it == 0) {
+      m0 = m_lo = m_hi = m;
+      d_lo = d_hi = d;
+      sig_max = sig;
+    } else {
+      m_lo = fminf(m_lo, m);
+      m_hi = fmaxf(m_hi, m);
+      d_lo = fminf(d_lo, d);
+      d_hi = fmaxf(d_hi, d);
+      sig_max = fmaxf(sig_max, sig);
+    }
+    const float thr = (float)fmin(kappa * (double)sig, 3e38);
+    const int nl = pos(m - thr, false), nh = pos(m + thr, true);
+    if (nl == lo && nh == hi) break;
+    lo = nl;
+    hi = nh;
+    __syncthreads();  // the next step's word is reset
   }
-  for (int b = tid; b < 2 * NZ_BINS; b += NZ_TX) g[b] = 0u;
+  for (int i = tid; i < NZ_SAMPLE; i += NZ_TX) S.sample[i] = s[i];
   if (tid == 0) {
-    for (int t = 0; t < 2; ++t) {
-      S.prefix[t] |= (uint64_t)dig[t] << lo;
-      S.rank[t] -= (int64_t)below[t];
+    S.n_sample = ns;
+    NoiseMap M;
+    M.mc = m0;
+    if (!(sig > 0.f)) {  // over half of the sample is one value: some other scale
+      if (ns > 0) sig = (fkey_value(s[(int)(0.95f * (ns - 1))]) - fkey_value(s[(int)(0.05f * (ns - 1))])) / 3.f;
+      if (!(sig > 0.f) && ns > 0) sig = (fkey_value(s[ns - 1]) - fkey_value(s[0])) / 8.f;
+      if (!(sig > 0.f)) sig = fmaxf(fabsf(m0) * 1e-3f, 1e-30f);
     }
-    if (lo == 0) {
-      for (int t = 0; t < 2; ++t)
-        S.val[t] = kind == 0 ? fkey_value(S.prefix[t]) : __longlong_as_double((long long)S.prefix[t]);
-    }
+    // (a scale outside this range makes a useless map, never a wrong result)
+    sig = clampf(sig, 1e-30f, 1e30f);
+    sig_max = clampf(fmaxf(sig_max, sig), 1e-30f, 1e30f);
+    // a median of NZ_SAMPLE values is within 0.02 sigma (one standard error)
+    const float w = 0.1f * sig;
+    M.wc = clampf(fmaxf(m_hi - m0, m0 - m_lo), 0.f, 1e30f) + w;
+    M.q0 = fmaxf(d_lo - M.wc, 0.f);
+    M.q1 = fminf(d_hi, 1e30f) + M.wc;
+    M.q0 = fminf(M.q0, M.q1 - w);
+    M.T = fmaxf((float)fmin(1.1 * kappa, 8.0) * sig_max + M.wc, M.q1);
+    M.a0 = 0.5f * NZ_COARSE / M.T;
+    M.a1 = 0.5f * NZ_CENTER / M.wc;
+    M.a2 = 0.5f * (float)(NZ_BINS - 4 - NZ_COARSE - NZ_CENTER) / (M.q1 - M.q0);
+    M.off = 0.5f * (float)(NZ_BINS - 4) + 1.f;
+    S.map = M;
   }
 }
 
-// Median found: m_new, then select the deviations over the same set.
-__global__ void k_noise_mid(NoiseState* st, int n_img) {
-  const int i = blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= n_img) return;
-  NoiseState& S = st[i];
-  if (S.done) return;
-  S.m_new = 0.5 * (S.val[0] + S.val[1]);
-  S.n_list = 0;
-  begin_select(S);
-}
-
-__global__ void k_noise_sigma(NoiseState* st, int n_img, double kappa) {
-  const int i = blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= n_img) return;
-  NoiseState& S = st[i];
-  if (S.done) return;
-  const double mad = 0.5 * (S.val[0] + S.val[1]);
-  S.sigma = 1.4826 * mad;
-  S.thr_new = kappa * S.sigma;
-  S.n_used = S.n;
-  S.iter += 1;
-  S.n_new = 0;
-  S.changed = 0;
-}
-
-// Size of the clipped set and whether any pixel changed membership; also the
-// histogram of the first median digit (top 11 bits of the float key) over
-// the clipped set, which is the next step's set if the step is repeated.
 template <typename T>
-__global__ __launch_bounds__(NZ_TX) void k_noise_clip(const void* const* imgs, const int64_t* npix, NoiseState* st,
-                                                     uint32_t* hist) {
+__global__ __launch_bounds__(NZ_TX) void k_noise_bins(const void* const* imgs, const int64_t* npix, NoiseImage* st) {
   const int img = blockIdx.y;
-  const NoiseState S = st[img];
-  if (S.done) return;
   __shared__ uint32_t h[NZ_BINS];
   for (int b = threadIdx.x; b < NZ_BINS; b += NZ_TX) h[b] = 0u;
+  NoiseImage& S = st[img];
+  const NoiseMap M = S.map;
   __syncthreads();
-  const void* X = imgs[img];
-  const int64_t n = npix[img];
-  uint64_t c = 0;
-  int ch = 0;
-  for (int64_t i = (int64_t)blockIdx.x * NZ_TX + threadIdx.x; i < n; i += (int64_t)gridDim.x * NZ_TX) {
-    const float x = nz_load<T>(X, i);
-    if (!__builtin_isfinite(x)) continue;
-    const double xd = (double)x;
-    const bool k_old = fabs(xd - S.m_cur) <= S.thr_cur;
-    const bool k_new = fabs(xd - S.m_new) <= S.thr_new;
-    c += k_new ? 1u : 0u;
-    ch |= (k_old != k_new) ? 1 : 0;
-    if (k_new) atomicAdd(&h[(uint32_t)(fkey(x) >> 21) & (NZ_BINS - 1)], 1u);
-  }
-  for (int o = 32; o > 0; o >>= 1) {
-    c += __shfl_xor(c, o);
-    ch |= __shfl_xor(ch, o);
-  }
-  if ((threadIdx.x & 63) == 0) {
-    if (c) atomicAdd((unsigned long long*)&st[img].n_new, (unsigned long long)c);
-    if (ch) atomicOr(&st[img].changed, 1);
-  }
+  for_pixels<T>(imgs[img], npix[img], blockIdx.x, gridDim.x, [&](float x) {
+    if (__builtin_isfinite(x)) atomicAdd(&h[map_bin(M, x)], 1u);
+  });
   __syncthreads();
-  uint32_t* g = hist + (int64_t)img * 2 * NZ_BINS;
   for (int b = threadIdx.x; b < NZ_BINS; b += NZ_TX)
-    if (h[b]) atomicAdd(&g[b], h[b]);
+    if (h[b]) atomicAdd(&S.hist[b], h[b]);
 }
 
-__global__ void k_noise_update(NoiseState* st, int n_img, int max_iter) {
-  const int i = blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= n_img) return;
-  NoiseState& S = st[i];
-  if (S.done) return;
-  if (!S.changed || S.iter >= max_iter || S.n_new <= 0) {
-    S.done = 1;
-    return;
+// The iteration on the interpolated histogram (the first wavefront; 64
+// candidates per search round), marking the bins around each place visited;
+// then the table of marked bins.
+__global__ __launch_bounds__(NZ_TX) void k_noise_plan(NoiseImage* st, double kappa, int max_iter) {
+  const int tid = threadIdx.x, lane = tid & 63;
+  NoiseImage& S = st[blockIdx.x];
+  __shared__ uint32_t C[NZ_BINS + 1];
+  __shared__ uint32_t mark[NZ_BINS / 32];
+  __shared__ uint32_t tmp[NZ_WAVES];
+  constexpr int PER = NZ_BINS / NZ_TX;
+  uint32_t h[PER], sum = 0, N;
+#pragma unroll
+  for (int j = 0; j < PER; ++j) {
+    h[j] = S.hist[tid * PER + j];
+    sum += h[j];
   }
-  S.m_cur = S.m_new;
-  S.thr_cur = S.thr_new;
-  S.n = S.n_new;
-  begin_select(S);
+  uint32_t base = block_scan(sum, tmp, &N);
+#pragma unroll
+  for (int j = 0; j < PER; ++j) {
+    C[tid * PER + j] = base;
+    base += h[j];
+  }
+  if (tid == 0) C[NZ_BINS] = N;
+  for (int i = tid; i < NZ_BINS / 32; i += NZ_TX) mark[i] = 0u;
+  __syncthreads();
+  const NoiseMap M = S.map;
+  if (S.whole) {
+    if (tid == 0) mark[0] = 1u;
+  } else if (tid < 64 && N > 0) {
+    auto cum = [&](float g) {
+      const int b = pos_bin(g);
+      const double f = fmin(fmax((double)g - b, 0.0), 1.0);
+      return (double)C[b] + f * (double)(C[b + 1] - C[b]);
+    };
+    auto at = [&](float y) {  // pixels below mc + y
+      if (y >= M.T) return (double)N;
+      if (y <= -M.T) return 0.0;
+      return cum(map_pos(M, y));
+    };
+    // smallest y in [lo, hi] with test(y), to ~1e-9 of the range
+    auto find = [&](float lo, float hi, auto&& test) {
+      for (int r = 0; r < 5; ++r) {
+        const float step = (hi - lo) * (1.f / 64.f);
+        const uint64_t m = __ballot(test(lo + step * (float)(lane + 1)));
+        const int f = m ? __builtin_ctzll(m) : 63;
+        hi = lo + step * (float)(f + 1);
+        lo = lo + step * (float)f;
+      }
+      return hi;
+    };
+    auto set = [&](int b) {
+      if (b >= 0 && b < NZ_BINS) atomicOr(&mark[b >> 5], 1u << (b & 31));
+    };
+    auto mark_bins = [&](int b0, int b1) {  // lanes share the bins
+      for (int b = b0 + lane; b <= b1; b += 64) set(b);
+    };
+    auto mark_ranks = [&](double r, int e) {  // the bins of the pixels of ranks r - e .. r + e
+      if (lane <= 2 * e) {
+        const double q = fmin(fmax(floor(r) + (double)(lane - e), 0.0), (double)N - 1.0);
+        const uint32_t k = (uint32_t)q;
+        int a = 0, b = NZ_BINS;  // last bin whose count below is <= k
+        while (b - a > 1) {
+          const int c = (a + b) >> 1;
+          if (C[c] <= k) a = c;
+          else b = c;
+        }
+        set(a);
+      }
+    };
+    double L = 0.0, U = (double)N;
+    for (int it = 0; it < max_iter && U - L >= 0.5; ++it) {
+      const double n = U - L;
+      const double mid = L + 0.5 * n;
+      const float ym = find(-M.T, M.T, [&](float y) { return at(y) >= mid; });
+      mark_ranks(mid, 4);
+      const int bm = pos_bin(map_pos(M, ym));
+      mark_bins(bm - 1, bm + 1);
+      const float d = find(0.f, 2.f * M.T, [&](float v) {
+        return fmin(at(ym + v), U) - fmax(at(ym - v), L) >= 0.5 * n;
+      });
+      const float thr = (float)fmin(1.4826 * kappa * (double)d, 3e38);
+      if (lane == 0 && it < NZ_DHAT) S.dhat[it] = d;
+      // m and d are good to a bin or two here; the cuts move kappa * 1.4826 times as far as d
+      const float cut = (float)fmin(1.4826 * kappa, 1e3) * 1.5f / (M.a2 + M.a0) + 1.5f / (M.a1 + M.a0);
+#pragma unroll
+      for (int sgn = -1; sgn <= 1; sgn += 2) {
+        const float yd = ym + sgn * d, yc = ym + sgn * thr;
+        const int bd = pos_bin(map_pos(M, yd));
+        mark_bins(bd - 2, bd + 2);
+        mark_ranks(at(yd), 4);
+        mark_bins(pos_bin(map_pos(M, yc - cut)) - 1, pos_bin(map_pos(M, yc + cut)) + 1);
+      }
+      const double nl = at(ym - thr), nu = at(ym + thr);
+      const bool same = fabs(nl - L) < 0.25 && fabs(nu - U) < 0.25;
+      L = nl;
+      U = nu;
+      if (same) break;
+    }
+  }
+  __syncthreads();
+  // table of the marked bins; all are listed while that fits
+  const uint32_t bits = (mark[tid * PER >> 5] >> ((tid * PER) & 31)) & ((1u << PER) - 1u);
+  uint32_t n_tab, total;
+  const uint32_t first = block_scan((uint32_t)__builtin_popcount(bits), tmp, &n_tab);
+  uint32_t c = 0;
+#pragma unroll
+  for (int j = 0; j < PER; ++j)
+    if (bits >> j & 1u) c += std::min<uint32_t>(h[j], NZ_LIST + 1u);
+  (void)block_scan(c, tmp, &total);
+  const bool all = total <= (uint32_t)NZ_LIST;
+  const int ns = S.n_sample;
+  uint32_t k = first;
+#pragma unroll
+  for (int j = 0; j < PER; ++j) {
+    uint16_t mode = 0;
+    if (bits >> j & 1u) {
+      if (k < (uint32_t)NZ_TAB) {
+        const int b = tid * PER + j;
+        uint32_t heavy = 0;
+        mode = 0xffffu;
+        if (!all && h[j] > (uint32_t)NZ_LIST / 64) {
+          // too full to list: the most frequent sample value in it is left
+          // out; a bin without a value that fills most of it stays unlisted
+          int lo = 0, hi = ns;
+          while (lo < hi) {
+            const int q = (lo + hi) >> 1;
+            if (map_bin(M, fkey_value(S.sample[q])) < b) lo = q + 1;
+            else hi = q;
+          }
+          int run = 0, most = 0, n_in = 0;
+          for (int q = lo; q < ns && map_bin(M, fkey_value(S.sample[q])) == b; ++q, ++n_in) {
+            run = q > lo && S.sample[q] == S.sample[q - 1] ? run + 1 : 1;
+            if (run > most) {
+              most = run;
+              heavy = S.sample[q];
+            }
+          }
+          const bool use = 10 * most >= 9 * n_in && n_in > 0;
+          mode = use ? (uint16_t)(k + 1) : (uint16_t)0;
+          if (!use) heavy = 0;
+        }
+        S.bin[k] = (uint32_t)b;
+        S.below[k] = C[b];
+        S.cnt[k] = h[j];
+        S.heavy[k] = heavy;
+      }
+      ++k;
+    }
+    S.mode[tid * PER + j] = mode;
+  }
+  if (tid == 0) {
+    S.n = N;
+    S.n_tab = n_tab <= (uint32_t)NZ_TAB ? (int32_t)n_tab : -1;
+  }
 }
 
-__global__ void k_noise_out(const NoiseState* st, int n_img, double* sigma, int64_t* n_used, int32_t* iters,
-                            ExpMeta* meta) {
-  const int i = blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= n_img) return;
-  if (sigma) sigma[i] = st[i].sigma;
-  if (n_used) n_used[i] = st[i].n_used;
-  if (iters) iters[i] = st[i].iter;
+// The values of the marked bins.
+template <typename T>
+__global__ __launch_bounds__(NZ_TX) void k_noise_collect(const void* const* imgs, const int64_t* npix,
+                                                         NoiseImage* st) {
+  const int img = blockIdx.y;
+  NoiseImage& S = st[img];
+  if (S.n_tab < 0) return;
+  __shared__ uint16_t mode[NZ_BINS];
+  __shared__ uint32_t buf[NZ_STAGE];
+  __shared__ unsigned int cnt, base;
+  for (int b = threadIdx.x; b < NZ_BINS / 2; b += NZ_TX)
+    reinterpret_cast<uint32_t*>(mode)[b] = reinterpret_cast<const uint32_t*>(S.mode)[b];
+  if (threadIdx.x == 0) cnt = 0u;
+  const NoiseMap M = S.map;
+  __syncthreads();
+  for_pixels<T>(imgs[img], npix[img], blockIdx.x, gridDim.x, [&](float x) {
+    if (!__builtin_isfinite(x)) return;
+    const uint16_t md = mode[map_bin(M, x)];
+    if (md == 0) return;
+    const uint32_t key = fkey(x);
+    if (md != 0xffffu && key == S.heavy[md - 1]) return;
+    const unsigned int i = atomicAdd(&cnt, 1u);
+    if (i < (unsigned)NZ_STAGE) {
+      buf[i] = key;
+    } else {  // staging full: append directly
+      const unsigned int g = atomicAdd(&S.n_list, 1u);
+      if (g < (unsigned)NZ_LIST) S.list[g] = key;
+    }
+  });
+  __syncthreads();
+  const unsigned int c = std::min<unsigned>(cnt, NZ_STAGE);
+  if (threadIdx.x == 0) base = c ? atomicAdd(&S.n_list, c) : 0u;
+  __syncthreads();
+  for (unsigned int i = threadIdx.x; i < c; i += NZ_TX)
+    if (base + i < (unsigned)NZ_LIST) S.list[base + i] = buf[i];
+}
+
+// Result of one image.
+struct NoiseResult {
+  double sigma;
+  int64_t used;
+  int iter;
+};
+
+// The iteration by radix selection over the pixels (11-bit digits of the
+// float key, then of the bits of |x - m|), one workgroup; for images whose
+// places the plan missed.  h: 2 x 2048 words of LDS.
+template <typename T>
+__device__ __noinline__ NoiseResult noise_from_pixels(const void* img, int64_t n_pix, double kappa, int max_iter,
+                                                      uint32_t* h, uint32_t* tmp, uint64_t* sh) {
+  constexpr int B = 2048;
+  const int tid = threadIdx.x;
+  double m = 0.0, thr = __builtin_inf();
+  auto count = [&](double mm, double tt) {
+    uint32_t c = 0, total;
+    for_pixels<T, 8>(img, n_pix, 0, 1, [&](float x) {
+      c += __builtin_isfinite(x) && fabs((double)x - mm) <= tt ? 1u : 0u;
+    });
+    (void)block_scan(c, tmp, &total);
+    return (int64_t)total;
+  };
+  // the two middle keys of the set (m, thr): of x, or of |x - mn|
+  auto middle = [&](int64_t n, bool dev, double mn, double out[2]) {
+    const int lo_x[3] = {21, 10, 0}, lo_d[6] = {52, 41, 30, 19, 8, 0};
+    uint64_t pre[2] = {0, 0};
+    int64_t rank[2] = {(n - 1) / 2, n / 2};
+    int hi = dev ? 63 : 32;
+    for (int q = 0; q < (dev ? 6 : 3); ++q) {
+      const int lo = dev ? lo_d[q] : lo_x[q];
+      const uint32_t mask = (1u << (hi - lo)) - 1u;
+      const bool two = pre[0] != pre[1];
+      for (int b = tid; b < 2 * B; b += NZ_TX) h[b] = 0u;
+      __syncthreads();
+      for_pixels<T, 8>(img, n_pix, 0, 1, [&](float x) {
+        if (!(__builtin_isfinite(x) && fabs((double)x - m) <= thr)) return;
+        const uint64_t key = dev ? (uint64_t)__double_as_longlong(fabs((double)x - mn)) : (uint64_t)fkey(x);
+        const uint32_t d = (uint32_t)(key >> lo) & mask;
+        if (key >> hi == pre[0] >> hi) atomicAdd(&h[d], 1u);
+        if (two && key >> hi == pre[1] >> hi) atomicAdd(&h[B + d], 1u);
+      });
+      __syncthreads();
+      for (int t = 0; t < 2; ++t) {
+        const uint32_t* H = h + (two && t ? B : 0);
+        const uint32_t c0 = H[2 * tid], c1 = H[2 * tid + 1];
+        uint32_t total;
+        const uint32_t e = block_scan(c0 + c1, tmp, &total);
+        const uint32_t r = (uint32_t)rank[t];
+        if (r >= e && r < e + c0 + c1) {
+          const bool second = r >= e + c0;
+          sh[0] = (uint64_t)(2 * tid + (second ? 1 : 0));
+          sh[1] = e + (second ? c0 : 0u);
+        }
+        __syncthreads();
+        pre[t] |= sh[0] << lo;
+        rank[t] -= (int64_t)sh[1];
+        __syncthreads();
+      }
+      hi = lo;
+    }
+    for (int t = 0; t < 2; ++t)
+      out[t] = dev ? __longlong_as_double((long long)pre[t]) : (double)fkey_value((uint32_t)pre[t]);
+  };
+  NoiseResult R{__builtin_nan(""), 0, 0};
+  int64_t n = count(m, thr);
+  while (n > 0) {
+    double v[2];
+    middle(n, false, 0.0, v);
+    const double mn = 0.5 * (v[0] + v[1]);
+    middle(n, true, mn, v);
+    R.sigma = 1.4826 * (0.5 * (v[0] + v[1]));
+    R.used = n;
+    R.iter++;
+    const double tn = kappa * R.sigma;
+    uint32_t c = 0, changed;  // pixels in one of the two sets only
+    for_pixels<T, 8>(img, n_pix, 0, 1, [&](float x) {
+      if (__builtin_isfinite(x)) c += (fabs((double)x - m) <= thr) != (fabs((double)x - mn) <= tn) ? 1u : 0u;
+    });
+    (void)block_scan(c, tmp, &changed);
+    m = mn;
+    thr = tn;
+    if (!changed || R.iter >= max_iter) break;
+    n = count(m, thr);
+  }
+  return R;
+}
+
+template <typename T>
+__global__ __launch_bounds__(NZ_TX) void k_noise_solve(const void* const* imgs, const int64_t* npix, NoiseImage* st,
+                                                       double kappa, int max_iter, int n_img, double* sigma,
+                                                       int64_t* n_used, int32_t* iters, ExpMeta* meta) {
+  const int img = blockIdx.x, tid = threadIdx.x;
+  NoiseImage& S = st[img];
+  __shared__ uint32_t A[NZ_LIST];  // the listed keys, sorted
+  __shared__ float elo[NZ_TAB], ehi[NZ_TAB], heavy[NZ_TAB];  // first value of a bin and after it; value not listed
+  __shared__ uint32_t below[NZ_TAB], cnt[NZ_TAB], off[NZ_TAB];
+  __shared__ uint32_t n_heavy[NZ_TAB];  // pixels of the value that is not listed
+  __shared__ uint8_t known[NZ_TAB];
+  __shared__ uint32_t tmp[NZ_WAVES];
+  __shared__ unsigned long long dmin[2];
+  __shared__ uint32_t q_rank[16];
+  __shared__ int q_bad;
+  __shared__ uint64_t sh[2];
+  const uint32_t N = S.n;
+  const int nt = S.n_tab;
+  bool good = nt >= 0 && S.n_list <= (uint32_t)NZ_LIST;
+  NoiseResult R{__builtin_nan(""), 0, 0};
+  if (good && N > 0) {
+    const NoiseMap M = S.map;
+    const int n_list = (int)S.n_list;
+    int per = 1;
+    while (per * NZ_TX < n_list) per <<= 1;
+    for (int i = tid; i < per * NZ_TX; i += NZ_TX) A[i] = i < n_list ? S.list[i] : 0xffffffffu;
+    switch (per) {
+      case 1: sort_per<1>(A); break;
+      case 2: sort_per<2>(A); break;
+      case 4: sort_per<4>(A); break;
+      case 8: sort_per<8>(A); break;
+      case 16: sort_per<16>(A); break;
+      default: sort_per<32>(A); break;
+    }
+    if (tid == 0) q_bad = 0;
+    if (tid < nt) {
+      const int b = (int)S.bin[tid];
+      // key of the first value with bin >= v (+inf's when there is none)
+      auto edge = [&](int v) {
+        uint32_t lo = fkey(-3.4028234664e38f), hi = fkey(3.4028234664e38f) + 1u;
+        while (lo < hi) {
+          const uint32_t k = lo + (hi - lo) / 2;
+          if (map_bin(M, fkey_value(k)) >= v) hi = k;
+          else lo = k + 1;
+        }
+        return lo;
+      };
+      auto first = [&](uint32_t key) {  // listed keys below `key`
+        int lo = 0, hi = n_list;
+        while (lo < hi) {
+          const int k = (lo + hi) >> 1;
+          if (A[k] < key) lo = k + 1;
+          else hi = k;
+        }
+        return lo;
+      };
+      const uint32_t k0 = S.whole ? fkey(-3.4028234664e38f) : edge(b);
+      const uint32_t k1 = S.whole ? fkey(3.4028234664e38f) + 1u : edge(b + 1);
+      elo[tid] = fkey_value(k0);
+      ehi[tid] = fkey_value(k1);
+      below[tid] = S.below[tid];
+      cnt[tid] = S.cnt[tid];
+      const int a0 = first(k0), listed = first(k1) - a0;
+      off[tid] = (uint32_t)a0;
+      const uint32_t rest = S.cnt[tid] - (uint32_t)listed;
+      n_heavy[tid] = rest;
+      heavy[tid] = fkey_value(S.heavy[tid]);
+      known[tid] = rest == 0 || S.heavy[tid] != 0u;
+    }
+    __syncthreads();
+    // The pixels for which `pred` holds, pred true for a prefix of the sorted
+    // pixels: their number, and exact = false when it ends among pixels that
+    // are not known.
+    auto rank_of = [&](auto&& pred, bool& exact) -> uint32_t {
+      int a = 0, b = nt;  // first entry whose first value fails
+      while (a < b) {
+        const int k = (a + b) >> 1;
+        if (pred(elo[k])) a = k + 1;
+        else b = k;
+      }
+      const int j = a - 1;
+      if (j < 0) {
+        exact &= (nt > 0 ? below[0] : N) == 0u;
+        return 0u;
+      }
+      const uint32_t end = below[j] + cnt[j];
+      if (pred(ehi[j])) {  // past this bin, before the next marked one
+        exact &= (j + 1 < nt ? below[j + 1] : N) == end;
+        return end;
+      }
+      exact &= known[j] != 0;
+      int l = 0, r = (int)(cnt[j] - n_heavy[j]);
+      const uint32_t* q = A + off[j];
+      while (l < r) {
+        const int k = (l + r) >> 1;
+        if (pred(fkey_value(q[k]))) l = k + 1;
+        else r = k;
+      }
+      return below[j] + (uint32_t)l + (n_heavy[j] && pred(heavy[j]) ? n_heavy[j] : 0u);
+    };
+    // The value of the pixel of rank r.
+    auto value_at = [&](uint32_t r, bool& exact) -> double {
+      int a = 0, b = nt;  // last entry with below <= r (entries of empty bins come before the one that holds r)
+      while (a < b) {
+        const int k = (a + b) >> 1;
+        if (below[k] <= r) a = k + 1;
+        else b = k;
+      }
+      const int j = a - 1;
+      if (j < 0 || r >= below[j] + cnt[j] || !known[j]) {
+        exact = false;
+        return 0.0;
+      }
+      r -= below[j];
+      const uint32_t* q = A + off[j];
+      if (n_heavy[j]) {
+        int l = 0, e = (int)(cnt[j] - n_heavy[j]);  // listed values below the heavy one
+        while (l < e) {
+          const int k = (l + e) >> 1;
+          if (fkey_value(q[k]) < heavy[j]) l = k + 1;
+          else e = k;
+        }
+        if (r >= (uint32_t)l) {
+          if (r < (uint32_t)l + n_heavy[j]) return (double)heavy[j];
+          r -= n_heavy[j];
+        }
+      }
+      return (double)fkey_value(q[r]);
+    };
+    // pixels up to m + D (right) or below m - D
+    auto rank_at = [&](double m, double D, bool right, bool& exact) {
+      return rank_of([&](float x) {
+        const double y = (double)x;
+        return right ? y < m || y - m <= D : y < m && m - y > D;
+      }, exact);
+    };
+    uint32_t L = 0, U = N;
+    while (U > L) {
+      const uint32_t n = U - L;
+      const uint32_t k[2] = {(n - 1) / 2, n / 2};
+      bool exact = true;
+      const double m = 0.5 * (value_at(L + k[0], exact) + value_at(L + k[1], exact));
+      // the middle deviations are deviations of listed (or heavy) values: the
+      // smallest one that covers more than k pixels of the set
+      if (tid < 2) dmin[tid] = ~0ull;
+      __syncthreads();
+      const float dh = R.iter < NZ_DHAT ? S.dhat[R.iter] : 0.f;
+      const double slack = 0.03 * (double)dh + 2.0 / (double)M.a0;  // the plan's value is good to a bin or two
+      const double near0 = dh > 0.f ? dh - slack : 0.0, near1 = dh > 0.f ? dh + slack : __builtin_inf();
+      for (int i = tid; i < n_list + nt; i += NZ_TX) {
+        const bool hv = i >= n_list;
+        if (hv && !n_heavy[i - n_list]) continue;
+        const double x = (double)(hv ? heavy[i - n_list] : fkey_value(A[i]));
+        const double D = fabs(x - m);
+        if (!(D >= near0 && D <= near1)) continue;
+        bool e = true;
+        const uint32_t hi = std::min(rank_at(m, D, true, e), U), lo = std::max(rank_at(m, D, false, e), L);
+        const uint32_t c = hi > lo ? hi - lo : 0u;
+        for (int t = 0; t < 2; ++t)
+          if (c > k[t]) atomicMin(&dmin[t], (unsigned long long)__double_as_longlong(D));
+      }
+      __syncthreads();
+      const double dev[2] = {__longlong_as_double((long long)dmin[0]), __longlong_as_double((long long)dmin[1])};
+      exact &= dmin[0] != ~0ull && dmin[1] != ~0ull;
+      if (!exact) {
+        good = false;
+        break;
+      }
+      const double sigma_new = 1.4826 * (0.5 * (dev[0] + dev[1]));
+      const double thr = kappa * sigma_new;
+      // proof: the pixels within each deviation, and within the next smaller
+      // number, counted exactly; and the cuts (ten ranks, one per lane)
+      if (tid < 10) {
+        bool e = true;
+        const int t = tid >> 2;
+        const uint64_t bits = t < 2 ? dmin[t] : (uint64_t)__double_as_longlong(thr);
+        const bool prev = t < 2 && (tid & 2);
+        // (below zero: no deviation, nothing to count)
+        const double D = __longlong_as_double((long long)(prev && bits > 0 ? bits - 1 : bits));
+        q_rank[tid] = rank_at(m, D, (tid & 1) != 0, e);
+        if (!e) q_bad = 1;
+      }
+      __syncthreads();
+      good = q_bad == 0;
+      auto inside = [&](int q) -> uint32_t {
+        const uint32_t hi = std::min(q_rank[q + 1], U), lo = std::max(q_rank[q], L);
+        return hi > lo ? hi - lo : 0u;
+      };
+      for (int t = 0; t < 2; ++t) {
+        good &= inside(4 * t) > k[t];
+        if (dmin[t] > 0) good &= inside(4 * t + 2) <= k[t];
+      }
+      const uint32_t l2 = q_rank[8], u2 = q_rank[9];
+      if (!good) break;
+      R.sigma = sigma_new;
+      R.used = n;
+      R.iter++;
+      if ((l2 == L && u2 == U) || R.iter >= max_iter) break;
+      L = l2;
+      U = u2;
+      __syncthreads();  // dmin and q_rank are read
+    }
+  }
+  // (every thread computed the same `good` and R)
+  if (!good) {
+    __syncthreads();
+    R = noise_from_pixels<T>(imgs[img], npix[img], kappa, max_iter, A, tmp, sh);
+  }
+  if (tid == 0) {
+    if (sigma) sigma[img] = R.sigma;
+    if (n_used) n_used[img] = R.used;
+    if (iters) iters[img] = R.iter;
+  }
   if (meta) {
     // meta is in epoch order; meta[i].src names the image
-    const double s = st[meta[i].src].sigma;
-    meta[i].vs = (float)(s * s);
+    for (int i = tid; i < n_img; i += NZ_TX)
+      if (meta[i].src == img) meta[i].vs = (float)(R.sigma * R.sigma);
   }
 }
 
-size_t noise_scratch_bytes(int n_img) {
-  return (sizeof(NoiseState) + 2 * NZ_BINS * sizeof(uint32_t) + NOISE_LIST_CAP * sizeof(uint64_t)) * (size_t)n_img;
-}
+size_t noise_scratch_bytes(int n_img) { return sizeof(NoiseImage) * (size_t)n_img; }
 
 template <typename T>
 static hipError_t noise_t(const void* const* d_imgs, const int64_t* d_npix, int64_t max_pix, int n_img, double kappa,
                           int max_iter, void* scratch, double* d_sigma, int64_t* d_used, int32_t* d_iters,
                           ExpMeta* d_meta, hipStream_t s) {
-  NoiseState* st = static_cast<NoiseState*>(scratch);
-  uint32_t* hist = reinterpret_cast<uint32_t*>(static_cast<char*>(scratch) + sizeof(NoiseState) * (size_t)n_img);
-  uint64_t* lists = reinterpret_cast<uint64_t*>(reinterpret_cast<char*>(hist) +
-                                                2 * NZ_BINS * sizeof(uint32_t) * (size_t)n_img);
-  const int64_t nh = (int64_t)n_img * 2 * NZ_BINS;
-  const unsigned g1 = (unsigned)((std::max<int64_t>(nh, n_img) + 255) / 256);
-  const unsigned gi = (unsigned)((n_img + 63) / 64);
-  // 64 pixels per thread per pass, at most 1024 blocks per image
-  const unsigned bx = (unsigned)std::min<int64_t>(1024, std::max<int64_t>(1, (max_pix + NZ_TX * 64 - 1) / (NZ_TX * 64)));
-  const dim3 grid(bx, (unsigned)n_img);
-  hipLaunchKernelGGL(k_noise_init, dim3(g1), dim3(256), 0, s, st, hist, n_img);
-  hipLaunchKernelGGL(k_noise_count<T>, grid, dim3(NZ_TX), 0, s, d_imgs, d_npix, st);
-  hipLaunchKernelGGL(k_noise_begin, dim3(gi), dim3(64), 0, s, st, n_img);
-  static const int lo_x[3] = {21, 10, 0}, nb_x[3] = {11, 11, 10};
-  static const int lo_d[6] = {52, 41, 30, 19, 8, 0}, nb_d[6] = {11, 11, 11, 11, 11, 8};
-  // the first step's first median digit; later steps get it from the clip pass
-  hipLaunchKernelGGL((k_noise_hist<T, 0, 0>), grid, dim3(NZ_TX), 0, s, d_imgs, d_npix, st, hist, lists, lo_x[0],
-                     nb_x[0]);
-  for (int it = 0; it < max_iter; ++it) {
-    hipLaunchKernelGGL(k_noise_pick, dim3(n_img), dim3(NZ_TX), 0, s, st, hist, lo_x[0], 0);
-    for (int p = 1; p < 3; ++p) {
-      hipLaunchKernelGGL((k_noise_hist<T, 0, 0>), grid, dim3(NZ_TX), 0, s, d_imgs, d_npix, st, hist, lists, lo_x[p],
-                         nb_x[p]);
-      hipLaunchKernelGGL(k_noise_pick, dim3(n_img), dim3(NZ_TX), 0, s, st, hist, lo_x[p], 0);
-    }
-    hipLaunchKernelGGL(k_noise_mid, dim3(gi), dim3(64), 0, s, st, n_img);
-    for (int p = 0; p < 6; ++p) {
-      if (p < 2)
-        hipLaunchKernelGGL((k_noise_hist<T, 1, 0>), grid, dim3(NZ_TX), 0, s, d_imgs, d_npix, st, hist, lists, lo_d[p],
-                           nb_d[p]);
-      else if (p == 2)
-        hipLaunchKernelGGL((k_noise_hist<T, 1, 1>), grid, dim3(NZ_TX), 0, s, d_imgs, d_npix, st, hist, lists, lo_d[p],
-                           nb_d[p]);
-      else
-        hipLaunchKernelGGL((k_noise_hist<T, 1, 2>), grid, dim3(NZ_TX), 0, s, d_imgs, d_npix, st, hist, lists, lo_d[p],
-                           nb_d[p]);
-      hipLaunchKernelGGL(k_noise_pick, dim3(n_img), dim3(NZ_TX), 0, s, st, hist, lo_d[p], 1);
-    }
-    hipLaunchKernelGGL(k_noise_sigma, dim3(gi), dim3(64), 0, s, st, n_img, kappa);
-    hipLaunchKernelGGL(k_noise_clip<T>, grid, dim3(NZ_TX), 0, s, d_imgs, d_npix, st, hist);
-    hipLaunchKernelGGL(k_noise_update, dim3(gi), dim3(64), 0, s, st, n_img, max_iter);
-  }
-  hipLaunchKernelGGL(k_noise_out, dim3(gi), dim3(64), 0, s, st, n_img, d_sigma, d_used, d_iters, d_meta);
+  NoiseImage* st = static_cast<NoiseImage*>(scratch);
+  // about four workgroups per resident one (two fit a CU) for balance, while
+  // each has 64 pixels per thread or more: its histogram costs 16384 adds
+  const int64_t per = std::max<int64_t>(1, 2048 / n_img);
+  const unsigned bx = (unsigned)std::min<int64_t>(per, std::max<int64_t>(1, (max_pix + NZ_TX * 64 - 1) / (NZ_TX * 64)));
+  const dim3 grid(bx, (unsigned)n_img), blk(NZ_TX);
+  hipLaunchKernelGGL(k_noise_sample<T>, dim3(n_img), blk, 0, s, d_imgs, d_npix, st, kappa, max_iter);
+  hipLaunchKernelGGL(k_noise_bins<T>, grid, blk, 0, s, d_imgs, d_npix, st);
+  hipLaunchKernelGGL(k_noise_plan, dim3(n_img), blk, 0, s, st, kappa, max_iter);
+  hipLaunchKernelGGL(k_noise_collect<T>, grid, blk, 0, s, d_imgs, d_npix, st);
+  hipLaunchKernelGGL(k_noise_solve<T>, dim3(n_img), blk, 0, s, d_imgs, d_npix, st, kappa, max_iter, n_img, d_sigma,
+                     d_used, d_iters, d_meta);
   return hipGetLastError();
 }
 
