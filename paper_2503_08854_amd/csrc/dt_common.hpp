@@ -74,23 +74,31 @@ __device__ __forceinline__ T global_load(const T* p, int64_t i) {
 // One tile of the matched-filter pre-pass.
 struct PrepTile {
   int32_t e;       // exposure (sorted index)
-  int32_t x0, y0;  // tile origin
-  int32_t pad;
+  int32_t x0, y0;  // tile origin (x0 even)
+  int32_t ny;      // output rows
 };
 
-constexpr int PREP_TX = 256;  // tile width (output pixels) = threads per workgroup
-constexpr int PREP_TY = 128;  // tile height (output rows streamed per workgroup)
-constexpr int PREP_DEPTH = 4; // input rows each thread keeps in flight
+constexpr int PREP_TY = 128;      // output rows a wavefront streams, about; down to
+constexpr int PREP_TY_MIN = 16;   // this in patches of fewer than
+constexpr int PREP_TILES = 1536;  // tiles (the card holds 3072 wavefronts of this kernel)
+constexpr int PREP_DEPTH = 4; // input rows each lane keeps in flight
+// A lane holds `groups` pairs of columns (one where the partial sums of two
+// would leave a single wavefront per SIMD); a wavefront's 128 x groups input
+// columns start prep_lead(R) columns before its prep_width(R) output columns.
+constexpr int prep_groups(int R) { return R <= 6 ? 2 : 1; }
+constexpr int prep_lead(int R) { return (R + 1) & ~1; }
+constexpr int prep_width(int R) { return (128 * prep_groups(R) - prep_lead(R) - R) & ~1; }
 constexpr int PREP_RMAX = 12; // largest stamp half-width supported (FWHM <= 8 px gives R = 11)
 
 // Launchers (defined in the .hip files; all enqueue on `s`).
 hipError_t launch_exposure_prep(const dt_exposure* d_in, const int64_t* d_plane_off, const int32_t* d_src,
                                 const int32_t* d_R, int n, ExpMeta* d_out, hipStream_t s);
 // Tiles are grouped by stamp half-width: group gi covers tiles
-// [group_off[gi], group_off[gi+1]) whose exposures all have R = group_R[gi].
+// [group_off[gi], group_off[gi+1]) whose exposures all have R = group_R[gi];
+// group_R 0: the images one column wide, of any half-width.
 hipError_t launch_prepass(const ExpMeta* d_meta, const PrepTile* d_tiles, const int64_t* group_off,
                           const int32_t* group_R, int n_groups, const void* const* d_flux,
-                          const void* const* d_var, dt_dtype dtype, float2* d_planes, hipStream_t s);
+                          const void* const* d_var, bool has_var, dt_dtype dtype, float2* d_planes, hipStream_t s);
 
 // Stamp half-width for a PSF FWHM: R = ceil(3 sigma), sigma = FWHM / (2 sqrt(2 ln 2)).
 inline int stamp_radius(double fwhm) {

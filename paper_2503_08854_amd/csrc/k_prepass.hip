@@ -136,36 +136,79 @@ hipError_t launch_exposure_prep(const dt_exposure* d_in, const int64_t* d_plane_
 }
 
 // ----------------------------------------------------------------------------
-// Matched-filter planes.  One workgroup of PREP_TX threads per PREP_TX-wide
-// column strip and PREP_TY output rows.  The workgroup streams the input rows
-// y0 - R .. y0 + TY + R - 1: each row is loaded once (coalesced, the next row
-// prefetched into registers), turned into {D w, w} with w = 1/V (0 where the
-// pixel is masked or off the image) in a double-buffered LDS row, filtered
-// along x with the 1-D Gaussian, and pushed into a (2R+1)-row register window
-// per column that is filtered along y to give one output row.  R is a
-// template parameter so the window lives in registers.
+// Matched-filter planes.  One wavefront per strip of prep_width(R) output
+// columns and up to a few hundred output rows; wavefronts share nothing, so
+// there is no barrier.  It streams the input rows y0 - R .. y0 + ny + R - 1:
+// each lane holds two adjacent columns (two groups of them up to R = 6, so
+// 256 input columns per row), loads them with one access per image and
+// group, PREP_DEPTH rows ahead, turns them into {D w, w} with w = 1/V (0
+// where the pixel is masked or off the image) in an LDS row, filters along x
+// for its output columns (16-byte LDS reads, two pixels each) and pushes the
+// result into a chain of 2R+1 partial sums per column: partial sum j of an
+// output row becomes partial sum j + 1 with the next input row's term, so the
+// filter along y is one fused multiply-add per tap and no register is moved.
+// Sums run in the order of the taps, as the definition's.
+//
+// HBM bounds it: 57 vector instructions per pixel at R = 4 (120 with one
+// column per thread, of them 18 moves of the row window and 12 of rows in
+// flight, each of which waited for the newest row).  120 FP16 4096^2 images
+// (24 GB): 4.6-5.5 ms by where the buffers lie (4.4-5.3 TB/s; a device copy
+// reaches 4.8), 9.6 ms before; 57 of 1031 x 773: 0.15 ms (3.7 TB/s), 0.38
+// before; 200 FP32 2048^2 (13.4 GB): 2.55-3.0 ms, 2.95 before.  Four rows in
+// flight measured as six and three do.
 // ----------------------------------------------------------------------------
 // The image pointers come from a device array, so they are generic to the
 // compiler; reading through global pointers keeps these loads off the LDS
 // counter (a generic load is counted with the LDS operations, so the waits
 // for a row's LDS reads would also wait for rows still in flight).
+//
+// Two adjacent pixels of a row, loaded together at the element's alignment
+// (image rows of odd width start anywhere).  use(): the pair as it is
+// filtered: `second` (all ones or zero per lane) puts the second pixel first,
+// `kill[j]` of all ones makes pixel j a NaN.
 template <typename T>
-__device__ __forceinline__ float load_px(const void* p, int64_t k);
+struct Pair;
 template <>
-__device__ __forceinline__ float load_px<float>(const void* p, int64_t k) {
-  return __builtin_nontemporal_load(global_ptr(static_cast<const float*>(p)) + k);
-}
+struct Pair<float> {
+  typedef uint32_t vec __attribute__((ext_vector_type(2), aligned(4)));
+  vec v;
+  __device__ __forceinline__ void load(const float* p, int c) {
+    v = __builtin_nontemporal_load((const __attribute__((address_space(1))) vec*)(global_ptr(p) + c));
+  }
+  // {pixel 0, pixel 1}
+  __device__ __forceinline__ float2 use(bool second, uint32_t kill0, uint32_t kill1) const {
+    return make_float2(__uint_as_float((second ? v[1] : v[0]) | kill0), __uint_as_float(v[1] | kill1));
+  }
+};
 template <>
-__device__ __forceinline__ float load_px<_Float16>(const void* p, int64_t k) {
-  return (float)__builtin_nontemporal_load(global_ptr(static_cast<const _Float16*>(p)) + k);
+struct Pair<_Float16> {
+  typedef uint32_t word __attribute__((aligned(2)));
+  uint32_t v;
+  __device__ __forceinline__ void load(const _Float16* p, int c) {
+    v = __builtin_nontemporal_load((const __attribute__((address_space(1))) word*)(global_ptr(p) + c));
+  }
+  __device__ __forceinline__ float2 use(bool second, uint32_t kill0, uint32_t kill1) const {
+    const uint32_t u = (second ? v >> 16 : v) | (kill0 & 0xffffu) | (kill1 << 16);
+    return make_float2((float)__builtin_bit_cast(_Float16, (uint16_t)(u & 0xffffu)),
+                       (float)__builtin_bit_cast(_Float16, (uint16_t)(u >> 16)));
+  }
+};
+
+// {D w, w}, w = 1/V; zeros unless D is finite and V finite and positive
+// (selected, not branched: masked pixels are rare and scattered).
+__device__ __forceinline__ float2 weight_pair(float d, float v) {
+  constexpr int FINITE = 0x1f8, POSITIVE = 0x180;  // v_cmp_class: any finite value; positive normal or denormal
+  const bool ok = __builtin_amdgcn_classf(d, FINITE) & __builtin_amdgcn_classf(v, POSITIVE);
+  const float w = 1.0f / v;
+  return make_float2(ok ? d * w : 0.f, ok ? w : 0.f);
 }
 
-__device__ __forceinline__ float2 weight_pair(float d, float v) {
-  if (__builtin_isfinite(d) && __builtin_isfinite(v) && v > 0.f) {
-    float w = 1.0f / v;
-    return make_float2(d * w, w);
-  }
-  return make_float2(0.f, 0.f);
+// g a + s into a register of its own: the partial sums move one place per
+// row, and the two-address form the compiler prefers copies each of them.
+__device__ __forceinline__ float chain(float g, float a, float s) {
+  float d;
+  asm("v_fma_f32 %0, %1, %2, %3" : "=v"(d) : "s"(g), "v"(a), "v"(s));
+  return d;
 }
 
 __device__ __forceinline__ unsigned xcd_tile(unsigned b, unsigned nb) {
@@ -175,115 +218,213 @@ __device__ __forceinline__ unsigned xcd_tile(unsigned b, unsigned nb) {
   return x < r ? x * (q + 1) + l : r * (q + 1) + (x - r) * q + l;
 }
 
-template <typename T, int R>
-__global__ __launch_bounds__(PREP_TX) void k_prepass(const ExpMeta* __restrict__ meta,
-                                                     const PrepTile* __restrict__ tiles,
-                                                     const void* const* __restrict__ flux,
-                                                     const void* const* __restrict__ var,
-                                                     float2* __restrict__ planes) {
+__device__ __forceinline__ double lane_value(double v, int lane) {
+  const uint64_t u = (uint64_t)__double_as_longlong(v);
+  const uint32_t lo = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)u, lane);
+  const uint32_t hi = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)(u >> 32), lane);
+  return __longlong_as_double((long long)(((uint64_t)hi << 32) | lo));
+}
+
+typedef float plane4_t __attribute__((ext_vector_type(4)));
+typedef uint32_t store4_t __attribute__((ext_vector_type(4)));
+constexpr int STORE_NT = 2;  // buffer cache policy: non-temporal
+
+template <typename T, int R, bool VAR>
+__global__ __launch_bounds__(64) void k_prepass(const ExpMeta* __restrict__ meta, const PrepTile* __restrict__ tiles,
+                                                const void* const* __restrict__ flux,
+                                                const void* const* __restrict__ var, float2* __restrict__ planes) {
   constexpr int K = 2 * R + 1;
-  constexpr int RW = PREP_TX + 2 * R;
-  constexpr int DEPTH = PREP_DEPTH;  // input rows in flight per thread
-  __shared__ float2 row[2][RW];
+  constexpr int G = prep_groups(R);     // column pairs per lane
+  constexpr int RA = prep_lead(R);      // input columns left of the first output column (even)
+  constexpr int OFF = RA - R;           // first tap of output column c is input column c + OFF
+  constexpr int NP = (OFF + K + 2) / 2; // pairs read for two output columns
+  constexpr int DEPTH = PREP_DEPTH;     // input rows in flight per lane
+  __shared__ float4 row[64 * G + NP];   // {D w, w} of two columns each
   // XCD-aware order: workgroups are dispatched round-robin over the 8 XCDs,
   // so give each XCD a contiguous run of tiles; neighbouring tiles (which
   // share halo rows and halo cache lines) then meet in the same L2
   const PrepTile tl = tiles[xcd_tile(blockIdx.x, gridDim.x)];
   const ExpMeta& m = meta[tl.e];
-  const int W = m.W, H = m.H;
-  const int tid = threadIdx.x;
-  // 1-D weights g and g^2; the 2-D stamp is g(dx) g(dy) / Z with Z = (sum g)^2
+  const int W = m.W, H = m.H;  // W >= 2
+  const int lane = threadIdx.x;
+  // 1-D weights g and g^2 (lane j computes tap j; wave-uniform values); the
+  // 2-D stamp is g(dx) g(dy) / Z with Z = (sum g)^2
   const double sig = (double)m.fwhm / (2.0 * sqrt(2.0 * log(2.0)));
+  const double gd = (double)(min(lane, K - 1) - R);
+  const double gl = exp(-gd * gd / (2.0 * sig * sig));
   float g1[K], g2[K];
   double zs = 0.0;
 #pragma unroll
   for (int j = 0; j < K; ++j) {
-    double d = (double)(j - R);
-    double g = exp(-d * d / (2.0 * sig * sig));
+    const double g = lane_value(gl, j);
     zs += g;
-    g1[j] = (float)g;
-    g2[j] = (float)(g * g);
+    g1[j] = __uint_as_float((uint32_t)__builtin_amdgcn_readfirstlane((int)__float_as_uint((float)g)));
+    g2[j] = __uint_as_float((uint32_t)__builtin_amdgcn_readfirstlane((int)__float_as_uint((float)(g * g))));
   }
   const double z = zs * zs;
   const float n1 = (float)(1.0 / z), n2 = (float)(1.0 / (z * z));
-  const void* Dp = flux[m.src];
-  const void* Vp = var[m.src];
-  // this thread's input columns: x0 - R + tid, and (halo) x0 + TX - R + tid
-  const int cx = tl.x0 - R + tid;
-  const int hx = tl.x0 + PREP_TX - R + tid;
-  const bool has_h = tid < 2 * R;
-  const bool in_c = cx >= 0 && cx < W;
-  const bool in_h = has_h && hx >= 0 && hx < W;
-  const int gx = tl.x0 + tid;  // output column
-  const int rows = PREP_TY + 2 * R;
-  // ring of DEPTH prefetched rows: (D, V) at the centre column and the halo column
-  float rd[DEPTH], rv[DEPTH], hd[DEPTH], hv[DEPTH];
-  auto fetch = [&](int r, float& d, float& v, float& dh, float& vh) {
-    d = v = dh = vh = __builtin_nanf("");
-    const int gy = tl.y0 - R + r;
-    if (r < rows && gy >= 0 && gy < H) {
-      const int64_t base = (int64_t)gy * W;
-      if (in_c) {
-        d = load_px<T>(Dp, base + cx);
-        v = Vp ? load_px<T>(Vp, base + cx) : m.vs;
-      }
-      if (in_h) {
-        dh = load_px<T>(Dp, base + hx);
-        vh = Vp ? load_px<T>(Vp, base + hx) : m.vs;
-      }
+  const T* Dp = static_cast<const T*>(flux[m.src]);
+  const T* Vp = VAR ? static_cast<const T*>(var[m.src]) : nullptr;
+  const float vs = m.vs;
+  // This lane's columns: group g holds c and c + 1.  The loop over rows has
+  // no branch (one around a load or a store makes the waits cover all loads
+  // in flight): every lane loads a pair inside the row on every row; rows and
+  // columns off the image read the nearest ones and are masked.  x0 and RA
+  // are even, so only the right edge cuts a pair; its one column is the
+  // second one loaded.
+  int cs[G];
+  bool cut[G];
+  uint32_t kill0[G], kill1[G];
+#pragma unroll
+  for (int g = 0; g < G; ++g) {
+    const int c = tl.x0 - RA + 128 * g + 2 * lane;
+    cs[g] = min(max(c, 0), W - 2);
+    cut[g] = c == W - 1;
+    kill0[g] = c >= 0 && c < W ? 0u : ~0u;
+    kill1[g] = c >= 0 && c + 1 < W ? 0u : ~0u;
+  }
+  const int rows = tl.ny + 2 * R;
+  Pair<T> D[DEPTH][G], V[DEPTH][G];
+  auto fetch = [&](int r, Pair<T>* d, Pair<T>* v) {
+    const int64_t base = (int64_t)min(max(tl.y0 - R + r, 0), H - 1) * W;
+#pragma unroll
+    for (int g = 0; g < G; ++g) {
+      d[g].load(Dp + base, cs[g]);
+      if (VAR) v[g].load(Vp + base, cs[g]);
     }
   };
 #pragma unroll
-  for (int q = 0; q < DEPTH; ++q) fetch(q, rd[q], rv[q], hd[q], hv[q]);
-  float2 win[K];
+  for (int q = 0; q < DEPTH; ++q) {
+    fetch(q, D[q], V[q]);
+    __builtin_amdgcn_sched_barrier(0);  // in the order of their use, as in the loop
+  }
+  // partial sums of the output rows the last K input rows belong to
+  float sa[2 * G][K], sb[2 * G][K];
 #pragma unroll
-  for (int j = 0; j < K; ++j) win[j] = make_float2(0.f, 0.f);
-  for (int r = 0; r < rows; ++r) {
-    float2* buf = row[r & 1];
-    buf[tid] = weight_pair(rd[0], rv[0]);
-    if (has_h) buf[PREP_TX + tid] = weight_pair(hd[0], hv[0]);
+  for (int c = 0; c < 2 * G; ++c)
 #pragma unroll
-    for (int q = 0; q < DEPTH - 1; ++q) {
-      rd[q] = rd[q + 1];
-      rv[q] = rv[q + 1];
-      hd[q] = hd[q + 1];
-      hv[q] = hv[q + 1];
-    }
-    fetch(r + DEPTH, rd[DEPTH - 1], rv[DEPTH - 1], hd[DEPTH - 1], hv[DEPTH - 1]);
-    __syncthreads();
-    float a = 0.f, b = 0.f;
+    for (int j = 0; j < K; ++j) sa[c][j] = sb[c][j] = 0.f;
+  // Output rows are stored through a buffer whose range is the row's part in
+  // this strip (nothing for the rows before the first one and past the last
+  // one): the hardware drops the lanes past it.  The pair that an odd width
+  // cuts is stored on its own.
+  const int n_out = min(W - tl.x0, prep_width(R));
+  const bool odd = (n_out & 1) != 0;
+  float2* out = planes + m.plane_off + (int64_t)(tl.y0 - 2 * R) * W + tl.x0;
+#pragma unroll 1
+  for (int r0 = 0; r0 < rows; r0 += DEPTH) {
 #pragma unroll
-    for (int j = 0; j < K; ++j) {
-      float2 v = buf[tid + j];
-      a = fmaf(g1[j], v.x, a);
-      b = fmaf(g2[j], v.y, b);
-    }
+    for (int u = 0; u < DEPTH; ++u) {  // row r sits in slot u: nothing moves
+      const int r = r0 + u;
+      const int gy = tl.y0 - R + r;
+      const uint32_t off = gy >= 0 && gy < H ? 0u : ~0u;
+      float a[2 * G], b[2 * G];
 #pragma unroll
-    for (int j = 0; j < K - 1; ++j) win[j] = win[j + 1];
-    win[K - 1] = make_float2(a, b);
-    const int gy = tl.y0 + r - 2 * R;  // output row centred in the window
-    if (r >= 2 * R && gy < H && gx < W) {
-      float pa = 0.f, pb = 0.f;
+      for (int c = 0; c < 2 * G; ++c) a[c] = b[c] = 0.f;
 #pragma unroll
-      for (int j = 0; j < K; ++j) {
-        pa = fmaf(g1[j], win[j].x, pa);
-        pb = fmaf(g2[j], win[j].y, pb);
+      for (int g = 0; g < G; ++g) {
+        const float2 d = D[u][g].use(cut[g], kill0[g] | off, kill1[g] | off);
+        const float2 v = VAR ? V[u][g].use(cut[g], 0u, 0u) : make_float2(vs, vs);
+        const float2 p0 = weight_pair(d.x, v.x), p1 = weight_pair(d.y, v.y);
+        row[64 * g + lane] = make_float4(p0.x, p0.y, p1.x, p1.y);
       }
-      const uint64_t bits = (uint64_t)__float_as_uint(pa * n1) | ((uint64_t)__float_as_uint(pb * n2) << 32);
-      __builtin_nontemporal_store(bits, reinterpret_cast<uint64_t*>(planes + m.plane_off + (int64_t)gy * W + gx));
+      // The loads into slot u are issued after its last use, into the same
+      // registers: moved above it they would need others, and a copy of
+      // values in flight, which waits for them, at the end of the loop.
+      __builtin_amdgcn_sched_barrier(0);
+      fetch(r + DEPTH, D[u], V[u]);
+      __builtin_amdgcn_sched_barrier(0);
+      // LDS operations of one wavefront complete in order: only the compiler
+      // has to keep the reads between this row's writes and the next one's
+      __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+#pragma unroll
+      for (int g = 0; g < G; ++g) {
+#pragma unroll
+        for (int q = 0; q < NP; ++q) {
+          const float4 v = row[64 * g + lane + q];
+#pragma unroll
+          for (int h = 0; h < 2; ++h) {
+            const int i = 2 * q + h - OFF;  // tap of the first of the two output columns
+            const float x = h ? v.z : v.x, w = h ? v.w : v.y;
+            if (i >= 0 && i < K) {
+              a[2 * g] = fmaf(g1[i], x, a[2 * g]);
+              b[2 * g] = fmaf(g2[i], w, b[2 * g]);
+            }
+            if (i >= 1 && i - 1 < K) {
+              a[2 * g + 1] = fmaf(g1[i - 1], x, a[2 * g + 1]);
+              b[2 * g + 1] = fmaf(g2[i - 1], w, b[2 * g + 1]);
+            }
+          }
+        }
+      }
+      __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+#pragma unroll
+      for (int c = 0; c < 2 * G; ++c) {
+#pragma unroll
+        for (int j = K - 1; j > 0; --j) {
+          sa[c][j] = chain(g1[j], a[c], sa[c][j - 1]);
+          sb[c][j] = chain(g2[j], b[c], sb[c][j - 1]);
+        }
+        sa[c][0] = chain(g1[0], a[c], 0.f);
+        sb[c][0] = chain(g2[0], b[c], 0.f);
+      }
+      const bool keep = r >= 2 * R && r < rows;
+      float2* q = keep ? out + (int64_t)r * W : planes;
+      const auto rsrc = __builtin_amdgcn_make_buffer_rsrc(q, (short)0, keep ? 8 * (n_out & ~1) : 0, 0x00020000);
+#pragma unroll
+      for (int g = 0; g < G; ++g) {
+        const plane4_t v = {sa[2 * g][K - 1] * n1, sb[2 * g][K - 1] * n2, sa[2 * g + 1][K - 1] * n1,
+                            sb[2 * g + 1][K - 1] * n2};
+        __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(store4_t, v), rsrc, 8 * (128 * g + 2 * lane), 0,
+                                               STORE_NT);
+        if (odd && keep && 128 * g + 2 * lane == n_out - 1) q[n_out - 1] = make_float2(v[0], v[1]);
+      }
+      __builtin_amdgcn_sched_barrier(0);
     }
   }
 }
 
+// Images one column wide: one thread per output row.
 template <typename T>
+__global__ __launch_bounds__(256) void k_prepass_column(const ExpMeta* __restrict__ meta,
+                                                        const PrepTile* __restrict__ tiles,
+                                                        const void* const* __restrict__ flux,
+                                                        const void* const* __restrict__ var,
+                                                        float2* __restrict__ planes) {
+  const PrepTile tl = tiles[blockIdx.x];
+  const ExpMeta& m = meta[tl.e];
+  const T* Dp = static_cast<const T*>(flux[m.src]);
+  const T* Vp = static_cast<const T*>(var[m.src]);
+  const double sig = (double)m.fwhm / (2.0 * sqrt(2.0 * log(2.0)));
+  auto tap = [&](int j) { return exp(-(double)(j * j) / (2.0 * sig * sig)); };
+  double zs = 0.0;
+  for (int j = -m.R; j <= m.R; ++j) zs += tap(j);
+  const double z = zs * zs;
+  for (int y = tl.y0 + (int)threadIdx.x; y < tl.y0 + tl.ny; y += 256) {
+    float a = 0.f, b = 0.f;
+    for (int j = -m.R; j <= m.R; ++j) {
+      if (y + j < 0 || y + j >= m.H) continue;
+      const float2 p = weight_pair((float)Dp[y + j], Vp ? (float)Vp[y + j] : m.vs);
+      const double g = tap(j);  // (the tap across the column, 0, is 1)
+      a = fmaf((float)g, p.x, a);
+      b = fmaf((float)(g * g), p.y, b);
+    }
+    planes[m.plane_off + y] = make_float2(a * (float)(1.0 / z), b * (float)(1.0 / (z * z)));
+  }
+}
+
+template <typename T, bool VAR>
 static hipError_t launch_prepass_t(int R, const ExpMeta* d_meta, const PrepTile* d_tiles, unsigned g,
                                    const void* const* d_flux, const void* const* d_var, float2* d_planes,
                                    hipStream_t s) {
   switch (R) {
-#define DT_CASE(RR)                                                                                          \
-  case RR:                                                                                                   \
-    hipLaunchKernelGGL((k_prepass<T, RR>), dim3(g), dim3(PREP_TX), 0, s, d_meta, d_tiles, d_flux, d_var,  \
-                       d_planes);                                                                            \
+    case 0:
+      hipLaunchKernelGGL((k_prepass_column<T>), dim3(g), dim3(256), 0, s, d_meta, d_tiles, d_flux, d_var, d_planes);
+      break;
+#define DT_CASE(RR)                                                                                        \
+  case RR:                                                                                                 \
+    hipLaunchKernelGGL((k_prepass<T, RR, VAR>), dim3(g), dim3(64), 0, s, d_meta, d_tiles, d_flux, d_var,   \
+                       d_planes);                                                                          \
     break;
     DT_CASE(1) DT_CASE(2) DT_CASE(3) DT_CASE(4) DT_CASE(5) DT_CASE(6)
     DT_CASE(7) DT_CASE(8) DT_CASE(9) DT_CASE(10) DT_CASE(11) DT_CASE(12)
@@ -296,15 +437,15 @@ static hipError_t launch_prepass_t(int R, const ExpMeta* d_meta, const PrepTile*
 
 hipError_t launch_prepass(const ExpMeta* d_meta, const PrepTile* d_tiles, const int64_t* group_off,
                           const int32_t* group_R, int n_groups, const void* const* d_flux,
-                          const void* const* d_var, dt_dtype dtype, float2* d_planes, hipStream_t s) {
+                          const void* const* d_var, bool has_var, dt_dtype dtype, float2* d_planes, hipStream_t s) {
   for (int gi = 0; gi < n_groups; ++gi) {
     const int64_t beg = group_off[gi], end = group_off[gi + 1];
     for (int64_t off = beg; off < end; off += 0x7fffffff) {
-      unsigned g = (unsigned)std::min<int64_t>(end - off, 0x7fffffff);
-      hipError_t e = dtype == DT_F32
-                         ? launch_prepass_t<float>(group_R[gi], d_meta, d_tiles + off, g, d_flux, d_var, d_planes, s)
-                         : launch_prepass_t<_Float16>(group_R[gi], d_meta, d_tiles + off, g, d_flux, d_var,
-                                                      d_planes, s);
+      const unsigned g = (unsigned)std::min<int64_t>(end - off, 0x7fffffff);
+      const auto launch = dtype == DT_F32 ? (has_var ? launch_prepass_t<float, true> : launch_prepass_t<float, false>)
+                                          : (has_var ? launch_prepass_t<_Float16, true>
+                                                     : launch_prepass_t<_Float16, false>);
+      const hipError_t e = launch(group_R[gi], d_meta, d_tiles + off, g, d_flux, d_var, d_planes, s);
       if (e != hipSuccess) return e;
     }
   }
