@@ -218,9 +218,9 @@ hipError_t launch_stack_ids(const StackArgs& a, const int64_t* d_ids, const int6
 hipError_t launch_stack_cells(const StackArgs& a, const int64_t* d_cells, int64_t n_sel, int cell_size,
                               hipStream_t s);
 
-// Outlier trimming of m candidate orbits (n_exp <= 512); d_buf is m x n_exp float2 scratch.
-hipError_t launch_clip(const StackArgs& a, const int64_t* d_ids, int64_t m, double kappa, int max_iter,
-                       float2* d_buf, float* snr, float* flux, int32_t* nkept, hipStream_t s);
+// Outlier trimming of m candidate orbits (n_exp <= 512).
+hipError_t launch_clip(const StackArgs& a, const int64_t* d_ids, int64_t m, double kappa, int max_iter, float* snr,
+                       float* flux, int32_t* nkept, hipStream_t s);
 
 // Fused inference forward of the cell scorer.
 struct ScorerFusedArgs {

@@ -51,14 +51,9 @@ dt_status dt_clip_candidates(dt_patch* p, const dt_orbits* orbits, const int64_t
   if (m == 0) return DT_OK;
   DeviceGuard guard(p->ctx->device);
   dt_ctx* c = p->ctx;
-  const size_t need = sizeof(float2) * (size_t)m * p->n_exp;
-  float2* buf = nullptr;
-  st = ctx_alloc(c, (void**)&buf, need, "outlier-trimming scratch");
-  if (st != DT_OK) return st;
   StackArgs a = stack_args(p, orbits);
-  hipError_t e = launch_clip(a, d_ids, m, kappa, max_iter, buf, d_snr, d_flux, d_nkept, c->stream);
-  if (e == hipSuccess) e = hipStreamSynchronize(c->stream);  // the scratch is freed below
-  ctx_free(c, buf, need);
+  hipError_t e = launch_clip(a, d_ids, m, kappa, max_iter, d_snr, d_flux, d_nkept, c->stream);
+  if (e == hipSuccess) e = hipStreamSynchronize(c->stream);
   return e == hipSuccess ? DT_OK : hip_fail(e, "outlier trimming");
 }
 

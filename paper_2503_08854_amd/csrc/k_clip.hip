@@ -9,44 +9,47 @@
 // keeps the samples with |chi_e| <= kappa; it stops when a round keeps
 // exactly the set it started from, or after max_iter rounds.
 //
-// Pass 1 (one lane per candidate) walks the candidate's exposures with the
-// stack's device code and writes its (psi, phi) per exposure; pass 2 (one
-// wavefront per candidate, each lane owning up to 8 exposures) finds the
-// median by ranking in LDS and iterates the clipping with FP64 wave
-// reductions.  The per-sample arithmetic is FP64 without contraction, as in
-// the definition.
+// One wavefront per candidate.  Its exposures are cut into 64 runs, one lane
+// walking each from a cold start with the stack's device code (a candidate's
+// walk is a serial chain: one lane over all exposures, two wavefronts for a
+// hundred candidates, took 117 us for 200 exposures, and 28 us more in a
+// second kernel for the rest; this takes 16 us together); the samples' (psi,
+// phi) meet in LDS, where the lanes, each owning up to 8 exposures, find the
+// median by ranking the valid ones and iterate the clipping with FP64 wave
+// reductions.  The per-sample arithmetic of the fit is FP64 without
+// contraction, as in the definition.
 #include "dt_stack.hpp"
 
 namespace dtk {
 
 constexpr int CLIP_PER_LANE = 8;  // exposures per lane: n_exp <= 512
 
-__global__ __launch_bounds__(256) void k_clip_samples(StackArgs A, const int64_t* __restrict__ ids, int64_t m,
-                                                      float2* __restrict__ buf) {
-  const int64_t r = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (r >= m) return;
-  float2* out = buf + r * A.n_exp;
-  const int64_t o = ids[r];
-  bool ok = o >= 0 && o < A.n;
+// (psi, phi) of candidate o's exposures ({0, 0} where no valid sample) into smp.
+__device__ __forceinline__ void clip_samples(const StackArgs& A, int64_t o, float2* smp) {
+  const int lane = threadIdx.x;
   double a = 0, e = 0, inc = 0, node = 0, peri = 0, m0 = 0;
+  bool ok = o >= 0 && o < A.n;
   if (ok) {
     a = A.a[o]; e = A.e[o]; inc = A.inc[o]; node = A.node[o]; peri = A.peri[o]; m0 = A.m0[o];
     ok = orbit_ok(a, e, inc, node, peri, m0);
   }
+  const int ch = (A.n_exp + 63) / 64;
+  const int ex0 = lane * ch, cnt = min(ch, A.n_exp - ex0);
   if (!ok) {
-    for (int ex = 0; ex < A.n_exp; ++ex) out[ex] = make_float2(0.f, 0.f);
+    for (int i = 0; i < cnt; ++i) smp[ex0 + i] = make_float2(0.f, 0.f);
     return;
   }
+  if (cnt <= 0) return;
   Orbit ob;
   orbit_prep(a, e, inc, node, peri, m0, ob);
-  walk_orbit<false>(ob, A.meta, A.n_exp, A.epoch, [&](int ex, const SampleOut& so) {
-    const ExpMeta& x = A.meta[ex];
+  walk_orbit<false>(ob, A.meta + ex0, cnt, A.epoch, [&](int i, const SampleOut& so) {
+    const ExpMeta& x = A.meta[ex0 + i];
     float2 v = make_float2(0.f, 0.f);
     if (so.inside) {
       v = A.planes[x.plane_off + (int64_t)so.iy * x.W + so.ix];
       if (!(v.y > 0.f)) v = make_float2(0.f, 0.f);
     }
-    out[ex] = v;
+    smp[ex0 + i] = v;
   });
 }
 
@@ -56,43 +59,45 @@ __device__ __forceinline__ double wave_sum_d(double v) {
   return v;
 }
 
-__global__ __launch_bounds__(64) void k_clip_fit(const float2* __restrict__ buf, int n_exp, int64_t m,
-                                                 double kappa, int max_iter, float* __restrict__ snr,
-                                                 float* __restrict__ flux, int32_t* __restrict__ nkept) {
+__global__ __launch_bounds__(64) void k_clip(StackArgs A, const int64_t* __restrict__ ids, double kappa, int max_iter,
+                                             float* __restrict__ snr, float* __restrict__ flux,
+                                             int32_t* __restrict__ nkept) {
 #pragma clang fp contract(off)
   const int64_t r = blockIdx.x;
-  if (r >= m) return;
   const int lane = threadIdx.x;
-  __shared__ double fl[64 * CLIP_PER_LANE];  // per-sample flux psi / phi
-  __shared__ int vf[64 * CLIP_PER_LANE];     // sample valid (phi > 0)
+  const int n_exp = A.n_exp;
+  __shared__ float2 smp[64 * CLIP_PER_LANE];
+  __shared__ double fl[64 * CLIP_PER_LANE];  // fluxes psi / phi of the valid samples, in epoch order
+  clip_samples(A, ids[r], smp);
+  __syncthreads();
   double ps[CLIP_PER_LANE], ph[CLIP_PER_LANE];
+  int at[CLIP_PER_LANE];  // place among the valid samples
   bool valid[CLIP_PER_LANE], kept[CLIP_PER_LANE];
-  int nv = 0;
+  int nvalid = 0;
 #pragma unroll
   for (int q = 0; q < CLIP_PER_LANE; ++q) {
     const int ex = lane + 64 * q;
-    float2 v = ex < n_exp ? buf[r * n_exp + ex] : make_float2(0.f, 0.f);
+    const float2 v = ex < n_exp ? smp[ex] : make_float2(0.f, 0.f);
     ps[q] = v.x;
     ph[q] = v.y;
     valid[q] = v.y > 0.f;
     kept[q] = valid[q];
-    nv += valid[q] ? 1 : 0;
-    fl[ex] = valid[q] ? ps[q] / ph[q] : 0.0;
-    vf[ex] = valid[q] ? 1 : 0;
+    const uint64_t m = __ballot(valid[q]);
+    at[q] = nvalid + __popcll(m & ((1ull << lane) - 1ull));
+    nvalid += __popcll(m);
+    if (valid[q]) fl[at[q]] = ps[q] / ph[q];
   }
   __syncthreads();
-  const int nvalid = (int)wave_sum_d((double)nv);
   // iteration 1 expectation: the median of the per-sample fluxes (ranks with
-  // ties broken by exposure index; mean of the two middle values)
+  // ties broken by exposure order; mean of the two middle values)
   const int lo = (nvalid - 1) / 2, hi = nvalid / 2;
   double vlo = 0.0, vhi = 0.0;
 #pragma unroll
   for (int q = 0; q < CLIP_PER_LANE; ++q) {
     if (!valid[q]) continue;
-    const int me = lane + 64 * q;
-    const double f = fl[me];
+    const double f = fl[at[q]];
     int rank = 0;
-    for (int j = 0; j < n_exp; ++j) rank += (vf[j] && (fl[j] < f || (fl[j] == f && j < me))) ? 1 : 0;
+    for (int j = 0; j < nvalid; ++j) rank += (fl[j] < f || (fl[j] == f && j < at[q])) ? 1 : 0;
     if (rank == lo) vlo = f;
     if (rank == hi) vhi = f;
   }
@@ -138,13 +143,11 @@ __global__ __launch_bounds__(64) void k_clip_fit(const float2* __restrict__ buf,
   }
 }
 
-hipError_t launch_clip(const StackArgs& a, const int64_t* d_ids, int64_t m, double kappa, int max_iter,
-                       float2* d_buf, float* snr, float* flux, int32_t* nkept, hipStream_t s) {
+hipError_t launch_clip(const StackArgs& a, const int64_t* d_ids, int64_t m, double kappa, int max_iter, float* snr,
+                       float* flux, int32_t* nkept, hipStream_t s) {
   if (m <= 0) return hipSuccess;
   if (a.n_exp > 64 * CLIP_PER_LANE) return hipErrorInvalidValue;
-  hipLaunchKernelGGL(k_clip_samples, dim3((unsigned)((m + 255) / 256)), dim3(256), 0, s, a, d_ids, m, d_buf);
-  hipLaunchKernelGGL(k_clip_fit, dim3((unsigned)m), dim3(64), 0, s, d_buf, a.n_exp, m, kappa, max_iter, snr, flux,
-                     nkept);
+  hipLaunchKernelGGL(k_clip, dim3((unsigned)m), dim3(64), 0, s, a, d_ids, kappa, max_iter, snr, flux, nkept);
   return hipGetLastError();
 }
 
