@@ -110,7 +110,9 @@ dt_status dt_ctx_destroy(dt_ctx *ctx);
 /* Work counters (measurement, no paper counterpart).  While counting is on
  * (on != 0; turning it on zeroes the counters), every stack launch of the
  * context that runs the checkpoint walk (dt_stack, dt_stack_generated,
- * dt_stack_batched, dt_stack_cells) adds what it did.  dt_ctx_work
+ * dt_stack_batched, dt_stack_cells) adds what it did; small launches, which
+ * otherwise cut the exposures of 64 orbits over several wavefronts, run that
+ * walk too while counting is on (their results are the same bits).  dt_ctx_work
  * synchronises the context stream, writes the totals since the last read
  * (out, host, DT_WORK_COUNTERS values) and zeroes them:
  *   out[0] samples tested by the checkpoint prediction (live orbit x exposure)
@@ -476,7 +478,7 @@ dt_status dt_scorer_train_step(dt_scorer *s, const uint16_t *d_stamps, const uin
 dt_status dt_debug_samples(dt_patch *p, const dt_orbits *orbits, const int64_t *d_ids, int64_t m,
                            double *d_px, double *d_py, int32_t *d_ix, int32_t *d_iy,
                            int32_t *d_flags, float *d_psi, float *d_phi, double *d_tau);
-/* The same table from the walk dt_stack itself runs on this patch (the
+/* The same table from the walk dt_stack runs on this patch for large sets (the
  * checkpoint walk with its queue, and the per-sample tail it may switch to;
  * or, for patches without an observer speed bound, the per-sample walk with
  * its sky-cone test): only the samples that walk solves exactly carry

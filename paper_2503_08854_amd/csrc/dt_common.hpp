@@ -154,6 +154,30 @@ struct WorkItem {
   int64_t begin;
 };
 
+// Wavefronts that share 64 orbits of a small launch (their exposures cut
+// into that many ranges, split_walk), 0: one wavefront walks all exposures.
+// A launch of up to 48 x 1024 orbits leaves most of the chip's wavefront slots
+// empty and takes as long as one walk; cut, it does up to twice the work
+// (samples solved one by one, a cold start per range) in parallel.  The line
+// is where that work fills the chip: three workgroups of four wavefronts per
+// CU, or one of eight, with their samples in LDS.  Measured (checkpoint walk
+// -> split): 10^4 orbits x 20 exposures 25 -> 13.5 us, x 200 88-114 -> 33-35
+// (distant objects, which land often: 389 -> 50); 3 x 10^4 x 60 42-49 -> 27-32;
+// 6 x 10^4 x 60 43-51 -> 42-50 (equal); 1.3 x 10^5 x 60 50-59 -> 68-86.
+// Launches that count their work run the checkpoint walk, which is what the
+// counters are about (the sums are the same).
+inline size_t stack_split_lds(int n_exp) { return sizeof(float2) * 64 * (size_t)n_exp; }
+// Allows kernel f the dynamic LDS of a split launch.
+inline hipError_t stack_split_attr(const void* f, size_t lds) {
+  return lds > 65536 ? hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds) : hipSuccess;
+}
+inline int stack_split(const StackArgs& a) {
+  constexpr int64_t CUS = 256, LDS = 156 * 1024;
+  const int64_t per_cu = (a.n + 64 * CUS - 1) / (64 * CUS);
+  if (a.work || a.n_exp < 2 || per_cu > 3 || per_cu * (int64_t)(stack_split_lds(a.n_exp) + 4096) > LDS) return 0;
+  return per_cu == 1 ? 8 : 4;
+}
+
 // The stack: the checkpoint walk (then, when a.defer_list is set, the
 // per-sample walk of the wavefronts it deferred), or the per-sample walk for
 // an unbounded observer speed.

@@ -107,6 +107,60 @@ __device__ __forceinline__ void stack_walk(const StackArgs& A, const Orbit& ob, 
   stack_finish(P, snr_out, flux_out, nv_out);
 }
 
+// 64 orbits by a workgroup of SPLIT wavefronts, for launches too small to fill
+// the chip: lane l of every wavefront holds orbit l (prepared when `good`),
+// and the exposures are cut into SPLIT contiguous ranges, each walked per
+// sample by one wavefront from a cold start (the range is uniform over the
+// wavefront, so exposure records stay scalar loads).  The gathered values
+// meet in LDS (smp: n_exp x 64) and are summed in epoch order, psi by the
+// first wavefront and phi by the second, so the sums equal those of one walk
+// bit for bit.  Returns true in the first wavefront, with the sums in P.
+template <int SPLIT>
+__device__ __forceinline__ bool split_walk(const StackArgs& A, const Orbit& ob, bool good, float2* smp, StackPart& P) {
+  static_assert(SPLIT >= 2, "two wavefronts sum");
+  __shared__ float phi[64];  // the second wavefront's sum, s - c
+  const int j = (int)__builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = (int)(threadIdx.x & 63);
+  const int ch = (A.n_exp + SPLIT - 1) / SPLIT;
+  const int ex0 = j * ch;
+  const int cnt = min(ch, A.n_exp - ex0);
+  if (cnt > 0) {
+    float2* out = smp + ex0 * 64 + lane;
+    if (good) {
+      // each gather is stored one exposure later (as in stack_range)
+      float2 pend = make_float2(0.f, 0.f);
+      walk_orbit<false>(ob, A.meta + ex0, cnt, A.epoch, [&](int i, const SampleOut& so) {
+        const ExpMeta& x = A.meta[ex0 + i];
+        if (i > 0) out[(i - 1) * 64] = pend;
+        pend = so.inside ? gather_nt(A.planes, x.plane_off + (int64_t)so.iy * x.W + so.ix) : make_float2(0.f, 0.f);
+      });
+      out[(cnt - 1) * 64] = pend;
+    } else {
+      for (int i = 0; i < cnt; ++i) out[i * 64] = make_float2(0.f, 0.f);
+    }
+  }
+  __syncthreads();
+  if (j >= 2) return false;
+  Kahan k;
+  k.init();
+  int nv = 0;
+#pragma unroll 4
+  for (int ex = 0; ex < A.n_exp; ++ex) {
+    const float2 v = smp[ex * 64 + lane];
+    if (v.y > 0.f) {
+      k.add(j ? v.y : v.x);
+      nv++;
+    }
+  }
+  if (j == 1) phi[lane] = k.s - k.c;
+  __syncthreads();
+  if (j == 1) return false;
+  P.ps = k;
+  P.ph.s = phi[lane];
+  P.ph.c = 0.f;
+  P.nv = nv;
+  return true;
+}
+
 // One orbit of the stack; DEBUG also fills the per-sample table of `dbg`
 // (row `row`), walking every sample exactly.
 template <bool DEBUG>

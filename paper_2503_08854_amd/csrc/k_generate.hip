@@ -140,6 +140,35 @@ __global__ __launch_bounds__(64, 4) void k_stack_generated_track(StackArgs A, dt
   if (A.nvalid) A.nvalid[i] = nv;
 }
 
+// Few generated orbits: 64 per workgroup, generated by its first wavefront
+// (every wavefront for itself: 5 us longer), their exposures cut over all.
+template <int SPLIT>
+__global__ __launch_bounds__(64 * SPLIT) void k_stack_generated_split(StackArgs A, dt_orbit_sampler S, int64_t first) {
+  extern __shared__ float2 gen_smp[];
+  __shared__ double gen_el[6][64];  // a = NaN: no orbit
+  const int lane = (int)(threadIdx.x & 63);
+  const int64_t i = (int64_t)blockIdx.x * 64 + lane;
+  const bool in = i < A.n;
+  double el[6] = {__builtin_nan(""), 0.0, 0.0, 0.0, 0.0, 0.0};
+  if (threadIdx.x < 64) {
+    if (in) (void)gen_orbit(S, (uint64_t)(first + i), el);
+    for (int k = 0; k < 6; ++k) gen_el[k][lane] = el[k];
+  }
+  __syncthreads();
+  for (int k = 0; k < 6; ++k) el[k] = gen_el[k][lane];
+  const bool good = orbit_ok(el[0], el[1], el[2], el[3], el[4], el[5]);
+  Orbit ob;
+  if (good) orbit_prep(el[0], el[1], el[2], el[3], el[4], el[5], ob);
+  StackPart P;
+  if (!split_walk<SPLIT>(A, ob, good, gen_smp, P) || !in) return;
+  float snr = __builtin_nanf(""), flux = __builtin_nanf("");
+  int nv = -1;
+  if (good) stack_finish(P, snr, flux, nv);
+  if (A.snr) A.snr[i] = snr;
+  if (A.flux) A.flux[i] = flux;
+  if (A.nvalid) A.nvalid[i] = nv;
+}
+
 // The deferred wavefronts of k_stack_generated_track, walked per sample: one
 // wavefront per list entry (the first orbit index of 64); wavefronts past the
 // number of entries return at once.  (A persistent loop over the entries kept
@@ -197,6 +226,17 @@ hipError_t launch_stack_generated_walk(const StackArgs& a, const dt_orbit_sample
 
 hipError_t launch_stack_generated(const StackArgs& a, const dt_orbit_sampler& S, int64_t first, hipStream_t s) {
   if (a.n <= 0) return hipSuccess;
+  const int split = stack_split(a);
+  if (split) {
+    const size_t lds = stack_split_lds(a.n_exp);
+    const unsigned g = (unsigned)((a.n + 63) / 64);
+    const hipError_t e = stack_split_attr(
+        split == 8 ? (const void*)k_stack_generated_split<8> : (const void*)k_stack_generated_split<4>, lds);
+    if (e != hipSuccess) return e;
+    if (split == 8) hipLaunchKernelGGL(k_stack_generated_split<8>, dim3(g), dim3(512), lds, s, a, S, first);
+    else hipLaunchKernelGGL(k_stack_generated_split<4>, dim3(g), dim3(256), lds, s, a, S, first);
+    return hipGetLastError();
+  }
   if (a.vobs < __builtin_inf()) {
     if (a.defer_list) {
       hipError_t e = launch_zero_u32(a.defer_count, s);

@@ -79,6 +79,29 @@ __global__ __launch_bounds__(256, 4) void k_stack_deferred(StackArgs A) {
   if (A.nvalid) A.nvalid[o] = nv;
 }
 
+// Few orbits: 64 per workgroup, their exposures cut over its wavefronts.
+template <int SPLIT>
+__global__ __launch_bounds__(64 * SPLIT) void k_stack_split(StackArgs A) {
+  extern __shared__ float2 smp[];
+  const int64_t o = (int64_t)blockIdx.x * 64 + (threadIdx.x & 63);
+  const bool in = o < A.n;
+  double el[6] = {0.0, 0.0, 0.0, 0.0, 0.0, 0.0};
+  if (in) {
+    el[0] = A.a[o]; el[1] = A.e[o]; el[2] = A.inc[o]; el[3] = A.node[o]; el[4] = A.peri[o]; el[5] = A.m0[o];
+  }
+  const bool good = in && orbit_ok(el[0], el[1], el[2], el[3], el[4], el[5]);
+  Orbit ob;
+  if (good) orbit_prep(el[0], el[1], el[2], el[3], el[4], el[5], ob);
+  StackPart P;
+  if (!split_walk<SPLIT>(A, ob, good, smp, P) || !in) return;
+  float snr = __builtin_nanf(""), flux = __builtin_nanf("");
+  int nv = -1;
+  if (good) stack_finish(P, snr, flux, nv);
+  if (A.snr) A.snr[o] = snr;
+  if (A.flux) A.flux[o] = flux;
+  if (A.nvalid) A.nvalid[o] = nv;
+}
+
 __global__ void k_zero_u32(unsigned int* p) { *p = 0u; }
 
 __global__ __launch_bounds__(64) void k_stack_debug(StackArgs A, DebugArgs D) {
@@ -241,6 +264,17 @@ hipError_t launch_gather_replay(const float2* planes, const int64_t* gstart, con
 
 hipError_t launch_stack(const StackArgs& a, hipStream_t s) {
   if (a.n <= 0) return hipSuccess;
+  const int split = stack_split(a);
+  if (split) {
+    const size_t lds = stack_split_lds(a.n_exp);
+    const unsigned g = grid_for(a.n, 64);
+    const hipError_t e =
+        stack_split_attr(split == 8 ? (const void*)k_stack_split<8> : (const void*)k_stack_split<4>, lds);
+    if (e != hipSuccess) return e;
+    if (split == 8) hipLaunchKernelGGL(k_stack_split<8>, dim3(g), dim3(512), lds, s, a);
+    else hipLaunchKernelGGL(k_stack_split<4>, dim3(g), dim3(256), lds, s, a);
+    return hipGetLastError();
+  }
   if (a.vobs < __builtin_inf()) {
     if (a.defer_list) hipLaunchKernelGGL(k_zero_u32, dim3(1), dim3(1), 0, s, a.defer_count);
     hipLaunchKernelGGL(k_stack_track, dim3(grid_for(a.n, 64)), dim3(64), 0, s, a);
