@@ -415,7 +415,7 @@ dt_status dt_cell_members_near(dt_ctx *ctx, const dt_orbits *grid, const int64_t
 dt_status dt_stack_ids(dt_patch *p, const dt_orbits *orbits, const int64_t *d_ids, const int64_t *d_count,
                        int64_t m_max, float *d_snr, float *d_flux, int32_t *d_nvalid);
 
-/* The scorer's GEMM on its own: C = op(A) op(B) (+ bias[n]) (ReLU if relu),
+/* A BF16 GEMM on the matrix cores: C = op(A) op(B) (+ bias[n]) (ReLU if relu),
  * BF16 inputs, FP32 accumulation and output (device, row-major with leading
  * dimensions; op(A) is M x K and A is stored K x M when transA; op(B) is
  * K x N and B is stored N x K when transB).  Synchronises. */
@@ -432,7 +432,7 @@ dt_status dt_gemm_bf16(dt_ctx *ctx, const uint16_t *d_A, int32_t lda, int32_t tr
 typedef struct dt_scorer dt_scorer;
 int64_t dt_scorer_num_params(void);
 /* He-normal weights from a counter-based generator seeded by `seed`, zero biases;
- * 1 <= max_batch <= 32768 (the activations of max_batch cells are held). */
+ * 1 <= max_batch <= 32768 (the inputs and deltas of the fully connected layers of max_batch cells are held). */
 dt_status dt_scorer_create(dt_ctx *ctx, int32_t max_batch, uint64_t seed, dt_scorer **out);
 dt_status dt_scorer_destroy(dt_scorer *s);
 dt_status dt_scorer_get_params(dt_scorer *s, float *d_params);

@@ -208,19 +208,39 @@ struct GemmArgs {
   int ldcb;
 };
 hipError_t launch_gemm_bf16(const GemmArgs& g, float* d_part, size_t part_elems, hipStream_t s);
-hipError_t launch_im2col(const uint16_t* x, int Bn, int H, int W, int C, int stride, int Ho, int Wo, uint16_t* cols,
-                         hipStream_t s);
-hipError_t launch_col2im_mask(const float* dcols, int Bn, int H, int W, int C, int stride, int Ho, int Wo,
-                              const uint16_t* act, uint16_t* dx, float* dx_f, hipStream_t s);
-hipError_t launch_relu_mask(const float* src, int lds, const uint16_t* act, int lda, int M, int N, uint16_t* dst,
-                            float* dst_f, hipStream_t s);
-hipError_t launch_colsum(const float* d, int M, int N, float* out, hipStream_t s);
-hipError_t launch_bce(const float* z, const float* y, int Bn, float* loss, float* dz, uint16_t* dz_bf, hipStream_t s);
-hipError_t launch_adam(float* w, float* m, float* v, const float* g, int64_t n, float lr, int64_t t, uint16_t* w_bf,
-                       hipStream_t s);
-hipError_t launch_cast_bf16(const float* x, int64_t n, uint16_t* y, hipStream_t s);
 hipError_t launch_init_params(float* w, int64_t off, int64_t n, int fan_in, uint64_t seed, int is_bias,
                               hipStream_t s);
+
+// Training path of the cell scorer (any output of the backward pass may be
+// null in a forward pass).
+constexpr int TRAIN_FRAGS = 382 * 512;  // BF16 weights in the order of the products' lanes
+constexpr int TRAIN_RECORD = 14336;  // floats of one workgroup's gradient record (14 306 used, whole 128-byte lines)
+struct TrainArgs {
+  const uint16_t* stamps;  // B x 441 BF16
+  const uint16_t* feats;   // B x 16 BF16
+  const float* labels;     // B
+  int B;
+  int splits;              // partial sums of the 1152-deep layer (1, 2 or 4)
+  const float* w;          // FP32 parameters (the biases are read here)
+  const uint16_t* wf;      // BF16 weights, TRAIN_FRAGS
+  float* z;                // B logits
+  uint16_t *h3, *ft, *cat;  // inputs of the fully connected layers, B x 1152, 16, 128
+  uint16_t *d4, *d5, *d6;   // their output deltas, B x 64 each
+  float* records;          // train_groups(B) x TRAIN_RECORD
+};
+struct AdamArgs {
+  float *w, *m, *v;
+  uint16_t *wt, *wf;
+  float lr, b1, b2, eps, c1, c2;
+};
+int train_groups(int B);
+int train_splits(int B);
+hipError_t launch_train_forward(const TrainArgs& a, hipStream_t s);
+// step: apply Adam instead of writing grad.
+hipError_t launch_train_grad(const TrainArgs& a, float* loss, float* grad, const AdamArgs* step, hipStream_t s);
+// BF16 copies of the parameters w: the weights transposed ([N][K], layer after
+// layer) and as TRAIN_FRAGS (whose padding stays as it is: zero).
+hipError_t launch_scorer_weights(const float* w, uint16_t* wt, uint16_t* wf, hipStream_t s);
 
 // Coarse stamps (21 x 21) and 16 features per representative orbit; d_track
 // is n x n_exp int2 scratch.  Any output may be null.
@@ -251,11 +271,9 @@ struct ScorerFusedArgs {
   const uint16_t* stamps;  // B x 441 BF16
   const uint16_t* feats;   // B x 16 BF16
   int B;
-  const uint16_t* wb;      // BF16 weights, layer-wise [K][N]
-  uint16_t* wt;            // scratch: the BF16 weights transposed, layer i at t_off[i] as [N][K]
+  const uint16_t* wt;      // the BF16 weights transposed, layer i at t_off[i] as [N][K]
   const float* w;          // FP32 master parameters (the biases are read here)
-  int64_t w_off[7], b_off[7], t_off[8];
-  int K[7], N[7];
+  int64_t b_off[7], t_off[7];
   float* z;                // B logits
   const int64_t* rows;     // NULL, or cell i of the batch is row rows[i] of stamps / feats and of z
 };
@@ -277,8 +295,7 @@ int64_t topk_seg_tile();      // keys per tile
 int64_t topk_seg_max_keys();  // largest k * tiles of one array
 hipError_t launch_topk_segmented(const SegTopkArgs& a, int n_tiles, int n_arrays, hipStream_t s);
 
-// transpose: rebuild A.wt from A.wb first (needed after the weights changed).
-hipError_t launch_scorer_fused(const ScorerFusedArgs& a, bool transpose, hipStream_t s);
+hipError_t launch_scorer_fused(const ScorerFusedArgs& a, hipStream_t s);
 
 // Replay of a recorded gather stream (measurement yardstick).
 hipError_t launch_record_gathers(const StackArgs& a, int64_t* cnt, const int64_t* gstart, int64_t* list,

@@ -59,19 +59,6 @@ constexpr int FTS = 20, CTS = 132, H6S = 68;
 constexpr int SPAD = 23 * 23;                // the stamp with a one-pixel zero border
 }  // namespace
 
-// wt[toff[i] + n * K_i + k] = wb[w_off[i] + k * N_i + n]
-__global__ void k_scorer_transpose(const uint16_t* __restrict__ wb, uint16_t* __restrict__ wt, ScorerFusedArgs A,
-                                   int total) {
-  const int i = blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= total) return;
-  int l = 0;
-  while (l < 6 && i >= A.t_off[l + 1]) ++l;
-  const int r = i - (int)A.t_off[l];
-  const int K = A.K[l], N = A.N[l];
-  const int n = r / K, k = r % K;
-  wt[i] = wb[A.w_off[l] + (int64_t)k * N + n];
-}
-
 template <bool ROWS>
 __global__ __launch_bounds__(NTH) void k_scorer_fused(ScorerFusedArgs A) {
   // A workgroup owns 16 cells at a time; the cells are the M (row) dimension
@@ -306,12 +293,8 @@ __global__ __launch_bounds__(NTH) void k_scorer_fused(ScorerFusedArgs A) {
   }
 }
 
-hipError_t launch_scorer_fused(const ScorerFusedArgs& a, bool transpose, hipStream_t s) {
+hipError_t launch_scorer_fused(const ScorerFusedArgs& a, hipStream_t s) {
   if (a.B <= 0) return hipSuccess;
-  const int total = (int)a.t_off[7];
-  if (transpose)
-    hipLaunchKernelGGL(k_scorer_transpose, dim3((unsigned)((total + 255) / 256)), dim3(256), 0, s, a.wb, a.wt, a,
-                       total);
   int dev = 0, n_cu = 256;
   if (hipGetDevice(&dev) == hipSuccess) (void)hipDeviceGetAttribute(&n_cu, hipDeviceAttributeMultiprocessorCount, dev);
   const int groups = (a.B + G - 1) / G;
