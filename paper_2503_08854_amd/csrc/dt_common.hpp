@@ -213,7 +213,18 @@ hipError_t launch_init_params(float* w, int64_t off, int64_t n, int fan_in, uint
 
 // Training path of the cell scorer (any output of the backward pass may be
 // null in a forward pass).
-constexpr int TRAIN_FRAGS = 382 * 512;  // BF16 weights in the order of the products' lanes
+// BF16 weights in fragments: 512 weights, eight consecutive K of row lane & 15
+// for each lane in turn (K 8 (lane >> 4) ..).  Forward (rows = output
+// channels): layer l from F<l>, row tile by row tile, K steps of 32 (padded
+// with zeros).  Back (rows = inputs, K = outputs): layer l from G<l>;
+// convolutions tap by tap, row tile by row tile.
+constexpr int SCORER_FRAG = 512;
+constexpr int SCORER_F1 = 0, SCORER_F2 = SCORER_F1 + SCORER_FRAG, SCORER_F3 = SCORER_F2 + 10 * SCORER_FRAG,
+              SCORER_F4 = SCORER_F3 + 18 * SCORER_FRAG, SCORER_F5 = SCORER_F4 + 144 * SCORER_FRAG,
+              SCORER_F6 = SCORER_F5 + 4 * SCORER_FRAG, SCORER_F7 = SCORER_F6 + 16 * SCORER_FRAG,
+              SCORER_G2 = SCORER_F7 + 2 * SCORER_FRAG, SCORER_G3 = SCORER_G2 + 9 * SCORER_FRAG,
+              SCORER_G4 = SCORER_G3 + 18 * SCORER_FRAG, SCORER_G6 = SCORER_G4 + 144 * SCORER_FRAG,
+              SCORER_FRAGS = SCORER_G6 + 16 * SCORER_FRAG;
 constexpr int TRAIN_RECORD = 14336;  // floats of one workgroup's gradient record (14 306 used, whole 128-byte lines)
 struct TrainArgs {
   const uint16_t* stamps;  // B x 441 BF16
@@ -222,7 +233,7 @@ struct TrainArgs {
   int B;
   int splits;              // partial sums of the 1152-deep layer (1, 2 or 4)
   const float* w;          // FP32 parameters (the biases are read here)
-  const uint16_t* wf;      // BF16 weights, TRAIN_FRAGS
+  const uint16_t* wf;      // BF16 weights, SCORER_FRAGS
   float* z;                // B logits
   uint16_t *h3, *ft, *cat;  // inputs of the fully connected layers, B x 1152, 16, 128
   uint16_t *d4, *d5, *d6;   // their output deltas, B x 64 each
@@ -230,7 +241,7 @@ struct TrainArgs {
 };
 struct AdamArgs {
   float *w, *m, *v;
-  uint16_t *wt, *wf;
+  uint16_t* wf;
   float lr, b1, b2, eps, c1, c2;
 };
 int train_groups(int B);
@@ -238,9 +249,8 @@ int train_splits(int B);
 hipError_t launch_train_forward(const TrainArgs& a, hipStream_t s);
 // step: apply Adam instead of writing grad.
 hipError_t launch_train_grad(const TrainArgs& a, float* loss, float* grad, const AdamArgs* step, hipStream_t s);
-// BF16 copies of the parameters w: the weights transposed ([N][K], layer after
-// layer) and as TRAIN_FRAGS (whose padding stays as it is: zero).
-hipError_t launch_scorer_weights(const float* w, uint16_t* wt, uint16_t* wf, hipStream_t s);
+// BF16 copies of the parameters w, SCORER_FRAGS (the padding stays as it is: zero).
+hipError_t launch_scorer_weights(const float* w, uint16_t* wf, hipStream_t s);
 
 // Coarse stamps (21 x 21) and 16 features per representative orbit; d_track
 // is n x n_exp int2 scratch.  Any output may be null.
@@ -271,9 +281,9 @@ struct ScorerFusedArgs {
   const uint16_t* stamps;  // B x 441 BF16
   const uint16_t* feats;   // B x 16 BF16
   int B;
-  const uint16_t* wt;      // the BF16 weights transposed, layer i at t_off[i] as [N][K]
+  const uint16_t* wf;      // BF16 weights, SCORER_FRAGS
   const float* w;          // FP32 master parameters (the biases are read here)
-  int64_t b_off[7], t_off[7];
+  int64_t b_off[7];
   float* z;                // B logits
   const int64_t* rows;     // NULL, or cell i of the batch is row rows[i] of stamps / feats and of z
 };

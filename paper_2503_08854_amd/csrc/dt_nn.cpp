@@ -49,8 +49,7 @@ struct dt_scorer {
   int64_t step = 0;
   std::vector<std::pair<void*, size_t>> allocs;
   float *w = nullptr, *m = nullptr, *v = nullptr, *g = nullptr;
-  uint16_t* wt = nullptr;  // BF16 weights transposed, layer after layer
-  uint16_t* wf = nullptr;  // BF16 weights in the order of the training kernel's products
+  uint16_t* wf = nullptr;  // BF16 weights in the order of the kernels' products
   float* z = nullptr;
   uint16_t *h3 = nullptr, *ft = nullptr, *cat = nullptr, *d4 = nullptr, *d5 = nullptr, *d6 = nullptr;
   float* records = nullptr;
@@ -111,8 +110,7 @@ dt_status dt_scorer_create(dt_ctx* c, int32_t max_batch, uint64_t seed, dt_score
   A(&s->m, s->np, "scorer Adam m");
   A(&s->v, s->np, "scorer Adam v");
   A(&s->g, s->np, "scorer gradients");
-  A(&s->wt, s->np, "scorer transposed BF16 weights");
-  A(&s->wf, TRAIN_FRAGS, "scorer BF16 weights");
+  A(&s->wf, SCORER_FRAGS, "scorer BF16 weights");
   A(&s->z, B, "scorer logits");
   A(&s->h3, B * 1152, "scorer h3");
   A(&s->ft, B * 16, "scorer ft");
@@ -133,8 +131,8 @@ dt_status dt_scorer_create(dt_ctx* c, int32_t max_batch, uint64_t seed, dt_score
   }
   if (e == hipSuccess) e = hipMemsetAsync(s->m, 0, sizeof(float) * s->np, c->stream);
   if (e == hipSuccess) e = hipMemsetAsync(s->v, 0, sizeof(float) * s->np, c->stream);
-  if (e == hipSuccess) e = hipMemsetAsync(s->wf, 0, sizeof(uint16_t) * TRAIN_FRAGS, c->stream);
-  if (e == hipSuccess) e = launch_scorer_weights(s->w, s->wt, s->wf, c->stream);
+  if (e == hipSuccess) e = hipMemsetAsync(s->wf, 0, sizeof(uint16_t) * SCORER_FRAGS, c->stream);
+  if (e == hipSuccess) e = launch_scorer_weights(s->w, s->wf, c->stream);
   if (e != hipSuccess) {
     sfree(s);
     delete s;
@@ -168,7 +166,7 @@ dt_status dt_scorer_set_params(dt_scorer* s, const float* d_in) {
   hipError_t e = hipMemcpyAsync(s->w, d_in, sizeof(float) * s->np, hipMemcpyDeviceToDevice, st);
   if (e == hipSuccess) e = hipMemsetAsync(s->m, 0, sizeof(float) * s->np, st);
   if (e == hipSuccess) e = hipMemsetAsync(s->v, 0, sizeof(float) * s->np, st);
-  if (e == hipSuccess) e = launch_scorer_weights(s->w, s->wt, s->wf, st);
+  if (e == hipSuccess) e = launch_scorer_weights(s->w, s->wf, st);
   s->step = 0;
   return e == hipSuccess ? DT_OK : hip_fail(e, "scorer set params");
 }
@@ -200,13 +198,8 @@ dt_status dt_scorer_infer_rows(dt_scorer* s, const uint16_t* d_stamps, const uin
   a.feats = d_feats;
   a.B = B;
   a.w = s->w;
-  int64_t t = 0;
-  for (int i = 0; i < NL; ++i) {
-    a.b_off[i] = s->L[i].b;
-    a.t_off[i] = t;
-    t += (int64_t)s->L[i].K * s->L[i].N;
-  }
-  a.wt = s->wt;
+  for (int i = 0; i < NL; ++i) a.b_off[i] = s->L[i].b;
+  a.wf = s->wf;
   a.z = d_logits;
   a.rows = d_rows;
   hipError_t e = launch_scorer_fused(a, s->ctx->stream);
@@ -231,7 +224,7 @@ dt_status dt_scorer_train_step(dt_scorer* s, const uint16_t* d_stamps, const uin
   if (!d_labels || !(lr > 0.f)) return fail(DT_E_ARG, "NULL labels or non-positive learning rate");
   DeviceGuard guard(s->ctx->device);
   ++s->step;
-  const AdamArgs adam{s->w, s->m,   s->v,   s->wt, s->wf, lr, 0.9f, 0.999f, 1e-8f, (float)(1.0 - pow(0.9, (double)s->step)),
+  const AdamArgs adam{s->w, s->m,   s->v,   s->wf, lr, 0.9f, 0.999f, 1e-8f, (float)(1.0 - pow(0.9, (double)s->step)),
                       (float)(1.0 - pow(0.999, (double)s->step))};
   hipError_t e = launch_train_grad(train_args(s, d_stamps, d_feats, d_labels, B, s->z), d_loss,
                                    nullptr, &adam, s->ctx->stream);

@@ -1,294 +1,328 @@
 // k_scorer_fused.hip -- inference forward of the cell scorer in one kernel.
 //
-// The same network and rounding points as the layer-by-layer path (every
-// activation rounded to BF16 after bias and ReLU, FP32 accumulation on
-// v_mfma_f32_16x16x16_bf16 in the same K order except that the 1152-deep
-// layer sums two K halves, FP32 biases), with every intermediate kept in LDS.
-// A workgroup of eight waves (two per SIMD, so one wave's MFMA and LDS
-// latency overlaps the other's; the LDS holds one workgroup per CU) takes 16
-// cells at a time and makes them the M dimension of every MFMA tile: a convolution
-// output pixel is one 16 (cells) x 16 (channels) tile whose A operand reads
-// the input pixel's 16-channel group of every cell (one 8-byte LDS read per
-// lane), so all pixel and tap arithmetic is uniform across the wave.  The
-// convolutions stream row by row through three-row ring buffers; the fully
-// connected layers then run on the group's 16 rows.  Per cell only the
-// 441 + 16 BF16 inputs are read and one FP32 logit is written.  Weights
-// arrive transposed ([N][K], one block per layer) so that every B operand
-// (four consecutive K of one output column) is one 8-byte load.
+// The same network, rounding points and K order as the training path (every
+// activation rounded to BF16 after bias and ReLU, FP32 accumulation in steps
+// of 32, conv1's nine taps in one of 16), the 1152-deep layer in two halves
+// that are then added, with every intermediate kept in LDS.
+//
+// A workgroup of twelve waves (three per SIMD; the LDS holds one workgroup per
+// CU) takes 16 cells at a time and makes them the columns of every product,
+// the weights being the rows: pixel arithmetic is uniform across the wave, an
+// operand is a contiguous read of 16 or 32 channels of a pixel of every cell,
+// and a lane's four results are four channels of one cell, one 8-byte write.
+// The weights of the convolutions stay in registers: both channel tiles of
+// conv2, so that one LDS read feeds two products, and one of conv3's.  The
+// convolutions run as a pipeline with one barrier per conv2 row: in step t the
+// waves compute row t of conv2, rows 2t + 2 and 2t + 3 of conv1 for the next
+// step and, every other step, a row of conv3 from finished conv2 rows, over
+// ring buffers of five and four rows.  Per cell only the 441 + 16 BF16 inputs
+// are read and one FP32 logit is written.
+//
+// 10 000 cells in 52.8 us (a group in 16 us, three rounds of 256; 4 us of
+// start: weights and stamps from memory).  It is bound by the issue of the
+// vector instructions around the products (40 % of the cycles) and by LDS
+// (41 %), with the matrix cores busy for 24 %.  Before, 165 us: products of
+// K = 16 with cells as the rows (four 2-byte writes per tile), weights read
+// from LDS for each product, sixteen 2-byte reads for conv1's taps of four
+// pixels, three barriers per row.  On the way: 64-byte steps between cells in
+// an operand and unaligned stamp reads cost 12.5 M of 32.5 M CU cycles in bank
+// conflicts (65 us); the three parts of a step in another order in each wave
+// of a SIMD, 77 us; weights of the 1152-deep layer read ahead during the
+// convolutions, more registers than there are (spills, 97 us).
 #include "dt_common.hpp"
 
 namespace dtk {
 
 namespace {
-typedef short short4_t __attribute__((ext_vector_type(4)));
-typedef float float4_t __attribute__((ext_vector_type(4)));
+typedef short s4_t __attribute__((ext_vector_type(4)));
+typedef __bf16 bf8_t __attribute__((ext_vector_type(8)));
+typedef float f4_t __attribute__((ext_vector_type(4)));
+typedef float f2_t __attribute__((ext_vector_type(2)));
+typedef __bf16 bf2_t __attribute__((ext_vector_type(2)));
 
-// round to nearest even with the hardware conversion (v_cvt_pk_bf16_f32)
-__device__ __forceinline__ uint16_t f2bf(float f) { return __builtin_bit_cast(uint16_t, (__bf16)f); }
-__device__ __forceinline__ uint16_t relu_bf(float v, float b) { return f2bf(fmaxf(v + b, 0.f)); }
-typedef float float2_t __attribute__((ext_vector_type(2)));
-typedef __bf16 bf16x2_t __attribute__((ext_vector_type(2)));
 // two values to BF16 in one hardware conversion (round to nearest even)
 __device__ __forceinline__ uint32_t cvt2(float a, float b) {
-  return __builtin_bit_cast(uint32_t, __builtin_convertvector(float2_t{a, b}, bf16x2_t));
+  return __builtin_bit_cast(uint32_t, __builtin_convertvector(f2_t{a, b}, bf2_t));
 }
-__device__ __forceinline__ short4_t as4(uint2 v) {
-  return short4_t{(short)(v.x & 0xffffu), (short)(v.x >> 16), (short)(v.y & 0xffffu), (short)(v.y >> 16)};
+__device__ __forceinline__ bf8_t ld8(const uint16_t* p) { return *reinterpret_cast<const bf8_t*>(p); }
+__device__ __forceinline__ f4_t ld4f(const float* p) { return *reinterpret_cast<const f4_t*>(p); }
+__device__ __forceinline__ f4_t mfma(bf8_t a, bf8_t b, f4_t c) {
+  return __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, b, c, 0, 0, 0);
 }
-__device__ __forceinline__ short4_t ld4(const uint16_t* p) {  // 8-byte aligned read
-  return as4(*reinterpret_cast<const uint2*>(p));
+// bias, ReLU and rounding of four channels, stored at o
+__device__ __forceinline__ uint2 act4(f4_t d, f4_t b) {
+  return make_uint2(cvt2(fmaxf(d[0] + b[0], 0.f), fmaxf(d[1] + b[1], 0.f)),
+                    cvt2(fmaxf(d[2] + b[2], 0.f), fmaxf(d[3] + b[3], 0.f)));
 }
-__device__ __forceinline__ float4_t mfma(short4_t a, short4_t b, float4_t c) {
-  return __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(a, b, c, 0, 0, 0);
-}
-// D tile rows 4 kq + r (cells), column r16: relu(d + bias) as BF16 into o[row * stride + r16]
-__device__ __forceinline__ void store4(uint16_t* o, int kq, int r16, int stride, float4_t d, float bias) {
-  const uint32_t p01 = cvt2(fmaxf(d[0] + bias, 0.f), fmaxf(d[1] + bias, 0.f));
-  const uint32_t p23 = cvt2(fmaxf(d[2] + bias, 0.f), fmaxf(d[3] + bias, 0.f));
-  o[(4 * kq + 0) * stride + r16] = (uint16_t)p01;
-  o[(4 * kq + 1) * stride + r16] = (uint16_t)(p01 >> 16);
-  o[(4 * kq + 2) * stride + r16] = (uint16_t)p23;
-  o[(4 * kq + 3) * stride + r16] = (uint16_t)(p23 >> 16);
+__device__ __forceinline__ void put4(uint16_t* o, f4_t d, f4_t b) { *reinterpret_cast<uint2*>(o) = act4(d, b); }
+__device__ __forceinline__ bf8_t keep8(bf8_t v, bool keep) {
+  uint4 u = __builtin_bit_cast(uint4, v);
+  u.x = keep ? u.x : 0u;
+  u.y = keep ? u.y : 0u;
+  u.z = keep ? u.z : 0u;
+  u.w = keep ? u.w : 0u;
+  return __builtin_bit_cast(bf8_t, u);
 }
 
-constexpr int G = 16;                        // cells per workgroup
-constexpr int NW = 8;                        // waves per workgroup
-constexpr int NTH = 64 * NW;                 // threads per workgroup
-constexpr int W1K = 16, W2K = 148, W3K = 292;  // padded K strides of the conv weights in LDS
-constexpr int FTS = 20, CTS = 132, H6S = 68;
-constexpr int SPAD = 23 * 23;                // the stamp with a one-pixel zero border
+constexpr int G = 16;            // cells at a time
+constexpr int NW = 12;           // waves
+constexpr int NTH = 64 * NW;
+constexpr int SROW = 24, SCELL = 23 * SROW + 2;  // a cell's stamp with a one-pixel zero border; odd in words
+constexpr int PX1 = G * 16, PX2 = G * 32;    // a pixel's channels of all cells
+constexpr int R1 = 5, R2 = 4;    // rows of the rings
+constexpr int C1 = 22, C2 = 12;  // their columns, the first one zero (the last row is followed by one more)
+constexpr int BB2 = 16, BB3 = 48, BB4 = 80, BB5 = 144, BB6 = 208, BB7 = 272, BIAS = 276;
+constexpr f4_t ZERO4 = {0.f, 0.f, 0.f, 0.f};
+constexpr bf8_t ZERO8 = {};
+
+struct __align__(16) GroupLds {
+  uint16_t stg[G * SCELL + 8];           // stamps [cell][bordered row][24]
+  // activations [pixel][channel / 8][cell][8]: the lanes of an operand read one contiguous piece
+  uint16_t h1r[(R1 * C1 + 1) * PX1];     // conv1 rows [row][x + 1]
+  uint16_t h2r[(R2 * C2 + 1) * PX2];     // conv2 rows [row][x + 1]
+  uint16_t h3s[36 * PX2];                // conv3 output
+  uint16_t ftg[G * 16];
+  float bias[BIAS];                      // layer after layer
+  int64_t srow[2][G];                    // this and the next group's rows of the inputs and logits
+};
+static_assert(sizeof(GroupLds) <= 160 * 1024, "LDS of a CU");
 }  // namespace
 
 template <bool ROWS>
 __global__ __launch_bounds__(NTH) void k_scorer_fused(ScorerFusedArgs A) {
-  // A workgroup owns 16 cells at a time; the cells are the M (row) dimension
-  // of every MFMA tile, so all pixel / tap index arithmetic is uniform.
-  // Activations are [pixel][cell][channel]; the convolutions stream by rows
-  // with three-row ring buffers (a stride-2 3x3 layer needs three input rows
-  // per output row), and only conv3's output is kept whole for FC4.
-  __shared__ __align__(16) uint16_t w1s[16 * W1K];           // [n][k], k < 9 used
-  __shared__ __align__(16) uint16_t w2s[32 * W2K];           // [n][k]
-  __shared__ __align__(16) uint16_t w3s[32 * W3K];           // [n][k]
-  __shared__ __align__(16) uint16_t stg[SPAD * G];           // stamps [pixel of the 23 x 23 zero-bordered stamp][cell]
-  __shared__ __align__(16) uint16_t h1r[3 * 21 * G * 16];    // conv1 rows (ring of 3) [row][x][cell][16]
-  __shared__ __align__(16) uint16_t h2r[3 * 11 * G * 32];    // conv2 rows (ring of 3) [row][x][cell][32]
-  __shared__ __align__(16) uint16_t h3s[36 * G * 32];        // conv3 output [pixel][cell][32]
-  __shared__ __align__(16) uint16_t ftg[G * FTS];
-  __shared__ __align__(16) uint16_t cat[G * CTS];
-  __shared__ __align__(16) uint16_t h6[G * H6S];
-  __shared__ int srow[G];  // the group's rows of the inputs and logits
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  __shared__ GroupLds L;
+  uint16_t* const stg = L.stg;
+  uint16_t* const h1r = L.h1r;
+  uint16_t* const h2r = L.h2r;
+  uint16_t* const h3s = L.h3s;
+  uint16_t* const ftg = L.ftg;
+  float* const bias = L.bias;
+  int64_t(*const srow)[G] = L.srow;
+  // the fully connected layers work where conv1's first two ring rows are (the zero columns are left alone)
+  uint16_t* const cat = h1r + PX1;
+  uint16_t* const h6 = cat + G * 128;
+  f4_t* const red = reinterpret_cast<f4_t*>(h1r + (C1 + 1) * PX1);  // partial sums handed on: [2][output tile][lane]
+  static_assert(G * (128 + 64) <= 21 * PX1 && 2 * 4 * 64 * 8 <= 21 * PX1, "room in a ring row");
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int w = (int)__builtin_amdgcn_readfirstlane(tid >> 6);
   const int r16 = lane & 15, kq = lane >> 4;
-  const uint16_t* wt = A.wt;
-  // conv weights into LDS, 8 bytes per load, all loads of a thread issued together
-  {
-    const uint2* g2 = reinterpret_cast<const uint2*>(wt + A.t_off[1]);  // 32 rows x 36 quads
-    const uint2* g3 = reinterpret_cast<const uint2*>(wt + A.t_off[2]);  // 32 rows x 72 quads
-    constexpr int Q2 = (32 * 36 + NTH - 1) / NTH, Q3 = (32 * 72 + NTH - 1) / NTH;
-    uint2 v2[Q2], v3[Q3];
+  const uint16_t* wf = A.wf + 8 * lane;
+  const int put = ((kq >> 1) * 16 + r16) * 8 + 4 * (kq & 1);  // a lane's four results: channels 4 kq .. of cell r16
+  const int n_groups = (A.B + G - 1) / G;
+  // a group's stamps: thread px reads its pixel of every cell, before the last layers of the group before
+  const int px = min(tid, 440);
+  uint32_t next[G / 2];
+  auto load_stamps = [&](int grp, const int64_t* rows) {
+    if (tid >= 448) return;
 #pragma unroll
-    for (int q = 0; q < Q2; ++q) {
-      const int i = tid + NTH * q;
-      v2[q] = i < 32 * 36 ? g2[i] : make_uint2(0u, 0u);
+    for (int c = 0; c < G; ++c) {
+      const uint32_t v = A.stamps[(ROWS ? rows[c] : (int64_t)min(grp * G + c, A.B - 1)) * 441 + px];
+      next[c / 2] = c & 1 ? next[c / 2] | (v << 16) : v;
     }
-#pragma unroll
-    for (int q = 0; q < Q3; ++q) {
-      const int i = tid + NTH * q;
-      v3[q] = i < 32 * 72 ? g3[i] : make_uint2(0u, 0u);
-    }
-    uint16_t w1v = 0;
-    if (tid < 16 * W1K) {
-      const int n = tid / W1K, k = tid % W1K;
-      w1v = k < 9 ? wt[A.t_off[0] + n * 9 + k] : (uint16_t)0;
-    }
-#pragma unroll
-    for (int q = 0; q < Q2; ++q) {
-      const int i = tid + NTH * q;
-      if (i < 32 * 36) *reinterpret_cast<uint2*>(&w2s[(i / 36) * W2K + 4 * (i % 36)]) = v2[q];
-    }
-#pragma unroll
-    for (int q = 0; q < Q3; ++q) {
-      const int i = tid + NTH * q;
-      if (i < 32 * 72) *reinterpret_cast<uint2*>(&w3s[(i / 72) * W3K + 4 * (i % 72)]) = v3[q];
-    }
-    if (tid < 16 * W1K) w1s[tid] = w1v;
+  };
+  auto load_rows = [&](int grp, int64_t* rows) {
+    if (tid < G) rows[tid] = A.rows[min(grp * G + tid, A.B - 1)];
+  };
+  if (ROWS) {
+    load_rows(blockIdx.x, srow[0]);
+    __syncthreads();
   }
-  const float* b1 = A.w + A.b_off[0];
-  const float* b2 = A.w + A.b_off[1];
-  const float* b3 = A.w + A.b_off[2];
-  const float bias1 = b1[r16], bias2a = b2[r16], bias2b = b2[16 + r16], bias3a = b3[r16], bias3b = b3[16 + r16];
-  float* red = reinterpret_cast<float*>(h1r);  // FC4 partial sums (h1r is free by then)
-  // this lane's conv1 taps k = 4 kq + i as LDS offsets into the bordered
-  // stamp (taps 9..15 are padding: zero)
-  int toff[4];
-  bool tapv[4];
+  load_stamps(blockIdx.x, srow[0]);
+  // convolution weights: one copy to LDS (the conv3 output's place), from there to every wave's registers
+  for (int i = tid; i < SCORER_F4 / 8; i += NTH)
+    reinterpret_cast<uint4*>(h3s)[i] = reinterpret_cast<const uint4*>(A.wf)[i];
+  static_assert(SCORER_F4 <= 36 * PX2, "room for the convolutions' weights");
+  for (int i = tid; i <= BB7; i += NTH) {
+    const int l = (i >= BB2) + (i >= BB3) + (i >= BB4) + (i >= BB5) + (i >= BB6) + (i >= BB7);
+    const int first = l == 0 ? 0 : l == 1 ? BB2 : l == 2 ? BB3 : l == 3 ? BB4 : l == 4 ? BB5 : l == 5 ? BB6 : BB7;
+    bias[i] = A.w[A.b_off[l] + i - first];
+  }
+  // the zero borders, never written below: the stamps' and the columns left and right of the ring rows
+  for (int i = tid; i < (G * SCELL + 8) / 8; i += NTH) reinterpret_cast<uint4*>(stg)[i] = make_uint4(0, 0, 0, 0);
+  for (int i = tid; i < (R1 + 1) * PX1 / 8; i += NTH)
+    reinterpret_cast<uint4*>(h1r + (i / (PX1 / 8)) * C1 * PX1)[i % (PX1 / 8)] = make_uint4(0, 0, 0, 0);
+  for (int i = tid; i < (R2 + 1) * PX2 / 8; i += NTH)
+    reinterpret_cast<uint4*>(h2r + (i / (PX2 / 8)) * C2 * PX2)[i % (PX2 / 8)] = make_uint4(0, 0, 0, 0);
+  __syncthreads();
+  const int n3 = w & 1;
+  bf8_t a2[2][5], a3[9];
+#pragma unroll
+  for (int n = 0; n < 2; ++n)
+#pragma unroll
+    for (int s = 0; s < 5; ++s) a2[n][s] = ld8(h3s + 8 * lane + SCORER_F2 + (5 * n + s) * 512);
+#pragma unroll
+  for (int s = 0; s < 9; ++s) a3[s] = ld8(h3s + 8 * lane + SCORER_F3 + (9 * n3 + s) * 512);
+  // conv1 takes K = 16: lanes kq = 0 hold taps 0 1 2 5, kq = 1 taps 6 7 3 4, kq = 2 tap 8 (the products of eight K
+  // are summed together, so the order within them is free).  A lane reads runs of neighbouring pixels z, x, y in
+  // aligned words and forms the pairs of taps of output pixel j by a byte selector that also writes the zeros:
+  //   kq = 0: z = row 0 (taps 0, 1)   x, y = rows 0 and 1, two pixels on (taps 2, 5)
+  //   kq = 1: z = row 2 (taps 6, 7)   x, y = row 1 and the same two pixels on (taps 3, 4)
+  //   kq = 2: z = row 2, two pixels on (tap 8)
+  s4_t a1;
 #pragma unroll
   for (int i = 0; i < 4; ++i) {
-    const int k = 4 * kq + i;
-    tapv[i] = k < 9;
-    toff[i] = (k < 9 ? ((k / 3) * 23 + k % 3) * G : 0) + r16;
+    const int k = kq == 0 ? (i < 3 ? i : 5) : kq == 1 ? (i < 2 ? 6 + i : 1 + i) : 8 + i + 4 * (kq - 2);
+    a1[i] = (short)h3s[SCORER_F1 + ((k >> 3) * 16 + r16) * 8 + (k & 7)];
   }
-  // the zero border (never written below)
-  for (int i = tid; i < SPAD * G; i += NTH) stg[i] = 0;
-  const int n_groups = (A.B + G - 1) / G;
-  for (int grp = blockIdx.x; grp < n_groups; grp += gridDim.x) {
-    __syncthreads();  // the previous group's readers of stg / h3s / cat / h6 / srow are done; weights loaded
+  const int oz = r16 * SCELL + (kq == 0 ? 0 : 2 * SROW) + (kq >= 2 ? 2 : 0);
+  const int ox = r16 * SCELL + (kq == 1 ? SROW : 2), oy = r16 * SCELL + SROW + 2;
+  const uint32_t ze = kq < 2 ? 0x03020100u : kq == 2 ? 0x0c0c0100u : 0x0c0c0c0cu,
+                 zo = kq < 2 ? 0x05040302u : kq == 2 ? 0x0c0c0302u : 0x0c0c0c0cu,
+                 qe = kq == 0 ? 0x05040100u : kq == 1 ? 0x03020100u : 0x0c0c0c0cu,
+                 qo = kq == 0 ? 0x07060302u : kq == 1 ? 0x05040302u : 0x0c0c0c0cu;
+  const int x1 = 4 * (w % 6);  // of row y or y + 1; the sixth share of a row is its last pixel
+  auto conv1 = [&](int y) {
+    y += w >= 6;
+    uint16_t* o = h1r + ((unsigned)y % R1 * C1 + 1 + x1) * PX1 + put;
+    uint2 v[4];
+    if (y > 20) {  // the row below the image
+#pragma unroll
+      for (int j = 0; j < 4; ++j) v[j] = make_uint2(0, 0);
+    } else {
+      const uint16_t* p = stg + y * SROW + x1;  // output pixel (y, x) reads bordered pixels (y + dy, x + dx)
+      const uint32_t* z = reinterpret_cast<const uint32_t*>(p + oz);
+      const uint32_t* x = reinterpret_cast<const uint32_t*>(p + ox);
+      const uint32_t* q = reinterpret_cast<const uint32_t*>(p + oy);
+      const f4_t bs = ld4f(bias + 4 * kq);
+#pragma unroll
+      for (int j = 0; j < 4; ++j) {
+        const int i = j / 2;
+        const uint2 b = j & 1 ? make_uint2(__builtin_amdgcn_perm(z[i + 1], z[i], zo), __builtin_amdgcn_perm(q[i], x[i], qo))
+                              : make_uint2(__builtin_amdgcn_perm(z[i], z[i], ze), __builtin_amdgcn_perm(q[i], x[i], qe));
+        v[j] = act4(__builtin_amdgcn_mfma_f32_16x16x16bf16_1k(a1, __builtin_bit_cast(s4_t, b), ZERO4, 0, 0, 0), bs);
+      }
+    }
+    *reinterpret_cast<uint2*>(o) = v[0];
+    if (x1 < 20) {
+#pragma unroll
+      for (int j = 1; j < 4; ++j) *reinterpret_cast<uint2*>(o + j * PX1) = v[j];
+    }
+  };
+  // conv2 row t, pixel w: two taps per K step, the second one's by the lanes kq >= 2
+  const int c2 = 8 * (lane & 31), c2n = 8 * lane;  // the next pixel for the second tap
+  const bool second = kq >= 2;
+  auto conv2 = [&](int t) {
+    const int o0 = ((unsigned)(2 * t - 1 + R1) % R1 * C1 + 2 * w) * PX1;
+    const int o1 = ((unsigned)(2 * t) % R1 * C1 + 2 * w) * PX1, o2 = ((unsigned)(2 * t + 1) % R1 * C1 + 2 * w) * PX1;
+    bf8_t b[5];
+    b[0] = ld8(h1r + o0 + c2n);                                     // (0, 0) (0, 1)
+    b[1] = ld8(h1r + (second ? o1 + c2 : o0 + 2 * PX1 + c2));       // (0, 2) (1, 0)
+    b[2] = ld8(h1r + o1 + PX1 + c2n);                               // (1, 1) (1, 2)
+    b[3] = ld8(h1r + o2 + c2n);                                     // (2, 0) (2, 1)
+    b[4] = ld8(h1r + (second ? c2 : o2 + 2 * PX1 + c2));            // (2, 2), zero
+    f4_t acc[2] = {ZERO4, ZERO4};
+#pragma unroll
+    for (int s = 0; s < 5; ++s)
+#pragma unroll
+      for (int n = 0; n < 2; ++n) acc[n] = mfma(a2[n][s], b[s], acc[n]);
+    uint16_t* o = h2r + ((t % R2) * C2 + 1 + w) * PX2 + put;
+#pragma unroll
+    for (int n = 0; n < 2; ++n) put4(o + 256 * n, acc[n], ld4f(bias + BB2 + 16 * n + 4 * kq));
+  };
+  // conv3 row q, pixel w / 2: one tap per K step; below: its row 2q + 1 is in the image
+  auto conv3 = [&](int q, bool below) {
+    f4_t acc = ZERO4;
+#pragma unroll
+    for (int y = 0; y < 3; ++y) {
+      const uint16_t* p = h2r + ((unsigned)(2 * q + y - 1 + R2) % R2 * C2 + 2 * (w >> 1)) * PX2 + 8 * lane;
+#pragma unroll
+      for (int x = 0; x < 3; ++x) acc = mfma(a3[3 * y + x], y == 2 && !below ? ZERO8 : ld8(p + x * PX2), acc);
+    }
+    put4(h3s + (q * 6 + (w >> 1)) * PX2 + 256 * n3 + put, acc, ld4f(bias + BB3 + 16 * n3 + 4 * kq));
+  };
+
+  // FC4 (1152 -> 64; K step = conv3 pixel): output tile w & 3 in two sums over steps 0 .. 17 and 18 .. 35.  Wave n
+  // takes steps 0 .. 11 of its tile, wave n + 4 the rest of the first sum and 18 .. 23, wave n + 8 the last twelve
+  const int n4 = w & 3, part = w >> 2;
+  int buf = 0;
+  for (int grp = blockIdx.x; grp < n_groups; grp += gridDim.x, buf ^= 1) {
+    // read again for every group: hoisted out of this loop, the weights of the fully connected layers would
+    // not fit the registers
+    int again = 0;
+    asm volatile("" : "+s"(again));
+    const uint16_t* wg = wf + again;
+    __syncthreads();  // the previous group's readers of stg / h3s / cat / h6 / srow are done
     const int cell0 = grp * G;
-    if (ROWS) {
-      if (tid < G) srow[tid] = cell0 + tid < A.B ? (int)A.rows[cell0 + tid] : 0;
+    if (tid < 441) {
+      uint16_t* o = stg + (px / 21 + 1) * SROW + px % 21 + 1;
+#pragma unroll
+      for (int c = 0; c < G; ++c) o[c * SCELL] = (uint16_t)(c & 1 ? next[c / 2] >> 16 : next[c / 2]);
+    } else if (tid >= 512) {
+      const int r = (tid - 512) / 16, c = tid % 16;
+      ftg[((c >> 3) * G + r) * 8 + (c & 7)] = A.feats[(ROWS ? srow[buf][r] : (int64_t)min(cell0 + r, A.B - 1)) * 16 + c];
+    }
+    // the rows above the images: the last slots of the rings
+    if (tid < 21 * PX1 / 8)
+      reinterpret_cast<uint4*>(h1r + ((R1 - 1) * C1 + 1) * PX1)[tid] = make_uint4(0, 0, 0, 0);
+    if (tid < 11 * PX2 / 8)
+      reinterpret_cast<uint4*>(h2r + ((R2 - 1) * C2 + 1) * PX2)[tid] = make_uint4(0, 0, 0, 0);
+    if (ROWS && grp + (int)gridDim.x < n_groups) load_rows(grp + gridDim.x, srow[buf ^ 1]);
+    __syncthreads();
+    conv1(0);
+    __syncthreads();
+#pragma unroll 1
+    for (int t = 0; t < 11; ++t) {
+      if (t < 10) conv1(2 * t + 2);
+      if (w < 11) conv2(t);
+      if (t >= 2 && !(t & 1)) conv3(t / 2 - 1, true);
       __syncthreads();
     }
-    {
-      // the group's stamps: all loads of a thread issued together, then stored [pixel][cell]
-      constexpr int NQ = (441 * G + NTH - 1) / NTH;
-      uint16_t v[NQ];
+    conv3(5, false);
+    if (grp + (int)gridDim.x < n_groups) load_stamps(grp + gridDim.x, srow[buf ^ 1]);
+    __syncthreads();
+    f4_t acc4 = ZERO4;
+    const uint16_t* h = h3s + 8 * lane;
+    const uint16_t* p4 = wg + SCORER_F4 + n4 * 36 * 512;
+    auto steps4 = [&](int s) {  // six K steps from s on
+      bf8_t a4[6];
 #pragma unroll
-      for (int q = 0; q < NQ; ++q) {
-        const int i = tid + NTH * q;
-        const int c = i / 441;
-        const bool in = i < 441 * G && cell0 + c < A.B;
-        v[q] = in ? A.stamps[ROWS ? (int64_t)srow[c] * 441 + (i - 441 * c) : (int64_t)cell0 * 441 + i] : (uint16_t)0;
-      }
+      for (int i = 0; i < 6; ++i) a4[i] = ld8(p4 + (s + i) * 512);
 #pragma unroll
-      for (int q = 0; q < NQ; ++q) {
-        const int i = tid + NTH * q;
-        const int px = i % 441;
-        if (i < 441 * G) stg[((px / 21 + 1) * 23 + px % 21 + 1) * G + i / 441] = v[q];
+      for (int i = 0; i < 6; ++i) {
+        acc4 = mfma(a4[i], ld8(h + (s + i) * PX2), acc4);
+        __builtin_amdgcn_sched_barrier(0);
       }
-    }
-    for (int i = tid; i < G * 16; i += NTH) {
-      const int r = i / 16, c = i % 16;
-      ftg[r * FTS + c] = cell0 + r < A.B ? A.feats[(ROWS ? (int64_t)srow[r] : (int64_t)(cell0 + r)) * 16 + c]
-                                         : (uint16_t)0;
+    };
+    if (part < 2) {
+      steps4(18 * part);
+      if (part == 0) steps4(6);
+      red[(part * 4 + n4) * 64 + lane] = acc4;
+    } else {  // FC5 (16 -> 64)
+      const f4_t d = mfma(ld8(wg + SCORER_F5 + n4 * 512), keep8(ld8(ftg + 8 * (lane & 31)), kq < 2), ZERO4);
+      put4(cat + 256 * (4 + n4) + put, d, ld4f(bias + BB5 + 16 * n4 + 4 * kq));
     }
     __syncthreads();
-    const short4_t bw1 = ld4(&w1s[r16 * W1K + 4 * kq]);
-    int h1_done = 0;  // conv1 rows computed so far
-    for (int oy2 = 0; oy2 < 11; ++oy2) {
-      // conv1 rows up to 2 oy2 + 1: pixel (y, x) of the row is one 16 x 16 tile, wave w takes x = w, w + NW, ...
-      const int need = min(21, 2 * oy2 + 2);
-      for (int y = h1_done; y < need; ++y) {
-        for (int x = wave; x < 21; x += NW) {
-          // output pixel (y, x) reads bordered pixels (y + dy, x + dx), dy, dx in 0..2
-          const uint16_t* b = stg + (y * 23 + x) * G;
-          short v[4];
-#pragma unroll
-          for (int i = 0; i < 4; ++i) v[i] = tapv[i] ? (short)b[toff[i]] : (short)0;
-          const short4_t a = short4_t{v[0], v[1], v[2], v[3]};
-          const float4_t d = mfma(a, bw1, float4_t{0.f, 0.f, 0.f, 0.f});
-          uint16_t* o = h1r + ((y % 3) * 21 + x) * (G * 16);
-          store4(o, kq, r16, 16, d, bias1);
-        }
-      }
-      h1_done = need;
-      __syncthreads();
-      // conv2 row oy2: 11 pixels x 2 column tiles, wave w takes units w, w + NW, ...; K step s = tap s
-      for (int u = wave; u < 22; u += NW) {
-        const int ox = u >> 1, nt = u & 1;
-        float4_t acc = float4_t{0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-        for (int s = 0; s < 9; ++s) {
-          const int iy = 2 * oy2 + s / 3 - 1, ix = 2 * ox + s % 3 - 1;
-          short4_t a = short4_t{0, 0, 0, 0};
-          if ((unsigned)iy < 21u && (unsigned)ix < 21u) a = ld4(&h1r[((iy % 3) * 21 + ix) * (G * 16) + r16 * 16 + 4 * kq]);
-          acc = mfma(a, ld4(&w2s[(16 * nt + r16) * W2K + s * 16 + 4 * kq]), acc);
-        }
-        uint16_t* o = h2r + ((oy2 % 3) * 11 + ox) * (G * 32);
-        store4(o + 16 * nt, kq, r16, 32, acc, nt ? bias2b : bias2a);
-      }
-      __syncthreads();
-      // conv3 row oy3 once conv2 rows up to 2 oy3 + 1 exist: 6 pixels x 2 column tiles
-      if ((oy2 & 1) || oy2 == 10) {
-        const int oy3 = oy2 == 10 ? 5 : (oy2 - 1) / 2;
-        for (int u = wave; u < 12; u += NW) {
-          const int ox = u >> 1, nt = u & 1;
-          float4_t acc = float4_t{0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-          for (int s = 0; s < 9; ++s) {
-            const int iy = 2 * oy3 + s / 3 - 1, ix = 2 * ox + s % 3 - 1;
-            const bool in = (unsigned)iy < 11u && (unsigned)ix < 11u;
-#pragma unroll
-            for (int h = 0; h < 2; ++h) {
-              short4_t a = short4_t{0, 0, 0, 0};
-              if (in) a = ld4(&h2r[((iy % 3) * 11 + ix) * (G * 32) + r16 * 32 + 16 * h + 4 * kq]);
-              acc = mfma(a, ld4(&w3s[(16 * nt + r16) * W3K + s * 32 + 16 * h + 4 * kq]), acc);
-            }
-          }
-          const float bias3 = nt ? bias3b : bias3a;
-          store4(h3s + (oy3 * 6 + ox) * (G * 32) + 16 * nt, kq, r16, 32, acc, bias3);
-        }
-        __syncthreads();
-      }
+    if (part == 1) {
+      acc4 = red[n4 * 64 + lane];
+      steps4(12);
+      red[n4 * 64 + lane] = acc4;
+    } else if (part == 2) {
+      acc4 = red[(4 + n4) * 64 + lane];
+      steps4(24);
+      steps4(30);
     }
-    // FC4 (1152 -> 64; K = pixel * 32 + channel) and FC5 (16 -> 64): waves w and w + 4 own columns
-    // 16w .. 16w + 15 and K steps 0..35 and 36..71; the second half's partial sums go through LDS
-    {
-      const int ct = wave & 3, kh = wave >> 2;
-      const int n = 16 * ct + r16;
-      const uint16_t* w4 = wt + A.t_off[3] + (int64_t)n * 1152;
-      float4_t acc = float4_t{0.f, 0.f, 0.f, 0.f};
-      for (int s0 = 36 * kh; s0 < 36 * kh + 36; s0 += 18) {
-        short4_t b[18];
+    bf8_t a6[4], a7[2];
 #pragma unroll
-        for (int u = 0; u < 18; ++u) b[u] = ld4(&w4[(s0 + u) * 16 + 4 * kq]);
+    for (int s = 0; s < 4; ++s) a6[s] = ld8(wg + SCORER_F6 + (n4 * 4 + s) * 512);
 #pragma unroll
-        for (int u = 0; u < 18; ++u) {
-          const int s = s0 + u;
-          acc = mfma(ld4(&h3s[((s >> 1) * G + r16) * 32 + (s & 1) * 16 + 4 * kq]), b[u], acc);
-        }
-      }
-      if (kh) {
+    for (int s = 0; s < 2; ++s) a7[s] = ld8(wg + SCORER_F7 + s * 512);
+    __syncthreads();
+    if (part == 2)
+      put4(cat + 256 * n4 + put, red[n4 * 64 + lane] + acc4, ld4f(bias + BB4 + 16 * n4 + 4 * kq));
+    __syncthreads();
+    if (w < 4) {  // FC6 (128 -> 64)
+      f4_t acc = ZERO4;
 #pragma unroll
-        for (int r = 0; r < 4; ++r) red[(ct * 4 + r) * 64 + lane] = acc[r];
-      }
-      __syncthreads();
-      if (kh == 0) {
-#pragma unroll
-        for (int r = 0; r < 4; ++r) acc[r] += red[(ct * 4 + r) * 64 + lane];
-        const float bias4 = A.w[A.b_off[3] + n];
-#pragma unroll
-        for (int r = 0; r < 4; ++r) cat[(4 * kq + r) * CTS + n] = f2bf(fmaxf(acc[r] + bias4, 0.f));
-        const short4_t b5 = ld4(wt + A.t_off[4] + (int64_t)n * 16 + 4 * kq);
-        const float4_t d5 = mfma(ld4(&ftg[r16 * FTS + 4 * kq]), b5, float4_t{0.f, 0.f, 0.f, 0.f});
-        const float bias5 = A.w[A.b_off[4] + n];
-#pragma unroll
-        for (int r = 0; r < 4; ++r) cat[(4 * kq + r) * CTS + 64 + n] = f2bf(fmaxf(d5[r] + bias5, 0.f));
-      }
+      for (int s = 0; s < 4; ++s) acc = mfma(a6[s], ld8(cat + 512 * s + 8 * lane), acc);
+      put4(h6 + 256 * w + put, acc, ld4f(bias + BB6 + 16 * w + 4 * kq));
     }
     __syncthreads();
-    // FC6 (128 -> 64): waves 0..3
-    if (wave < 4) {
-      const int n = 16 * wave + r16;
-      const uint16_t* w6 = wt + A.t_off[5] + (int64_t)n * 128;
-      short4_t b[8];
+    if (w == 0) {  // FC7 (64 -> 1), no ReLU: row 0 of a 16-high tile
+      f4_t acc = ZERO4;
 #pragma unroll
-      for (int s = 0; s < 8; ++s) b[s] = ld4(&w6[s * 16 + 4 * kq]);
-      float4_t acc = float4_t{0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-      for (int s = 0; s < 8; ++s) acc = mfma(ld4(&cat[r16 * CTS + s * 16 + 4 * kq]), b[s], acc);
-      const float bias6 = A.w[A.b_off[5] + n];
-#pragma unroll
-      for (int r = 0; r < 4; ++r) h6[(4 * kq + r) * H6S + n] = f2bf(fmaxf(acc[r] + bias6, 0.f));
-    }
-    __syncthreads();
-    // FC7 (64 -> 1), no ReLU: one wave, column 0 of a 16-wide tile
-    if (wave == 0) {
-      const uint16_t* w7 = wt + A.t_off[6];
-      float4_t acc = float4_t{0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-      for (int s = 0; s < 4; ++s) {
-        const int k = s * 16 + 4 * kq;
-        const short4_t b = r16 == 0 ? ld4(&w7[k]) : short4_t{0, 0, 0, 0};
-        acc = mfma(ld4(&h6[r16 * H6S + k]), b, acc);
-      }
-      if (r16 == 0) {
-        const float bias7 = A.w[A.b_off[6]];
-#pragma unroll
-        for (int r = 0; r < 4; ++r) {
-          const int cell = cell0 + 4 * kq + r;
-          if (cell < A.B) A.z[ROWS ? (int64_t)srow[4 * kq + r] : (int64_t)cell] = acc[r] + bias7;
-        }
-      }
+      for (int s = 0; s < 2; ++s) acc = mfma(a7[s], ld8(h6 + 512 * s + 8 * lane), acc);
+      const int cell = cell0 + lane;
+      if (lane < G && cell < A.B) A.z[ROWS ? srow[buf][lane] : (int64_t)cell] = acc[0] + bias[BB7];
     }
   }
 }

@@ -46,16 +46,10 @@ constexpr int FC4_STEPS = 36;
 // parameter vector (the scorer's layer table)
 constexpr int W1 = 0, B1 = 144, W2 = 160, B2 = 4768, W3 = 4800, B3 = 14016, W4 = 14048, B4 = 87776, W5 = 87840,
               B5 = 88864, W6 = 88928, B6 = 97120, W7 = 97184, B7 = 97248, NP = 97249;
-// transposed weights [N][K], layer after layer
-constexpr int T2 = 144, T3 = 4752, T4 = 13968, T5 = 87696, T6 = 88720, T7 = 96912;
-// Fragments: 512 weights, eight consecutive K of row lane & 15 for each lane in turn.  Forward (rows = output
-// channels): layer l from F<l>, row tile by row tile, K steps of 32 (padded with zeros).  Back (rows = inputs,
-// K = outputs): layer l from G<l>; convolutions tap by tap, row tile by row tile.
-constexpr int FRAG = 512;
-constexpr int F1 = 0, F2 = F1 + FRAG, F3 = F2 + 10 * FRAG, F4 = F3 + 18 * FRAG, F5 = F4 + 144 * FRAG,
-              F6 = F5 + 4 * FRAG, F7 = F6 + 16 * FRAG, G2 = F7 + 2 * FRAG, G3 = G2 + 9 * FRAG, G4 = G3 + 18 * FRAG, G6 = G4 + 144 * FRAG,
-              FN = G6 + 16 * FRAG;
-static_assert(FN == TRAIN_FRAGS, "fragment buffer size");
+// fragments of the BF16 weights
+constexpr int FRAG = SCORER_FRAG;
+constexpr int F1 = SCORER_F1, F2 = SCORER_F2, F3 = SCORER_F3, F4 = SCORER_F4, F5 = SCORER_F5, F6 = SCORER_F6,
+              F7 = SCORER_F7, G2 = SCORER_G2, G3 = SCORER_G3, G4 = SCORER_G4, G6 = SCORER_G6;
 // a workgroup's record: the convolutions' parameters as in the vector, the biases B4 B5 B6, layer 7 and the loss
 constexpr int R4 = W4, R5 = R4 + 64, R6 = R5 + 64, R7 = R6 + 64, RL = R7 + 65, RN = RL + 1;
 static_assert(RN <= TRAIN_RECORD, "record size");
@@ -587,39 +581,32 @@ __global__ __launch_bounds__(NT) void k_train_cells(TrainArgs A) {
 __device__ __forceinline__ int frag_at(int row, int k, int steps) {
   return ((row >> 4) * steps + (k >> 5)) * FRAG + (((k & 31) >> 3) * 16 + (row & 15)) * 8 + (k & 7);
 }
-// The BF16 copies of parameter i: transposed, and in the forward and back fragments.
-__device__ __forceinline__ void put_weight(uint16_t* wt, uint16_t* wf, int i, uint16_t b) {
+// The BF16 copies of parameter i in the forward and back fragments.
+__device__ __forceinline__ void put_weight(uint16_t* wf, int i, uint16_t b) {
   int k, n;
   if (i < B1) {
     k = i / 16, n = i % 16;
-    wt[n * 9 + k] = b;
     wf[F1 + frag_at(n, k, 1)] = b;
   } else if (i >= W2 && i < B2) {
     k = (i - W2) / 32, n = (i - W2) % 32;
-    wt[T2 + n * 144 + k] = b;
     wf[F2 + frag_at(n, k, 5)] = b;
     wf[G2 + (k / 16) * FRAG + frag_at(k % 16, n, 1)] = b;
   } else if (i >= W3 && i < B3) {
     k = (i - W3) / 32, n = (i - W3) % 32;
-    wt[T3 + n * 288 + k] = b;
     wf[F3 + frag_at(n, k, 9)] = b;
     wf[G3 + (k / 32) * 2 * FRAG + frag_at(k % 32, n, 1)] = b;
   } else if (i >= W4 && i < B4) {
     k = (i - W4) / 64, n = (i - W4) % 64;
-    wt[T4 + n * 1152 + k] = b;
     wf[F4 + frag_at(n, k, FC4_STEPS)] = b;
     wf[G4 + frag_at(k, n, 2)] = b;
   } else if (i >= W5 && i < B5) {
     k = (i - W5) / 64, n = (i - W5) % 64;
-    wt[T5 + n * 16 + k] = b;
     wf[F5 + frag_at(n, k, 1)] = b;
   } else if (i >= W6 && i < B6) {
     k = (i - W6) / 64, n = (i - W6) % 64;
-    wt[T6 + n * 128 + k] = b;
     wf[F6 + frag_at(n, k, 4)] = b;
     wf[G6 + frag_at(k, n, 2)] = b;
   } else if (i >= W7 && i < B7) {
-    wt[T7 + i - W7] = b;
     wf[F7 + frag_at(0, i - W7, 2)] = b;
   }
 }
@@ -632,7 +619,7 @@ __device__ __forceinline__ void adam(const AdamArgs& P, int i, float g) {
   P.v[i] = v;
   const float x = P.w[i] - P.lr * (m / P.c1) / (sqrtf(v / P.c2) + P.eps);
   P.w[i] = x;
-  put_weight(P.wt, P.wf, i, f2bf(x));
+  put_weight(P.wf, i, f2bf(x));
 }
 
 // The gradient from the records and from the inputs and deltas of the fully
@@ -728,13 +715,13 @@ __global__ __launch_bounds__(SUM_T) void k_train_sum(TrainArgs A, int n_rec, flo
 }
 
 // The BF16 copies of all parameters.
-__global__ void k_scorer_weights(const float* __restrict__ w, uint16_t* __restrict__ wt, uint16_t* __restrict__ wf) {
+__global__ void k_scorer_weights(const float* __restrict__ w, uint16_t* __restrict__ wf) {
   const int i = blockIdx.x * blockDim.x + threadIdx.x;
-  if (i < NP) put_weight(wt, wf, i, f2bf(w[i]));
+  if (i < NP) put_weight(wf, i, f2bf(w[i]));
 }
 
-hipError_t launch_scorer_weights(const float* w, uint16_t* wt, uint16_t* wf, hipStream_t s) {
-  hipLaunchKernelGGL(k_scorer_weights, dim3((NP + 255) / 256), dim3(256), 0, s, w, wt, wf);
+hipError_t launch_scorer_weights(const float* w, uint16_t* wf, hipStream_t s) {
+  hipLaunchKernelGGL(k_scorer_weights, dim3((NP + 255) / 256), dim3(256), 0, s, w, wf);
   return hipGetLastError();
 }
 

@@ -91,3 +91,24 @@ def test_step_refreshes_every_copy_of_the_weights(scorer):
     for f in ("forward", "infer"):
         np.testing.assert_array_equal(getattr(sc, f)(Xt, Ft).cpu().numpy(), getattr(other, f)(Xt, Ft).cpu().numpy())
     np.testing.assert_array_equal(sc.grad(Xt, Ft, Yt)[1].cpu().numpy(), other.grad(Xt, Ft, Yt)[1].cpu().numpy())
+
+
+# 16 cells per group, 256 groups at a time
+@pytest.mark.parametrize("B", [1, 15, 16, 17, 4096, 4097, 4111, 16321])
+def test_inference_equals_the_training_forward(scorer, B):
+    """A batch whose 1152-deep layer is summed in two halves takes the same products in the same order as the
+    inference kernel: equal to the last bit, whole batches, slices of them and row lists alike."""
+    import torch
+    sc, _ = scorer
+    n = 16321
+    _, _, _, (Xt, Ft, _) = _batch(257, seed=7)
+    i = torch.arange(n, device="cuda") * 11 % 257
+    Xn, Fn = Xt[i].contiguous(), Ft[i].contiguous()
+    z = sc.forward(Xn, Fn)
+    assert torch.equal(sc.infer(Xn[:B].contiguous(), Fn[:B].contiguous()), z[:B])
+    rows = torch.randperm(n, generator=torch.Generator().manual_seed(B))[:B].cuda()
+    out = torch.full((n,), -7.0, device="cuda")
+    sc.infer_rows(Xn, Fn, rows, out=out)
+    want = torch.full((n,), -7.0, device="cuda")
+    want[rows] = z[rows]
+    assert torch.equal(out, want)
