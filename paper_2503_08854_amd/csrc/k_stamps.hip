@@ -11,9 +11,8 @@
 // built from three walks (representative, a + da, M0 + dm) with the stack's
 // device code, rounded to the nearest pixel; the stamp value is the
 // constant-flux S/N of the matched-filter planes stacked along it (Sec. 3).
-// A source on any member therefore shows as a peak near its (u, v).  One
-// wavefront per cell; each lane owns 7 of the 441 nodes.  Per-cell features
-// summarise the stamp and the cell's elements.
+// A source on any member therefore shows as a peak near its (u, v).  Per-cell
+// features summarise the stamp and the cell's elements.
 #include "dt_track.hpp"
 
 namespace dtk {
@@ -41,20 +40,47 @@ __device__ __forceinline__ float wave_max(float v) {
   return v;
 }
 
+// floor(x) + 1 of x = p + 1.5 for the nearest pixel floor(p + 0.5) of p: the
+// conversion truncates and saturates, and what lies left of the image (or is
+// NaN) becomes 0 or less.
+__device__ __forceinline__ int pixel1(double x) {
+  int r;
+  asm("v_cvt_i32_f64 %0, %1" : "=v"(r) : "v"(x));
+  return r;
+}
+
 // One wavefront per cell.  The three walks (k = 0 the representative, k = 1
 // with a + da, k = 2 with M0 + dm) are split over 63 lanes, lane = 21 k + c
 // walking chunk c of the exposures from a cold start; their pixel
 // coordinates (NaN behind the tangent plane, or for an orbit outside the
-// domain) go to this wave's LDS, 3 x n_exp x 16 bytes.
+// domain) go to LDS, 3 x n_exp x 16 bytes, and the usable exposures (the
+// three walks in front, the lattice can touch the image) are then packed to
+// the front in order, as the origin and the two steps of the lattice.  Then
+// node j = lane + 63 q is gathered by that lane, so that a lane's seven nodes
+// share u.
+//
+// A cell is usable in anything from none to all of its exposures (26 of 150
+// on average for cells of distant orbits).  What an exposure costs is vector
+// instructions and the wait for its record, so a node takes two fused
+// multiply-adds and two conversions that truncate and saturate, and the
+// frames' sizes and offsets are read for all exposures of a batch before
+// their nodes: 5000 such cells 321 -> 179 us, from 60 instructions per node in
+// nested branches (64-bit floors, conversions and products) that each waited
+// for scalar loads.  The cells with the most usable exposures bound it now:
+// two batches in flight made no difference (175 us), and four wavefronts
+// sharing four cells' nodes took 172 us there but 12 % longer on survey
+// exposures, where the walks are most of the time and the larger workgroups
+// leave fewer wavefronts resident.
 constexpr int STAMP_CHUNKS = 21;
+constexpr int LANES = 63;
+constexpr int PER = SP / LANES;  // 7 nodes per lane
+constexpr int STAMP_GB = 4;      // exposures whose gathers are in flight together
 
-// GB: usable exposures whose gathers are issued together (more loads in
-// flight per lane where a cell has many usable exposures).
-template <int GB>
 __global__ __launch_bounds__(64) void k_cell_stamps(StackArgs R, double da, double dm, uint16_t* __restrict__ st_bf,
                                                     float* __restrict__ st_f, uint16_t* __restrict__ ft_bf,
                                                     float* __restrict__ ft_f) {
-  extern __shared__ double2 trk[];  // [3][n_exp]
+  // [3][n_exp] track points, then [n_exp] indices of the usable exposures; at the end the nodes' sums
+  extern __shared__ double2 trk[];
   const int64_t cell = blockIdx.x;
   if (cell >= R.n) return;
   const int lane = threadIdx.x;
@@ -62,6 +88,10 @@ __global__ __launch_bounds__(64) void k_cell_stamps(StackArgs R, double da, doub
   const int n_exp = R.n_exp;
   const float2* __restrict__ planes = R.planes;
   const double nan = __builtin_nan("");
+  double2* const t0 = trk;
+  double2* const ta = trk + n_exp;
+  double2* const tm = trk + 2 * n_exp;
+  uint16_t* const list = reinterpret_cast<uint16_t*>(trk + 3 * n_exp);
   if (lane < 3 * STAMP_CHUNKS) {
     const int k = lane / STAMP_CHUNKS, c = lane % STAMP_CHUNKS;
     const int ch = (n_exp + STAMP_CHUNKS - 1) / STAMP_CHUNKS;
@@ -83,99 +113,107 @@ __global__ __launch_bounds__(64) void k_cell_stamps(StackArgs R, double da, doub
     }
   }
   __syncthreads();
-  constexpr int PER = (SP + 63) / 64;  // 7
+  // the usable exposures, 64 at a time, one per lane
+  int m = 0, near = 0;
+  for (int c0 = 0; c0 < n_exp; c0 += 64) {
+    const int ex = c0 + lane;
+    bool use = false, in = false;
+    double2 p0 = make_double2(0.0, 0.0), A = p0, B = p0;
+    if (ex < n_exp) {
+      p0 = t0[ex];
+      const double2 pa = ta[ex], pm = tm[ex];
+      const ExpMeta& x = meta[ex];
+      A = make_double2(pa.x - p0.x, pa.y - p0.y);
+      B = make_double2(pm.x - p0.x, pm.y - p0.y);
+      const double rx = fabs(A.x) + fabs(B.x) + 1.0, ry = fabs(A.y) + fabs(B.y) + 1.0;
+      use = __builtin_isfinite(pa.x) && __builtin_isfinite(pm.x) && p0.x + rx >= -0.5 && p0.x - rx < x.W - 0.5 &&
+            p0.y + ry >= -0.5 && p0.y - ry < x.H - 0.5;
+      in = use && p0.x >= -0.5 && p0.x < x.W - 0.5 && p0.y >= -0.5 && p0.y < x.H - 0.5;
+    }
+    const uint64_t mask = __ballot(use);
+    near += __builtin_popcountll(__ballot(in));
+    __syncthreads();  // (the places written are at or below those just read)
+    if (use) {
+      const int r = m + (int)__builtin_amdgcn_mbcnt_hi((uint32_t)(mask >> 32),
+                                                       __builtin_amdgcn_mbcnt_lo((uint32_t)mask, 0u));
+      t0[r] = make_double2(p0.x + 1.5, p0.y + 1.5);
+      ta[r] = A;
+      tm[r] = B;
+      list[r] = (uint16_t)ex;
+    }
+    m += __builtin_popcountll(mask);
+  }
+  __syncthreads();
+  const double u = (double)(lane % SW - SH) / (double)SH;
   float ps[PER], ph[PER];
-  double u[PER], v[PER];
+  double v[PER];
 #pragma unroll
   for (int q = 0; q < PER; ++q) {
     ps[q] = ph[q] = 0.f;
-    const int j = lane + 64 * q;
-    u[q] = (double)(j % SW - SH) / (double)SH;
-    v[q] = (double)(j / SW - SH) / (double)SH;
+    v[q] = (double)(lane / SW + 3 * q - SH) / (double)SH;
   }
-  const double* ea = R.a;
-  const double* ee = R.e;
-  const double* ei = R.inc;
-  int near = 0;
-  const double2* t0 = trk;
-  const double2* ta = trk + n_exp;
-  const double2* tm = trk + 2 * n_exp;
-  // exposures where the three walks are in front and the lattice can touch
-  // the image, found 64 at a time (one per lane), then visited in order
-  auto usable = [&](int ex, double2& p0, double& Ax, double& Ay, double& Bx, double& By) {
-    p0 = t0[ex];
-    const double2 pa = ta[ex], pm = tm[ex];
-    const ExpMeta& x = meta[ex];
-    Ax = pa.x - p0.x;
-    Ay = pa.y - p0.y;
-    Bx = pm.x - p0.x;
-    By = pm.y - p0.y;
-    const double rx = fabs(Ax) + fabs(Bx) + 1.0, ry = fabs(Ay) + fabs(By) + 1.0;
-    return __builtin_isfinite(pa.x) && __builtin_isfinite(pm.x) && p0.x + rx >= -0.5 && p0.x - rx < x.W - 0.5 &&
-           p0.y + ry >= -0.5 && p0.y - ry < x.H - 0.5;
-  };
-  // The gathers of up to GB usable exposures are issued together, then
+  // The gathers of STAMP_GB usable exposures are issued together, then
   // accumulated in exposure order.  Every lane issues all its loads (a node
-  // off the image reads the plane's first pixel and is dropped), so the wait
-  // before each accumulation covers only the older loads.
-  for (int c0 = 0; c0 < n_exp; c0 += 64) {
-    bool use = false;
-    if (c0 + lane < n_exp) {
-      double2 p0;
-      double Ax, Ay, Bx, By;
-      use = usable(c0 + lane, p0, Ax, Ay, Bx, By);
+  // off the image, and a stage past the last usable exposure, reads a
+  // plane's first pixel and is dropped), so the wait before each accumulation
+  // covers only the older loads.
+  for (int i0 = 0; i0 < m; i0 += STAMP_GB) {
+    float2 cur[STAMP_GB][PER];
+    bool ok[STAMP_GB][PER];
+    const float2* pl[STAMP_GB];
+    uint32_t W[STAMP_GB], H[STAMP_GB];
+    const int exs = list[min(i0 + (lane & (STAMP_GB - 1)), m - 1)];
+#pragma unroll
+    for (int b = 0; b < STAMP_GB; ++b) {
+      const ExpMeta& x = meta[__builtin_amdgcn_readlane(exs, b)];
+      pl[b] = planes + x.plane_off;
+      W[b] = i0 + b < m ? (uint32_t)x.W : 0u;
+      H[b] = (uint32_t)x.H;
     }
-    uint64_t mask = __ballot(use);
-    while (mask) {
-      float2 cur[GB][PER];
-      bool cur_ok[GB][PER];
+    __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-      for (int b = 0; b < GB; ++b) {
-        // no branch: a stage past the last usable exposure reloads exposure
-        // c0's first pixel and drops it, so all GB x PER loads are in flight
-        const bool has = mask != 0;  // wave-uniform
-        const int ex = c0 + (has ? __builtin_ctzll(mask) : 0);
-        mask &= mask - 1;
-        double2 p0;
-        double Ax, Ay, Bx, By;
-        (void)usable(ex, p0, Ax, Ay, Bx, By);
-        const ExpMeta& x = meta[ex];
-        near += (has && p0.x >= -0.5 && p0.x < x.W - 0.5 && p0.y >= -0.5 && p0.y < x.H - 0.5) ? 1 : 0;
+    for (int b = 0; b < STAMP_GB; ++b) {
+      const int i = min(i0 + b, m - 1);
+      const double2 p0 = t0[i], A = ta[i], B = tm[i];
+      // the node's track point p0 + u A + v B (two fused multiply-adds)
+      const double bx = fma(u, A.x, p0.x), by = fma(u, A.y, p0.y);
 #pragma unroll
-        for (int q = 0; q < PER; ++q) {
-          const int j = lane + 64 * q;
-          // the node's track point p0 + u A + v B (two fused multiply-adds)
-          const double px = fma(v[q], Bx, fma(u[q], Ax, p0.x));
-          const double py = fma(v[q], By, fma(u[q], Ay, p0.y));
-          const double fx = floor(px + 0.5), fy = floor(py + 0.5);
-          cur_ok[b][q] = has && j < SP && fx >= 0.0 && fx < (double)x.W && fy >= 0.0 && fy < (double)x.H;
-          const int64_t off = cur_ok[b][q] ? (int64_t)fy * x.W + (int64_t)fx : 0;
-          cur[b][q] = planes[x.plane_off + off];
-        }
+      for (int q = 0; q < PER; ++q) {
+        const int ix = pixel1(fma(v[q], B.x, bx)) - 1, iy = pixel1(fma(v[q], B.y, by)) - 1;
+        ok[b][q] = (unsigned)ix < W[b] && (unsigned)iy < H[b];
+        // (an image has at most 2^31 pixels; opaque, as the compiler would branch around the product)
+        uint32_t off = (uint32_t)iy * W[b] + (uint32_t)ix;
+        asm("" : "+v"(off));
+        cur[b][q] = pl[b][ok[b][q] ? off : 0u];
       }
+    }
 #pragma unroll
-      for (int b = 0; b < GB; ++b) {
+    for (int b = 0; b < STAMP_GB; ++b) {
 #pragma unroll
-        for (int q = 0; q < PER; ++q) {
-          if (cur_ok[b][q] && cur[b][q].y > 0.f) {
-            ps[q] += cur[b][q].x;
-            ph[q] += cur[b][q].y;
-          }
+      for (int q = 0; q < PER; ++q) {
+        if (ok[b][q] && cur[b][q].y > 0.f) {
+          ps[q] += cur[b][q].x;
+          ph[q] += cur[b][q].y;
         }
       }
     }
   }
+  __syncthreads();
+  float2* const sums = reinterpret_cast<float2*>(trk);
+#pragma unroll
+  for (int q = 0; q < PER; ++q)
+    if (lane < LANES) sums[lane + LANES * q] = make_float2(ps[q], ph[q]);
+  __syncthreads();
   float smax = -1e30f, ssum = 0.f, ssq = 0.f, cov = 0.f, smax_c = -1e30f, center = 0.f;
   int amax = 0;
-  for (int q = 0; q < PER; ++q) {
-    const int j = lane + 64 * q;
-    if (j >= SP) continue;
-    const float snr = ph[q] > 0.f ? ps[q] / sqrtf(ph[q]) : 0.f;
+  for (int j = lane; j < SP; j += 64) {
+    const float2 t = sums[j];
+    const float snr = t.y > 0.f ? t.x / sqrtf(t.y) : 0.f;
     if (st_bf) st_bf[cell * SP + j] = f2bf_s(snr);
     if (st_f) st_f[cell * SP + j] = snr;
     ssum += snr;
     ssq += snr * snr;
-    cov += ph[q] > 0.f ? 1.f : 0.f;
+    cov += t.y > 0.f ? 1.f : 0.f;
     if (snr > smax) {
       smax = snr;
       amax = j;
@@ -189,36 +227,35 @@ __global__ __launch_bounds__(64) void k_cell_stamps(StackArgs R, double da, doub
   // its own first maximum; lanes hold nodes lane, lane + 64, ...)
   int jmax = smax == gmax ? amax : SP;
 #pragma unroll
-  for (int m = 32; m >= 1; m >>= 1) jmax = min(jmax, __shfl_xor(jmax, m, 64));
+  for (int o = 32; o >= 1; o >>= 1) jmax = min(jmax, __shfl_xor(jmax, o, 64));
   ssum = wave_sum(ssum);
   ssq = wave_sum(ssq);
   cov = wave_sum(cov);
   center = wave_sum(center);
   smax_c = wave_max(smax_c);
-  if (lane < NFEAT) {
-    const float mean = ssum / SP;
-    const float var = fmaxf(ssq / SP - mean * mean, 0.f);
-    const float dxm = (float)(jmax % SW - SH), dym = (float)(jmax / SW - SH);
-    float f = 0.f;
-    switch (lane) {
-      case 0: f = gmax; break;
-      case 1: f = center; break;
-      case 2: f = mean; break;
-      case 3: f = sqrtf(var); break;
-      case 4: f = cov / SP; break;
-      case 5: f = sqrtf(dxm * dxm + dym * dym) / SH; break;
-      case 6: f = (float)near / (float)max(n_exp, 1); break;
-      case 7: f = (float)((ea[cell] - 2.75) / 0.75); break;
-      case 8: f = (float)(ee[cell] / 0.3); break;
-      case 9: f = (float)(ei[cell] / 0.2618); break;
-      case 10: f = smax_c; break;
-      case 11: f = dxm / SH; break;  // lattice coordinates (u, v) of the maximum
-      case 12: f = dym / SH; break;
-      default: f = 0.f; break;
-    }
-    if (ft_bf) ft_bf[cell * NFEAT + lane] = f2bf_s(f);
-    if (ft_f) ft_f[cell * NFEAT + lane] = f;
+  if (lane >= NFEAT) return;
+  const float mean = ssum / SP;
+  const float var = fmaxf(ssq / SP - mean * mean, 0.f);
+  const float dxm = (float)(jmax % SW - SH), dym = (float)(jmax / SW - SH);
+  float f = 0.f;
+  switch (lane) {
+    case 0: f = gmax; break;
+    case 1: f = center; break;
+    case 2: f = mean; break;
+    case 3: f = sqrtf(var); break;
+    case 4: f = cov / SP; break;
+    case 5: f = sqrtf(dxm * dxm + dym * dym) / SH; break;
+    case 6: f = (float)near / (float)max(n_exp, 1); break;
+    case 7: f = (float)((R.a[cell] - 2.75) / 0.75); break;
+    case 8: f = (float)(R.e[cell] / 0.3); break;
+    case 9: f = (float)(R.inc[cell] / 0.2618); break;
+    case 10: f = smax_c; break;
+    case 11: f = dxm / SH; break;  // lattice coordinates (u, v) of the maximum
+    case 12: f = dym / SH; break;
+    default: f = 0.f; break;
   }
+  if (ft_bf) ft_bf[cell * NFEAT + lane] = f2bf_s(f);
+  if (ft_f) ft_f[cell * NFEAT + lane] = f;
 }
 
 // The plain stack restricted to the orbits of selected cells: orbit
@@ -555,13 +592,8 @@ hipError_t launch_cell_stamps(const StackArgs& reps, double da, double dm, uint1
                               uint16_t* ft_bf, float* ft_f, hipStream_t s) {
   if (reps.n <= 0) return hipSuccess;
   if (reps.n_exp > STAMP_MAX_EXP) return hipErrorInvalidValue;
-  const size_t lds = sizeof(double2) * 3 * (size_t)reps.n_exp;
-  if (reps.n_exp > 256)
-    hipLaunchKernelGGL(k_cell_stamps<4>, dim3((unsigned)reps.n), dim3(64), lds, s, reps, da, dm, st_bf, st_f, ft_bf,
-                       ft_f);
-  else
-    hipLaunchKernelGGL(k_cell_stamps<2>, dim3((unsigned)reps.n), dim3(64), lds, s, reps, da, dm, st_bf, st_f, ft_bf,
-                       ft_f);
+  const size_t lds = std::max((sizeof(double2) * 3 + sizeof(uint16_t)) * (size_t)reps.n_exp, sizeof(float2) * SP);
+  hipLaunchKernelGGL(k_cell_stamps, dim3((unsigned)reps.n), dim3(64), lds, s, reps, da, dm, st_bf, st_f, ft_bf, ft_f);
   return hipGetLastError();
 }
 
