@@ -28,10 +28,13 @@
 // so the result is exact on either route.
 //
 // Two image reads bound it.  200 FP32 2048^2 images (3.36 GB): bins 0.71 ms
-// (4.7 TB/s, the copy rate), collect 0.66 ms, sample + plan + solve 0.43 ms
-// (one workgroup per image, latency); 1.72 ms together, 32.2 ms before, when
+// (4.7 TB/s, the copy rate), collect 0.66 ms, sample + plan + solve 0.23 ms
+// (one workgroup per image, latency); 1.55 ms together, 32.2 ms before, when
 // every 11-bit digit of every median and deviation of every step read the
-// images again (26 reads).  48 FP32 2048 x 1536 images: 0.53 ms, 6.9 before.
+// images again (26 reads).  48 FP32 2048 x 1536 images: 0.43 ms, 6.9 before.
+// (In sample and solve the middle deviation is found by wavefronts over the
+// values sorted by their deviation on either side; with every value trying
+// itself and one atomic minimum they took 0.39 ms instead of 0.19.)
 #include <algorithm>
 #include <type_traits>
 
@@ -153,6 +156,23 @@ __device__ __forceinline__ uint32_t block_scan(uint32_t v, uint32_t* tmp, uint32
   return base + inc - v;
 }
 
+// Smallest j of [0, n) with f(j), n if there is none, for an f that stays true
+// from there on: 64 places per round, by a whole wavefront.
+template <typename F>
+__device__ __forceinline__ int wave_first(int n, F&& f) {
+  const int lane = threadIdx.x & 63;
+  int lo = 0, hi = n;
+  while (lo < hi) {
+    const int w = (hi - lo + 63) >> 6;
+    const uint64_t m = __ballot(f(min(lo + (lane + 1) * w, hi) - 1));
+    if (!m) return hi;
+    const int k = __builtin_ctzll(m);
+    hi = min(lo + (k + 1) * w, hi) - 1;
+    lo += k * w;
+  }
+  return hi;
+}
+
 // Ascending bitonic sort of the NZ_TX * PER keys in s (LDS).  Thread t holds
 // keys PER t .. PER t + PER - 1: a compare-exchange at distance j is in
 // registers for j < PER, between lanes for j < 64 PER, and through LDS, with
@@ -216,7 +236,7 @@ __global__ __launch_bounds__(NZ_TX) void k_noise_sample(const void* const* imgs,
   NoiseImage& S = st[img];
   __shared__ uint32_t s[NZ_SAMPLE];
   __shared__ uint32_t tmp[NZ_WAVES];
-  __shared__ unsigned int best[2];
+  __shared__ float sh_d;
   for (int b = tid; b < NZ_BINS; b += NZ_TX) S.hist[b] = 0u;
   if (tid < NZ_DHAT) S.dhat[tid] = 0.f;
   if (tid == 0) {
@@ -225,7 +245,6 @@ __global__ __launch_bounds__(NZ_TX) void k_noise_sample(const void* const* imgs,
     S.n_tab = 0;
     S.whole = n <= NZ_WHOLE;
     S.n_sample = 0;
-    best[0] = best[1] = 0xffffffffu;
   }
   if (n <= NZ_WHOLE) {  // every value is listed: one bin
     if (tid == 0) S.map = NoiseMap{0.f, 1.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
@@ -263,16 +282,18 @@ __global__ __launch_bounds__(NZ_TX) void k_noise_sample(const void* const* imgs,
       }
       return a;
     };
-    // the smallest deviation of a member that covers half of them (every
-    // thread tries its members; the words of `best` take turns)
-    for (int i = lo + tid; i < hi; i += NZ_TX) {
-      const float dd = fabsf(fkey_value(s[i]) - m);
-      if (2 * (pos(m + dd, true) - pos(m - dd, false)) >= c) atomicMin(&best[it & 1], __float_as_uint(dd));
+    // the deviation that covers half of the members: the k-th smallest of the
+    // sorted deviations right and left of the median, i of them from the right
+    if (tid < 64) {
+      const int p = lo + wave_first(c, [&](int j) { return fkey_value(s[lo + j]) >= m; });
+      const int k = (c + 1) / 2, nr = hi - p, nl = p - lo;
+      auto right = [&](int j) { return j < nr ? fkey_value(s[p + j]) - m : __builtin_inff(); };
+      auto left = [&](int j) { return j < nl ? m - fkey_value(s[p - 1 - j]) : __builtin_inff(); };
+      const int i = wave_first(k + 1, [&](int j) { return j == k || right(j) >= left(k - 1 - j); });
+      if (tid == 0) sh_d = fmaxf(i > 0 ? right(i - 1) : 0.f, i < k ? left(k - 1 - i) : 0.f);
     }
     __syncthreads();
-    const uint32_t db = best[it & 1];
-    if (tid == 0) best[(it + 1) & 1] = 0xffffffffu;
-    const float d = db == 0xffffffffu ? 0.f : __uint_as_float(db);
+    const float d = sh_d;
     sig = 1.4826f * d;
     if (it == 0) {
       m0 = m_lo = m_hi = m;
@@ -290,7 +311,7 @@ __global__ __launch_bounds__(NZ_TX) void k_noise_sample(const void* const* imgs,
     if (nl == lo && nh == hi) break;
     lo = nl;
     hi = nh;
-    __syncthreads();  // the next step's word is reset
+    __syncthreads();  // sh_d is read
   }
   for (int i = tid; i < NZ_SAMPLE; i += NZ_TX) S.sample[i] = s[i];
   if (tid == 0) {
@@ -653,36 +674,36 @@ __global__ __launch_bounds__(NZ_TX) void k_noise_solve(const void* const* imgs, 
       default: sort_per<32>(A); break;
     }
     if (tid == 0) q_bad = 0;
-    if (tid < nt) {
-      const int b = (int)S.bin[tid];
-      // key of the first value with bin >= v (+inf's when there is none)
-      auto edge = [&](int v) {
+    {
+      // a bin's lower edge by one half of the workgroup, its upper edge by the other
+      static_assert(2 * NZ_TAB == NZ_TX, "two threads per marked bin");
+      const int e = tid & (NZ_TAB - 1);
+      const bool upper = tid >= NZ_TAB;
+      if (e < nt) {
+        const int b = (int)S.bin[e] + upper;
+        // key of the first value with bin >= b (+inf's when there is none)
         uint32_t lo = fkey(-3.4028234664e38f), hi = fkey(3.4028234664e38f) + 1u;
+        if (S.whole) lo = hi = upper ? hi : lo;
         while (lo < hi) {
           const uint32_t k = lo + (hi - lo) / 2;
-          if (map_bin(M, fkey_value(k)) >= v) hi = k;
+          if (map_bin(M, fkey_value(k)) >= b) hi = k;
           else lo = k + 1;
         }
-        return lo;
-      };
-      auto first = [&](uint32_t key) {  // listed keys below `key`
-        int lo = 0, hi = n_list;
-        while (lo < hi) {
-          const int k = (lo + hi) >> 1;
-          if (A[k] < key) lo = k + 1;
-          else hi = k;
+        int l = 0, r = n_list;  // listed keys below it
+        while (l < r) {
+          const int k = (l + r) >> 1;
+          if (A[k] < lo) l = k + 1;
+          else r = k;
         }
-        return lo;
-      };
-      const uint32_t k0 = S.whole ? fkey(-3.4028234664e38f) : edge(b);
-      const uint32_t k1 = S.whole ? fkey(3.4028234664e38f) + 1u : edge(b + 1);
-      elo[tid] = fkey_value(k0);
-      ehi[tid] = fkey_value(k1);
+        (upper ? ehi : elo)[e] = fkey_value(lo);
+        (upper ? n_heavy : off)[e] = (uint32_t)l;
+      }
+    }
+    __syncthreads();
+    if (tid < nt) {
       below[tid] = S.below[tid];
       cnt[tid] = S.cnt[tid];
-      const int a0 = first(k0), listed = first(k1) - a0;
-      off[tid] = (uint32_t)a0;
-      const uint32_t rest = S.cnt[tid] - (uint32_t)listed;
+      const uint32_t rest = S.cnt[tid] - (n_heavy[tid] - off[tid]);
       n_heavy[tid] = rest;
       heavy[tid] = fkey_value(S.heavy[tid]);
       known[tid] = rest == 0 || S.heavy[tid] != 0u;
@@ -767,17 +788,33 @@ __global__ __launch_bounds__(NZ_TX) void k_noise_solve(const void* const* imgs, 
       const float dh = R.iter < NZ_DHAT ? S.dhat[R.iter] : 0.f;
       const double slack = 0.03 * (double)dh + 2.0 / (double)M.a0;  // the plan's value is good to a bin or two
       const double near0 = dh > 0.f ? dh - slack : 0.0, near1 = dh > 0.f ? dh + slack : __builtin_inf();
-      for (int i = tid; i < n_list + nt; i += NZ_TX) {
-        const bool hv = i >= n_list;
-        if (hv && !n_heavy[i - n_list]) continue;
-        const double x = (double)(hv ? heavy[i - n_list] : fkey_value(A[i]));
-        const double D = fabs(x - m);
-        if (!(D >= near0 && D <= near1)) continue;
+      // pixels of the set within D of m (never less for a larger D)
+      auto within = [&](double D) -> uint32_t {
         bool e = true;
         const uint32_t hi = std::min(rank_at(m, D, true, e), U), lo = std::max(rank_at(m, D, false, e), L);
-        const uint32_t c = hi > lo ? hi - lo : 0u;
-        for (int t = 0; t < 2; ++t)
-          if (c > k[t]) atomicMin(&dmin[t], (unsigned long long)__double_as_longlong(D));
+        return hi > lo ? hi - lo : 0u;
+      };
+      if (tid < 256) {
+        // listed values, sorted by their deviation on either side of m: a wavefront for each side and middle
+        const int t = tid >> 7;
+        const bool right = (tid >> 6) & 1;
+        const int p = wave_first(n_list, [&](int i) { return (double)fkey_value(A[i]) >= m; });
+        auto dev_at = [&](int j) { return fabs((double)fkey_value(A[right ? p + j : p - 1 - j]) - m); };
+        const int n_side = right ? n_list - p : p;
+        const int j0 = wave_first(n_side, [&](int j) { return dev_at(j) >= near0; });
+        const int n_near = wave_first(n_side - j0, [&](int j) { return dev_at(j0 + j) > near1; });
+        const int j = wave_first(n_near, [&](int i) { return within(dev_at(j0 + i)) > k[t]; });
+        if (j < n_near && (tid & 63) == 0)
+          atomicMin(&dmin[t], (unsigned long long)__double_as_longlong(dev_at(j0 + j)));
+      } else {
+        for (int i = tid - 256; i < nt; i += NZ_TX - 256) {
+          if (!n_heavy[i]) continue;
+          const double D = fabs((double)heavy[i] - m);
+          if (!(D >= near0 && D <= near1)) continue;
+          const uint32_t c = within(D);
+          for (int t = 0; t < 2; ++t)
+            if (c > k[t]) atomicMin(&dmin[t], (unsigned long long)__double_as_longlong(D));
+        }
       }
       __syncthreads();
       const double dev[2] = {__longlong_as_double((long long)dmin[0]), __longlong_as_double((long long)dmin[1])};
