@@ -25,17 +25,18 @@ import numpy as np
 ROOT = os.path.dirname(os.path.abspath(__file__))
 sys.path.insert(0, ROOT)
 
-# FP64 operations of the stack kernel's path as written (an FMA counts 2;
-# add / mul / hardware reciprocal or rsqrt estimate 1).  Every dense sample:
-# the prediction p = r + D (v + D h) - obs 15 and the sky-cone test of it 22
-# (axis projection 5, squared distance 5, bound 6, widened radius 2, test 4).
+# Operations of the stack kernel's path as written, in FP64 operations (an FMA
+# counts 2; add / mul / hardware reciprocal or rsqrt estimate 1; an FP32
+# operation counts half, as the vector peaks do).  Every dense sample, in FP32:
+# the prediction p = r + D (v + D h) - obs 15 and its test against the image
+# rectangle 26 (three projections 15, bound 5, widened half sizes 4, test 2).
 # Every exact solve (each orbit at each checkpoint, and each sample that lands
 # in an image; samples that are solved but miss are not counted): mean anomaly
 # 5, warm Kepler step 39 (2nd-order start 7, short rotation 20, Newton step
 # with a tiny rotation 12), position and distance 25, velocity and light-time
 # correction 23, corrected position 6, light time 1, projection with one-
 # refinement reciprocal 24, rounding 2.
-FLOPS_PER_SAMPLE = 37
+FLOPS_PER_SAMPLE = 20.5
 FLOPS_PER_SOLVE = 125
 # A wavefront whose samples land often leaves the prediction for the
 # per-sample walk: per sample 82 (mean anomaly with the predicted light time
@@ -378,12 +379,12 @@ def counted_work(ctx, launch):
 def roofline_block(kernel, ms, n_orbits, n_exp, valid, flops, stored, traffic):
     """Both rooflines of the dominant launch.  HBM: algorithmic bytes = 8 B per
     valid sample (the psi, phi gather) + 12 B of outputs per orbit + 48 B of
-    elements per stored orbit + 224 B per exposure record.  FP64: the
+    elements per stored orbit + 272 B per exposure record.  FP64: the
     kernel's own flop count (its work counters).  The binding one is HBM when
     the measured traffic (committed counters, same sources) keeps HBM busier
     than the FP64 units are, else the one whose algorithmic fraction is
     nearer its peak."""
-    nbytes = 8.0 * valid + (12.0 + (48.0 if stored else 0.0)) * n_orbits + 224.0 * n_exp
+    nbytes = 8.0 * valid + (12.0 + (48.0 if stored else 0.0)) * n_orbits + 272.0 * n_exp
     hbm = dict(bound="hbm", achieved=nbytes / (ms * 1e-3) / 1e9, peak=HBM_PEAK_GBS, unit="GB/s",
                algorithmic_bytes=nbytes, traffic=traffic)
     hbm["frac"] = hbm["achieved"] / HBM_PEAK_GBS

@@ -25,9 +25,15 @@ constexpr double CK_SPAN = 12.0;
 // Everything is expressed in the heliocentric ecliptic frame so no rotation
 // is needed per sample: the TAN basis is rotated once per exposure instead.
 struct alignas(16) ExpMeta {
-  // The fields every step of the checkpoint walk reads come first (72 bytes,
-  // two scalar loads issued together).
+  // The fields every step of the checkpoint walk reads come first (64 bytes,
+  // one scalar load).  A position q (AU from the observer) projects into the
+  // pixel rectangle only if c.q > 0, |A0'.q| <= (W / 2) c.q and likewise for y,
+  // with A0' = a0 + (px0 - (W - 1) / 2) c; kx X = A0' and so on are those scaled
+  // so that a displacement of q by d changes |X.q| - kx c.q by at most d.
   double t;                 // epoch (days)
+  float fX[3], fY[3], fZ[3];  // scaled A0', A1'; c
+  float kx, ky;             // scaled half sizes (widened by 0.01 px)
+  float fo[3];              // observer (AU, ecliptic)
   double ox, oy, oz;        // observer (AU, ecliptic)
   // Sky cone holding every direction that projects into the pixel rectangle
   // widened by one pixel: unit axis u, tangent of the half-angle, and the
@@ -48,7 +54,7 @@ struct alignas(16) ExpMeta {
 };
 // A patch holds n + 1 records: the last exposure's record is repeated once
 // (the checkpoint walk's final queue-serving step reads it, uses nothing of it).
-static_assert(sizeof(ExpMeta) == 224, "ExpMeta layout");
+static_assert(sizeof(ExpMeta) == 272, "ExpMeta layout");
 
 // Exposure records, planes and elements seen through a named address space.
 // A pointer read from device memory (a batched launch's per-patch

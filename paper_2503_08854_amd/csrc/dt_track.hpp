@@ -16,8 +16,14 @@
 // = sqrt(v^2 + 3 (r.v)^2 / r^2) / r^3 <= 2 |v| / r^3, r >= q the perihelion
 // distance, |v| <= vmax the perihelion speed), and the change of light time
 // obeys |tau' - tau| <= (vmax + vobs) D_t / (c - vmax) with vobs the patch's
-// observer speed bound.  The sky-cone test of the exposure, widened by
-// (1 + tan theta) m, then either proves the sample cannot land or queues it.
+// observer speed bound.  The test of p against the exposure's image rectangle
+// (ExpMeta: two linear inequalities), widened by m, then either proves the
+// sample cannot land or queues it.  Prediction and test run in FP32, m widened
+// by what their roundings can add, so that they drop no more than the exact
+// walk does; everything that reaches a result is FP64 as before.  10^7 orbits x
+// 200 survey exposures: 4.37 -> 3.81 ms from an FP64 prediction and a test
+// against the cone around the image (half as many vector cycles per sample, and
+// the rectangle queues two thirds of what the cone does).
 // Queued samples are solved exactly, as the per-sample walk solves them
 // (Kepler from the checkpoint state, light time to LT_LINEAR_MAX, projection,
 // nearest pixel), by whichever lanes are free, 64 at a time, and each orbit
@@ -69,8 +75,8 @@ struct TrackQueue {
 };
 typedef __attribute__((address_space(3))) TrackQueue LdsTrackQueue;
 
-// Coefficients of m (times D^3 and D), scaled by 1.1 >= 1 + tan(theta) (cones
-// wider than tan(theta) = 0.1 are not used).
+// Coefficients of m (times D^3 and D), scaled by 1.1 (the test itself widens by
+// exactly m).
 struct TrackBound {
   double j6, l1, vmax;
 };
@@ -94,8 +100,8 @@ __device__ __forceinline__ void track_bound(double a, double e, const Orbit& o, 
 // samples, 64 at a time, when a checkpoint is due, the queue is half full or
 // a lane's list is full, or after the last exposure; then the checkpoint
 // solve of every lane when due.  Both are one loop over jobs so the exact
-// solve exists once in the code.  Then the cone test of the prediction
-// queues the samples that may land.  After a cone test a wavefront of a
+// solve exists once in the code.  Then the rectangle test of the prediction
+// queues the samples that may land.  After a test a wavefront of a
 // launch that allows it may give its orbits up (*deferred = true; P is then
 // meaningless), see the file comment.
 //
@@ -132,12 +138,14 @@ __device__ __forceinline__ void track_walk(const StackArgs& A, const Orbit& o, c
   // stays 1e300 and the stored coefficients are 0, so no step of zero
   // multiplies an infinity.
   const bool bounded = bd.j6 < 1e30 && bd.l1 < 1e30 && bd.vmax < 1e30;
-  Q.bnd[0][lane] = bounded ? __double2float_ru(bd.j6) : 0.f;
-  Q.bnd[1][lane] = bounded ? __double2float_ru(bd.l1) : 0.f;
+  // (1e-6 more than covers the rounding of their use)
+  Q.bnd[0][lane] = bounded ? __double2float_ru(bd.j6 * 1.000001) : 0.f;
+  Q.bnd[1][lane] = bounded ? __double2float_ru(bd.l1 * 1.000001) : 0.f;
   Q.bnd[2][lane] = !live ? -__builtin_inff() : bounded ? __double2float_ru(bd.vmax) : -1.f;  // read at checkpoints
-  double j6 = 0.0, l1 = 0.0;  // reloaded after every service step
-  double r0 = 0.0, r1 = 0.0, r2 = 0.0, v0 = 0.0, v1 = 0.0, v2 = 0.0, h0 = 0.0, h1 = 0.0, h2 = 0.0;
+  float j6 = 0.f, l1 = 0.f;  // reloaded after every service step
+  float r0 = 0.f, r1 = 0.f, r2 = 0.f, v0 = 0.f, v1 = 0.f, v2 = 0.f, h0 = 0.f, h1 = 0.f, h2 = 0.f;
   float s0 = 0.f;    // slack (AU, rounded up); +inf: not pruned at this checkpoint; -inf: lane not live
+  float s1 = 0.f;    // s0 and the rounding of the FP32 prediction and test
   double tc = 0.0;   // checkpoint epoch
   int ck_at = 0;     // exposure of the next checkpoint (the last one's ck_next: the first more than CK_SPAN on)
   int n_ck = 0;      // checkpoints so far
@@ -154,13 +162,12 @@ __device__ __forceinline__ void track_walk(const StackArgs& A, const Orbit& o, c
     // the step after the last exposure only serves the queue; the record
     // after the last one repeats it, so it is read like any other
     GExpMeta& x = meta[ex];
-    // the cone of this exposure read now, with the epoch and observer, so
-    // both loads are in flight together
-    double ux = x.ux, uy = x.uy, uz = x.uz, ctan = x.cone_tan, clim = x.cone_lim;
-    double D = x.t - tc;
-    double p0 = fma(fma(h0, D, v0), D, r0) - x.ox;
-    double p1 = fma(fma(h1, D, v1), D, r1) - x.oy;
-    double p2 = fma(fma(h2, D, v2), D, r2) - x.oz;
+    float X0 = x.fX[0], X1 = x.fX[1], X2 = x.fX[2], Y0 = x.fY[0], Y1 = x.fY[1], Y2 = x.fY[2];
+    float Z0 = x.fZ[0], Z1 = x.fZ[1], Z2 = x.fZ[2], kx = x.kx, ky = x.ky;
+    float D = (float)(x.t - tc);
+    float p0 = fmaf(fmaf(h0, D, v0), D, r0) - x.fo[0];
+    float p1 = fmaf(fmaf(h1, D, v1), D, r1) - x.fo[1];
+    float p2 = fmaf(fmaf(h2, D, v2), D, r2) - x.fo[2];
     // one integer compare decides whether this step serves (svc_at <= n_exp,
     // so the final step always does)
     if (ex >= svc_at) {
@@ -178,8 +185,7 @@ __device__ __forceinline__ void track_walk(const StackArgs& A, const Orbit& o, c
       const int nb = fl ? (count + 63) >> 6 : 0;
       float tg_ck = 0.f;  // a Newton start only
       if (ck && ex > 0) {
-        const double d2 = fma(p0, p0, fma(p1, p1, p2 * p2));
-        tg_ck = (float)(d2 * __builtin_amdgcn_rsq(d2) * IC);
+        tg_ck = __builtin_amdgcn_sqrtf(fmaf(p0, p0, fmaf(p1, p1, p2 * p2))) * (float)IC;
       }
 #pragma unroll 1
       for (int jb = 0; jb < nb + (ck ? 1 : 0); ++jb) {
@@ -240,7 +246,7 @@ __device__ __forceinline__ void track_walk(const StackArgs& A, const Orbit& o, c
             // three roundings is below 1e-7 relative, and the factor
             // 1.1 * (1 + 1e-6) keeps s0 above 1.1 (PRED_SLACK + vmax dtau)
             const float dtau = fmaf(1.01f, fabsf((float)s.D), 1e-9f);
-            // a lane that is not live gets -inf: its cone test never passes
+            // a lane that is not live gets -inf: its test never passes
             const float vmax = Q.bnd[2][lane];
             s0 = vmax >= 0.f && dtau < 1.f ? 1.1000011f * fmaf(vmax, dtau, PRED_SLACK)
                                            : vmax < -1.f ? -__builtin_inff() : __builtin_inff();
@@ -286,20 +292,21 @@ __device__ __forceinline__ void track_walk(const StackArgs& A, const Orbit& o, c
         const double sE = Q.kep[1][lane], cE = Q.kep[2][lane], g = Q.kep[3][lane];
         const double cme = cE - e, ng = n * g;
         const double vs = -ng * sE, vc = ng * cE;
-        v0 = fma(vc, bQ0, vs * aP0);
-        v1 = fma(vc, bQ1, vs * aP1);
-        v2 = fma(vc, bQ2, vs * aP2);
-        r0 = fma(cme, aP0, sE * bQ0);
-        r1 = fma(cme, aP1, sE * bQ1);
-        r2 = fma(cme, aP2, sE * bQ2);
+        v0 = (float)fma(vc, bQ0, vs * aP0);
+        v1 = (float)fma(vc, bQ1, vs * aP1);
+        v2 = (float)fma(vc, bQ2, vs * aP2);
+        const double q0 = fma(cme, aP0, sE * bQ0), q1 = fma(cme, aP1, sE * bQ1), q2 = fma(cme, aP2, sE * bQ2);
+        r0 = (float)q0;
+        r1 = (float)q1;
+        r2 = (float)q2;
         double rr, irr;
-        sqrt_rsq(fma(r0, r0, fma(r1, r1, r2 * r2)), rr, irr);
-        const double hk = -0.5 * MU_SUN * irr * irr * irr;
+        sqrt_rsq(fma(q0, q0, fma(q1, q1, q2 * q2)), rr, irr);
+        const float hk = (float)(-0.5 * MU_SUN * irr * irr * irr);
         h0 = hk * r0;
         h1 = hk * r1;
         h2 = hk * r2;
-        j6 = (double)Q.bnd[0][lane];
-        l1 = (double)Q.bnd[1][lane];
+        j6 = Q.bnd[0][lane];
+        l1 = Q.bnd[1][lane];
       }
       // this exposure's record again, by an index the compiler does not
       // match with the first one (ex >> 30 is 0), so the first values need
@@ -310,36 +317,57 @@ __device__ __forceinline__ void track_walk(const StackArgs& A, const Orbit& o, c
         if (TCV) asm volatile("" : "+v"(tc));
         ck_at = y.ck_next;
         n_ck++;
-        D = 0.0;
+        D = 0.f;
       }
-      p0 = fma(fma(h0, D, v0), D, r0) - y.ox;
-      p1 = fma(fma(h1, D, v1), D, r1) - y.oy;
-      p2 = fma(fma(h2, D, v2), D, r2) - y.oz;
-      ux = y.ux;  // the cone again too: nothing of the first read stays live across the solves
-      uy = y.uy;
-      uz = y.uz;
-      ctan = y.cone_tan;
-      clim = y.cone_lim;
+      // what FP32 adds, as a displacement of the exact position: each of the
+      // ~24 roundings on the way to |X.p| - kx Z.p is at most 2^-24 of the sum
+      // of the sizes that enter, up to CK_SPAN days on; 64 of them.  A state
+      // too large for FP32 is zeroed and never pruned.
+      {
+        constexpr float T = (float)CK_SPAN;
+        const float size = fabsf(r0) + fabsf(r1) + fabsf(r2) + T * (fabsf(v0) + fabsf(v1) + fabsf(v2)) +
+                           T * T * (fabsf(h0) + fabsf(h1) + fabsf(h2)) + fabsf(y.fo[0]) + fabsf(y.fo[1]) +
+                           fabsf(y.fo[2]) + T * (float)A.vobs;
+        s1 = fmaf(size, 0x1p-18f, s0);
+        if (!(size < 1e15f)) {
+          r0 = r1 = r2 = v0 = v1 = v2 = h0 = h1 = h2 = 0.f;
+          s1 = s0 < 0.f ? s0 : __builtin_inff();
+        }
+      }
+      p0 = fmaf(fmaf(h0, D, v0), D, r0) - y.fo[0];
+      p1 = fmaf(fmaf(h1, D, v1), D, r1) - y.fo[1];
+      p2 = fmaf(fmaf(h2, D, v2), D, r2) - y.fo[2];
+      // the test again too: nothing of the first read stays live across the solves
+      X0 = y.fX[0];
+      X1 = y.fX[1];
+      X2 = y.fX[2];
+      Y0 = y.fY[0];
+      Y1 = y.fY[1];
+      Y2 = y.fY[2];
+      Z0 = y.fZ[0];
+      Z1 = y.fZ[1];
+      Z2 = y.fZ[2];
+      kx = y.kx;
+      ky = y.ky;
       svc_at = ck_at < A.n_exp ? ck_at : A.n_exp;
       if (last) break;
     }
     n_tested++;
-    // cone test of the prediction (bitwise logic, no branches)
-    const double sc = fma(ux, p0, fma(uy, p1, uz * p2));
-    const double d2 = fma(p0, p0, fma(p1, p1, p2 * p2));
-    const double m = fma(fma(j6, D * D, l1), D, (double)s0);
-    const double R = fma(ctan, sc, m);
-    const bool in_front = R >= 0.0, in_cone = fma(-R, R, fma(-sc, sc, d2)) <= clim;
-    const bool may = in_front & in_cone;
+    // the prediction against the rectangle widened by m (bitwise logic, no branches)
+    const float m = fmaf(fmaf(j6, D * D, l1), D, s1);
+    const float Z = fmaf(Z0, p0, fmaf(Z1, p1, Z2 * p2));
+    const bool in_x = fabsf(fmaf(X0, p0, fmaf(X1, p1, X2 * p2))) <= fmaf(kx, Z, m);
+    const bool in_y = fabsf(fmaf(Y0, p0, fmaf(Y1, p1, Y2 * p2))) <= fmaf(ky, Z, m);
+    const bool may = in_x & in_y;
     // the mask from one ballot per compare (each is the compare's own lane
     // mask; a ballot of the combined flag would rebuild it from a vector)
-    const uint64_t mask = __builtin_amdgcn_ballot_w64(in_front) & __builtin_amdgcn_ballot_w64(in_cone);
+    const uint64_t mask = __builtin_amdgcn_ballot_w64(in_x) & __builtin_amdgcn_ballot_w64(in_y);
     if (mask) {
       if (may) {
         const int slot = count + (int)__builtin_amdgcn_mbcnt_hi((uint32_t)(mask >> 32),
                                                                 __builtin_amdgcn_mbcnt_lo((uint32_t)mask, 0u));
         Q.ent[slot] = (ex << 6) | lane;
-        Q.tg[slot] = (float)(d2 * __builtin_amdgcn_rsq(d2) * IC);
+        Q.tg[slot] = __builtin_amdgcn_sqrtf(fmaf(p0, p0, fmaf(p1, p1, p2 * p2))) * (float)IC;
         Q.list[len][lane] = (unsigned char)slot;
         len++;
       }

@@ -123,6 +123,27 @@ __global__ void k_exposure_prep(const dt_exposure* __restrict__ in, const int64_
   m.uz = cone ? u[2] : 0.0;
   m.cone_tan = cone ? tmax * 1.0001 + 1e-12 : 0.0;
   m.cone_lim = cone ? 0.0 : __builtin_inf();
+  // the scaled rectangle test (see ExpMeta)
+  {
+    const double hx = 0.5 * x.width + 0.01, hy = 0.5 * x.height + 0.01;
+    const double dx = m.px0 - 0.5 * (x.width - 1), dy = m.py0 - 0.5 * (x.height - 1);
+    const double X[3] = {m.a0x + dx * cE[0], m.a0y + dx * cE[1], m.a0z + dx * cE[2]};
+    const double Y[3] = {m.a1x + dy * cE[0], m.a1y + dy * cE[1], m.a1z + dy * cE[2]};
+    const double cn = sqrt(cE[0] * cE[0] + cE[1] * cE[1] + cE[2] * cE[2]);
+    const double sx = 1.0 / (sqrt(X[0] * X[0] + X[1] * X[1] + X[2] * X[2]) + hx * cn);
+    const double sy = 1.0 / (sqrt(Y[0] * Y[0] + Y[1] * Y[1] + Y[2] * Y[2]) + hy * cn);
+    // (numbers beyond FP32's range: zeros, which no position fails)
+    const double o1 = fabs(x.obs_xyz_au[0]) + fabs(x.obs_xyz_au[1]) + fabs(x.obs_xyz_au[2]);
+    const bool fits = o1 < 1e15 && sx > 0.0 && sy > 0.0 && sx < 1e300 && sy < 1e300;
+    for (int k = 0; k < 3; ++k) {
+      m.fX[k] = fits ? (float)(sx * X[k]) : 0.f;
+      m.fY[k] = fits ? (float)(sy * Y[k]) : 0.f;
+      m.fZ[k] = fits ? (float)cE[k] : 0.f;
+      m.fo[k] = fits ? (float)x.obs_xyz_au[k] : 0.f;
+    }
+    m.kx = fits ? (float)(sx * hx) : 0.f;
+    m.ky = fits ? (float)(sy * hy) : 0.f;
+  }
   out[i] = m;
   if (i == n - 1) out[n] = m;  // the repeated last record
 }
