@@ -23,7 +23,7 @@
 //            histogram) + position in the sorted list.  Each rank it uses is
 //            checked to fall in a marked bin (or a gap without pixels); if
 //            one does not, the image is solved by radix selection over its
-//            pixels in the same workgroup.
+//            pixels (pixels, a kernel that ends at once if there is none).
 // All comparisons that decide the result are the FP64 ones of the definition,
 // so the result is exact on either route.
 //
@@ -53,6 +53,7 @@ constexpr int64_t NZ_WHOLE = 16384;   // images up to this size are listed whole
 constexpr int NZ_LIST = 32768;        // listed values per image
 constexpr int NZ_TAB = 512;           // marked bins per image
 constexpr int NZ_STAGE = 2048;        // values a collecting workgroup stages in LDS
+constexpr int NZ_PIECES = 256;        // most pieces of an image solved from its pixels
 constexpr int NZ_DHAT = 16;           // steps whose planned deviation median is kept
 
 // Monotone map of a value to a bin: the sum of clamped, scaled differences
@@ -73,6 +74,11 @@ struct NoiseImage {
   int32_t n_tab;    // marked bins; -1: too many, solve from the pixels
   int32_t whole;    // one bin, every value listed
   int32_t n_sample; // finite values of the sample
+  int32_t todo;     // the plan missed: solve from the pixels
+  uint32_t role, done;       // workgroups that came to it, pieces done
+  uint32_t call;             // number of the pass; 0: none yet, ~0: done
+  uint32_t taken[NZ_PIECES]; // pass in which a piece was taken last
+  uint64_t task[7];          // the pass
   float dhat[NZ_DHAT];  // the plan's deviation medians, by step (0: none)
   uint32_t bin[NZ_TAB], below[NZ_TAB], cnt[NZ_TAB];  // marked bins: index, pixels below, pixels in
   uint32_t heavy[NZ_TAB];                            // key of the value that is not listed (0: none)
@@ -239,12 +245,15 @@ __global__ __launch_bounds__(NZ_TX) void k_noise_sample(const void* const* imgs,
   __shared__ float sh_d;
   for (int b = tid; b < NZ_BINS; b += NZ_TX) S.hist[b] = 0u;
   if (tid < NZ_DHAT) S.dhat[tid] = 0.f;
+  if (tid < NZ_PIECES) S.taken[tid] = 0u;
   if (tid == 0) {
     S.n = 0;
     S.n_list = 0;
     S.n_tab = 0;
     S.whole = n <= NZ_WHOLE;
     S.n_sample = 0;
+    S.role = 0;
+    S.call = 0;
   }
   if (n <= NZ_WHOLE) {  // every value is listed: one bin
     if (tid == 0) S.map = NoiseMap{0.f, 1.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
@@ -557,92 +566,23 @@ struct NoiseResult {
   int iter;
 };
 
-// The iteration by radix selection over the pixels (11-bit digits of the
-// float key, then of the bits of |x - m|), one workgroup; for images whose
-// places the plan missed.  h: 2 x 2048 words of LDS.
-template <typename T>
-__device__ __noinline__ NoiseResult noise_from_pixels(const void* img, int64_t n_pix, double kappa, int max_iter,
-                                                      uint32_t* h, uint32_t* tmp, uint64_t* sh) {
-  constexpr int B = 2048;
-  const int tid = threadIdx.x;
-  double m = 0.0, thr = __builtin_inf();
-  auto count = [&](double mm, double tt) {
-    uint32_t c = 0, total;
-    for_pixels<T, 8>(img, n_pix, 0, 1, [&](float x) {
-      c += __builtin_isfinite(x) && fabs((double)x - mm) <= tt ? 1u : 0u;
-    });
-    (void)block_scan(c, tmp, &total);
-    return (int64_t)total;
-  };
-  // the two middle keys of the set (m, thr): of x, or of |x - mn|
-  auto middle = [&](int64_t n, bool dev, double mn, double out[2]) {
-    const int lo_x[3] = {21, 10, 0}, lo_d[6] = {52, 41, 30, 19, 8, 0};
-    uint64_t pre[2] = {0, 0};
-    int64_t rank[2] = {(n - 1) / 2, n / 2};
-    int hi = dev ? 63 : 32;
-    for (int q = 0; q < (dev ? 6 : 3); ++q) {
-      const int lo = dev ? lo_d[q] : lo_x[q];
-      const uint32_t mask = (1u << (hi - lo)) - 1u;
-      const bool two = pre[0] != pre[1];
-      for (int b = tid; b < 2 * B; b += NZ_TX) h[b] = 0u;
-      __syncthreads();
-      for_pixels<T, 8>(img, n_pix, 0, 1, [&](float x) {
-        if (!(__builtin_isfinite(x) && fabs((double)x - m) <= thr)) return;
-        const uint64_t key = dev ? (uint64_t)__double_as_longlong(fabs((double)x - mn)) : (uint64_t)fkey(x);
-        const uint32_t d = (uint32_t)(key >> lo) & mask;
-        if (key >> hi == pre[0] >> hi) atomicAdd(&h[d], 1u);
-        if (two && key >> hi == pre[1] >> hi) atomicAdd(&h[B + d], 1u);
-      });
-      __syncthreads();
-      for (int t = 0; t < 2; ++t) {
-        const uint32_t* H = h + (two && t ? B : 0);
-        const uint32_t c0 = H[2 * tid], c1 = H[2 * tid + 1];
-        uint32_t total;
-        const uint32_t e = block_scan(c0 + c1, tmp, &total);
-        const uint32_t r = (uint32_t)rank[t];
-        if (r >= e && r < e + c0 + c1) {
-          const bool second = r >= e + c0;
-          sh[0] = (uint64_t)(2 * tid + (second ? 1 : 0));
-          sh[1] = e + (second ? c0 : 0u);
-        }
-        __syncthreads();
-        pre[t] |= sh[0] << lo;
-        rank[t] -= (int64_t)sh[1];
-        __syncthreads();
-      }
-      hi = lo;
-    }
-    for (int t = 0; t < 2; ++t)
-      out[t] = dev ? __longlong_as_double((long long)pre[t]) : (double)fkey_value((uint32_t)pre[t]);
-  };
-  NoiseResult R{__builtin_nan(""), 0, 0};
-  int64_t n = count(m, thr);
-  while (n > 0) {
-    double v[2];
-    middle(n, false, 0.0, v);
-    const double mn = 0.5 * (v[0] + v[1]);
-    middle(n, true, mn, v);
-    R.sigma = 1.4826 * (0.5 * (v[0] + v[1]));
-    R.used = n;
-    R.iter++;
-    const double tn = kappa * R.sigma;
-    uint32_t c = 0, changed;  // pixels in one of the two sets only
-    for_pixels<T, 8>(img, n_pix, 0, 1, [&](float x) {
-      if (__builtin_isfinite(x)) c += (fabs((double)x - m) <= thr) != (fabs((double)x - mn) <= tn) ? 1u : 0u;
-    });
-    (void)block_scan(c, tmp, &changed);
-    m = mn;
-    thr = tn;
-    if (!changed || R.iter >= max_iter) break;
-    n = count(m, thr);
+__device__ __forceinline__ void noise_result(const NoiseResult& R, int img, int n_img, double* sigma, int64_t* n_used,
+                                             int32_t* iters, ExpMeta* meta) {
+  if (threadIdx.x == 0) {
+    if (sigma) sigma[img] = R.sigma;
+    if (n_used) n_used[img] = R.used;
+    if (iters) iters[img] = R.iter;
   }
-  return R;
+  if (meta) {
+    // meta is in epoch order; meta[i].src names the image
+    for (int i = threadIdx.x; i < n_img; i += NZ_TX)
+      if (meta[i].src == img) meta[i].vs = (float)(R.sigma * R.sigma);
+  }
 }
 
-template <typename T>
-__global__ __launch_bounds__(NZ_TX) void k_noise_solve(const void* const* imgs, const int64_t* npix, NoiseImage* st,
-                                                       double kappa, int max_iter, int n_img, double* sigma,
-                                                       int64_t* n_used, int32_t* iters, ExpMeta* meta) {
+__global__ __launch_bounds__(NZ_TX) void k_noise_solve(NoiseImage* st, double kappa, int max_iter, int n_img,
+                                                       double* sigma, int64_t* n_used, int32_t* iters,
+                                                       ExpMeta* meta) {
   const int img = blockIdx.x, tid = threadIdx.x;
   NoiseImage& S = st[img];
   __shared__ uint32_t A[NZ_LIST];  // the listed keys, sorted
@@ -654,7 +594,6 @@ __global__ __launch_bounds__(NZ_TX) void k_noise_solve(const void* const* imgs, 
   __shared__ unsigned long long dmin[2];
   __shared__ uint32_t q_rank[16];
   __shared__ int q_bad;
-  __shared__ uint64_t sh[2];
   const uint32_t N = S.n;
   const int nt = S.n_tab;
   bool good = nt >= 0 && S.n_list <= (uint32_t)NZ_LIST;
@@ -859,19 +798,264 @@ __global__ __launch_bounds__(NZ_TX) void k_noise_solve(const void* const* imgs, 
     }
   }
   // (every thread computed the same `good` and R)
-  if (!good) {
+  if (tid == 0) S.todo = !good;
+  if (good) noise_result(R, img, n_img, sigma, n_used, iters, meta);
+}
+
+// The iteration by radix selection over the pixels (11-bit digits of the float
+// key, then of the bits of |x - m|), for the images whose places the plan
+// missed.  The first workgroup to arrive at such an image leads it: it
+// publishes one pass over the pixels at a time (`call`: its number), takes
+// pieces like every other workgroup here (`taken`: the last pass a piece was
+// taken in), and reads the sums when all pieces are done.  A workgroup
+// waits only for pieces that a running workgroup took and, as a helper, for
+// the leader, which is running: none that has yet to start is waited for, so
+// any number of them may be resident.  All that workgroups share goes through
+// relaxed device-scope atomics, ordered by waiting for them (settle): a
+// release or acquire of the whole device would write back or drop the L2 each
+// time (100 images at once 844 ms instead of 69, before the rest below).
+// Latency bounds a pass of one image (20 to 50 us: the call, one piece of
+// 16384 pixels a workgroup, the sums' atomics), the LDS atomics of equal digits
+// many.  2048^2 pixels, half of them 10^6 times narrower than the others (five
+// steps of eleven passes): one image 1.5 ms, 16 images 5.6, 100 images 23; two
+// far groups (one step) 0.85, 2.1 and 9.2; 31, 37 and 33 (14, 14 and 15) when
+// one workgroup made an image's passes.  Where every image is solved before,
+// the kernel costs its launch (200 images: within the noise of 1.5 ms).
+enum NoisePass { NZ_DIGIT, NZ_DEV_DIGIT, NZ_COUNT, NZ_CHANGED };
+struct NoiseTask {
+  double m, thr, mn, tn;  // the set |x - m| <= thr; center of the deviations; the next set
+  uint64_t pre[2];        // digits found above bit `hi`
+  int pass, hi, lo;
+};
+
+// Waits for the memory operations this wavefront has issued.
+__device__ __forceinline__ void settle() { asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)" ::: "memory"); }
+__device__ __forceinline__ uint64_t shared_get(const uint64_t* p) {
+  return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+__device__ __forceinline__ void shared_set(uint64_t* p, uint64_t v) {
+  __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+
+__device__ __forceinline__ uint32_t shared_get(const uint32_t* p) {
+  return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+
+// A piece of the current pass for workgroup r of an image: its own one (r)
+// first, then every R-th from there (R: workgroups here), then any that nobody
+// took (256 workgroups that draw from one counter get in each other's way:
+// 1.7 ms a pass; so do 32 that go for the same next piece).  < 0 when there is none left (for
+// the leader, which alone starts a pass) or the image is done (for a helper,
+// which waits for the next pass).  last: the pass whose own piece was tried.
+// sh: 3 words of LDS.
+__device__ __forceinline__ int noise_take(NoiseImage& S, int pieces, int r, uint32_t& last, NoiseTask* t,
+                                          uint32_t* sh) {
+  const int tid = threadIdx.x;
+  for (;;) {
+    __syncthreads();  // t and sh are read
+    if (tid == 0) {
+      sh[0] = shared_get(&S.call);
+      sh[1] = ~0u;
+      sh[2] = min(shared_get(&S.role), (uint32_t)pieces);  // workgroups here
+      settle();
+    }
     __syncthreads();
-    R = noise_from_pixels<T>(imgs[img], npix[img], kappa, max_iter, A, tmp, sh);
+    const uint32_t seq = sh[0];
+    if (seq == ~0u) return -1;
+    int want = r;
+    if (seq == last) {
+      const int R = (int)sh[2];
+      if (tid < pieces && shared_get(&S.taken[tid]) < seq)
+        atomicMin(&sh[1], (uint32_t)((tid % R + R - r % R) % R * NZ_PIECES + tid));
+      __syncthreads();
+      want = sh[1] == ~0u ? -1 : (int)(sh[1] % NZ_PIECES);
+    }
+    last = seq;
+    if (want < 0 || seq == 0) {
+      if (r == 0) return -1;
+      if (tid == 0)
+        while (shared_get(&S.call) == seq) __builtin_amdgcn_s_sleep(32);
+      continue;
+    }
+    if (tid == 0) {
+      t->m = __longlong_as_double((long long)shared_get(&S.task[0]));
+      t->thr = __longlong_as_double((long long)shared_get(&S.task[1]));
+      t->mn = __longlong_as_double((long long)shared_get(&S.task[2]));
+      t->tn = __longlong_as_double((long long)shared_get(&S.task[3]));
+      t->pre[0] = shared_get(&S.task[4]);
+      t->pre[1] = shared_get(&S.task[5]);
+      const uint32_t w = (uint32_t)shared_get(&S.task[6]);
+      t->pass = w & 255;
+      t->hi = w >> 8 & 255;
+      t->lo = w >> 16;
+      settle();
+      // taken: the pass has not ended before this piece is done, so what was read above is its own
+      sh[2] = __hip_atomic_fetch_max(&S.taken[want], seq, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) < seq;
+    }
+    __syncthreads();
+    if (sh[2]) return want;
   }
-  if (tid == 0) {
-    if (sigma) sigma[img] = R.sigma;
-    if (n_used) n_used[img] = R.used;
-    if (iters) iters[img] = R.iter;
+}
+
+constexpr int NZ_DIGITS = 2048;
+
+// One piece: its histogram (or count) added to the image's.
+template <typename T>
+__device__ __forceinline__ void noise_piece(const void* img, int64_t n, int piece, int pieces, NoiseImage& S,
+                                            const NoiseTask& t, uint32_t* h, uint32_t* tmp) {
+  const double m = t.m, thr = t.thr, mn = t.mn, tn = t.tn;
+  if (t.pass >= NZ_COUNT) {
+    const bool changed = t.pass == NZ_CHANGED;  // pixels in one of the two sets only
+    uint32_t c = 0, total;
+    for_pixels<T, 2>(img, n, piece, pieces, [&](float x) {
+      if (!__builtin_isfinite(x)) return;
+      const bool in = fabs((double)x - m) <= thr;
+      c += (changed ? in != (fabs((double)x - mn) <= tn) : in) ? 1u : 0u;
+    });
+    (void)block_scan(c, tmp, &total);
+    if (threadIdx.x == 0 && total) atomicAdd(&S.hist[0], total);
+  } else {
+    const bool dev = t.pass == NZ_DEV_DIGIT, two = t.pre[0] != t.pre[1];
+    const int hi = t.hi, lo = t.lo;
+    const uint32_t mask = (1u << (hi - lo)) - 1u;
+    const uint64_t p0 = t.pre[0] >> hi, p1 = t.pre[1] >> hi;
+    for (int b = threadIdx.x; b < 2 * NZ_DIGITS; b += NZ_TX) h[b] = 0u;
+    __syncthreads();
+    for_pixels<T, 2>(img, n, piece, pieces, [&](float x) {
+      if (!(__builtin_isfinite(x) && fabs((double)x - m) <= thr)) return;
+      const uint64_t key = dev ? (uint64_t)__double_as_longlong(fabs((double)x - mn)) : (uint64_t)fkey(x);
+      const uint32_t d = (uint32_t)(key >> lo) & mask;
+      if (key >> hi == p0) atomicAdd(&h[d], 1u);
+      if (two && key >> hi == p1) atomicAdd(&h[NZ_DIGITS + d], 1u);
+    });
+    __syncthreads();
+    for (int b = threadIdx.x; b < 2 * NZ_DIGITS; b += NZ_TX)
+      if (h[b]) atomicAdd(&S.hist[b], h[b]);
   }
-  if (meta) {
-    // meta is in epoch order; meta[i].src names the image
-    for (int i = tid; i < n_img; i += NZ_TX)
-      if (meta[i].src == img) meta[i].vs = (float)(R.sigma * R.sigma);
+  settle();
+  __syncthreads();
+  if (threadIdx.x == 0) __hip_atomic_fetch_add(&S.done, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+
+template <typename T>
+__global__ __launch_bounds__(NZ_TX) void k_noise_pixels(const void* const* imgs, const int64_t* npix, NoiseImage* st,
+                                                        double kappa, int max_iter, int n_img, double* sigma,
+                                                        int64_t* n_used, int32_t* iters, ExpMeta* meta) {
+  __shared__ uint32_t h[2 * NZ_DIGITS];
+  __shared__ uint32_t tmp[NZ_WAVES];
+  __shared__ uint64_t sh[2];
+  __shared__ NoiseTask task;
+  __shared__ uint32_t sh_i[3];
+  __shared__ uint32_t n_todo;
+  const int tid = threadIdx.x;
+  if (tid == 0) n_todo = 0u;
+  __syncthreads();
+  for (int i = tid; i < n_img; i += NZ_TX)
+    if (st[i].todo) atomicAdd(&n_todo, 1u);
+  __syncthreads();
+  if (n_todo == 0u) return;
+  // pieces: two for each workgroup that an image gets (a piece costs its histogram of 4096 words)
+  const int most = (int)std::min<uint32_t>(NZ_PIECES, std::max<uint32_t>(16u, 2u * gridDim.x / n_todo));
+  for (int v = 0; v < n_img; ++v) {
+    const int img = (int)(((int64_t)blockIdx.x + v) % n_img);
+    NoiseImage& S = st[img];
+    if (!S.todo) continue;
+    const void* p = imgs[img];
+    const int64_t n_pix = npix[img];
+    const int pieces = (int)std::min<int64_t>(most, (n_pix + NZ_TX * 16 - 1) / (NZ_TX * 16));
+    __syncthreads();  // sh_i is read
+    if (tid == 0) sh_i[0] = __hip_atomic_fetch_add(&S.role, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    __syncthreads();
+    const int role = (int)sh_i[0];
+    uint32_t last = 0;
+    if (role > 0) {
+      if (role >= pieces) continue;
+      for (int i; (i = noise_take(S, pieces, role, last, &task, sh_i)) >= 0;)
+        noise_piece<T>(p, n_pix, i, pieces, S, task, h, tmp);
+      continue;
+    }
+    uint32_t seq = 0;
+    // one pass with the workgroups that are here; its sums are in h afterwards, and the image's are clear again
+    double m = 0.0, thr = __builtin_inf(), mn = 0.0, tn = 0.0;
+    auto run = [&](NoisePass pass, int hi, int lo, uint64_t pre0, uint64_t pre1) {
+      for (int b = tid; b < 2 * NZ_DIGITS; b += NZ_TX)
+        __hip_atomic_store(&S.hist[b], 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      settle();
+      __syncthreads();
+      ++seq;
+      if (tid == 0) {
+        shared_set(&S.task[0], (uint64_t)__double_as_longlong(m));
+        shared_set(&S.task[1], (uint64_t)__double_as_longlong(thr));
+        shared_set(&S.task[2], (uint64_t)__double_as_longlong(mn));
+        shared_set(&S.task[3], (uint64_t)__double_as_longlong(tn));
+        shared_set(&S.task[4], pre0);
+        shared_set(&S.task[5], pre1);
+        shared_set(&S.task[6], (uint64_t)(pass | hi << 8 | lo << 16));
+        __hip_atomic_store(&S.done, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        settle();
+        __hip_atomic_store(&S.call, seq, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      }
+      for (int i; (i = noise_take(S, pieces, 0, last, &task, sh_i)) >= 0;)
+        noise_piece<T>(p, n_pix, i, pieces, S, task, h, tmp);
+      if (tid == 0)
+        while (__hip_atomic_load(&S.done, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) < (uint32_t)pieces)
+          __builtin_amdgcn_s_sleep(2);
+      settle();
+      __syncthreads();
+      for (int b = tid; b < 2 * NZ_DIGITS; b += NZ_TX)
+        h[b] = __hip_atomic_load(&S.hist[b], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      __syncthreads();
+    };
+    auto count = [&](NoisePass pass) {
+      run(pass, 0, 0, 0, 0);
+      return (int64_t)h[0];
+    };
+    // mean of the two middle values of the set: of x, or of |x - mn|
+    auto middle = [&](int64_t n, bool dev) {
+      uint64_t pre0 = 0, pre1 = 0;
+      int64_t rank0 = (n - 1) / 2, rank1 = n / 2;
+      for (int hi = dev ? 63 : 32; hi > 0;) {
+        const int lo = max(hi - 11, 0);
+        const bool two = pre0 != pre1;
+        run(dev ? NZ_DEV_DIGIT : NZ_DIGIT, hi, lo, pre0, pre1);
+        auto digit = [&](const uint32_t* H, uint64_t& pre, int64_t& rank) {
+          const uint32_t c0 = H[2 * tid], c1 = H[2 * tid + 1];
+          uint32_t total;
+          const uint32_t e = block_scan(c0 + c1, tmp, &total);
+          const uint32_t r = (uint32_t)rank;
+          if (r >= e && r < e + c0 + c1) {
+            const bool second = r >= e + c0;
+            sh[0] = (uint64_t)(2 * tid + (second ? 1 : 0));
+            sh[1] = e + (second ? c0 : 0u);
+          }
+          __syncthreads();
+          pre |= sh[0] << lo;
+          rank -= (int64_t)sh[1];
+          __syncthreads();
+        };
+        digit(h, pre0, rank0);
+        digit(two ? h + NZ_DIGITS : h, pre1, rank1);
+        hi = lo;
+      }
+      if (dev) return 0.5 * (__longlong_as_double((long long)pre0) + __longlong_as_double((long long)pre1));
+      return 0.5 * ((double)fkey_value((uint32_t)pre0) + (double)fkey_value((uint32_t)pre1));
+    };
+    NoiseResult R{__builtin_nan(""), 0, 0};
+    int64_t n = count(NZ_COUNT);
+    while (n > 0) {
+      mn = middle(n, false);
+      R.sigma = 1.4826 * middle(n, true);
+      R.used = n;
+      R.iter++;
+      tn = kappa * R.sigma;
+      const bool changed = count(NZ_CHANGED) != 0;
+      m = mn;
+      thr = tn;
+      if (!changed || R.iter >= max_iter) break;
+      n = count(NZ_COUNT);
+    }
+    if (tid == 0) __hip_atomic_store(&S.call, ~0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    noise_result(R, img, n_img, sigma, n_used, iters, meta);
   }
 }
 
@@ -891,8 +1075,11 @@ static hipError_t noise_t(const void* const* d_imgs, const int64_t* d_npix, int6
   hipLaunchKernelGGL(k_noise_bins<T>, grid, blk, 0, s, d_imgs, d_npix, st);
   hipLaunchKernelGGL(k_noise_plan, dim3(n_img), blk, 0, s, st, kappa, max_iter);
   hipLaunchKernelGGL(k_noise_collect<T>, grid, blk, 0, s, d_imgs, d_npix, st);
-  hipLaunchKernelGGL(k_noise_solve<T>, dim3(n_img), blk, 0, s, d_imgs, d_npix, st, kappa, max_iter, n_img, d_sigma,
-                     d_used, d_iters, d_meta);
+  hipLaunchKernelGGL(k_noise_solve, dim3(n_img), blk, 0, s, st, kappa, max_iter, n_img, d_sigma, d_used, d_iters,
+                     d_meta);
+  if (max_pix > NZ_WHOLE)  // (images listed whole are always solved above)
+    hipLaunchKernelGGL(k_noise_pixels<T>, dim3(512), blk, 0, s, d_imgs, d_npix, st, kappa, max_iter, n_img, d_sigma,
+                       d_used, d_iters, d_meta);
   return hipGetLastError();
 }
 

@@ -72,3 +72,25 @@ def test_noise_routes_match_oracle(n, dtype):
             assert (used[k], it[k]) == (wu, wi), (KINDS[k], kappa, used[k], wu, it[k], wi)
             assert sig[k] == ws or (math.isnan(ws) and math.isnan(sig[k])), (KINDS[k], kappa, sig[k], ws)
     ctx.close()
+
+
+@pytest.mark.parametrize("n_img,n,every", [(1, 4194304, 1), (1, 262145, 1), (5, 1000003, 5), (300, 16385, 7), (30, 70001, 1)])
+def test_images_the_plan_misses_shared_by_workgroups(n_img, n, every):
+    """Every `every`-th image is solved from its pixels: one by all workgroups,
+    some among many, more pieces than workgroups; the calls follow one another
+    with no synchronisation."""
+    import torch
+    import paper_2503_08854_amd as dt
+    rng = np.random.default_rng(n_img + n)
+    host = [_images("two_scales" if k % (2 * every) == 0 else "bimodal" if k % every == 0 else "normal", n,
+                    rng).astype("float32") for k in range(n_img)]
+    dev = [torch.from_numpy(x).cuda().view(1, n) for x in host]
+    ctx = dt.Context(0)
+    got = [dt.image_noise(ctx, dev, 3.0, 10) for _ in range(3)]
+    torch.cuda.synchronize()
+    want = [oracle.mad_noise(x, 3.0, 10) for x in host]
+    for sig, used, it in got:
+        assert sig.cpu().tolist() == [w[0] for w in want]
+        assert used.cpu().tolist() == [w[1] for w in want]
+        assert it.cpu().tolist() == [w[2] for w in want]
+    ctx.close()
