@@ -330,9 +330,7 @@ hipError_t launch_noise(const void* const* d_imgs, const int64_t* d_npix, int64_
 // Device-side orbit sampling (GenerateOrbits) and generate-and-stack.
 hipError_t launch_generate(const dt_orbit_sampler& S, int64_t first, int64_t n, double* a, double* e, double* inc,
                            double* node, double* peri, double* m0, hipStream_t s);
-// probe: the checkpoint walk defers at a lower share of samples that land.
-hipError_t launch_stack_generated(const StackArgs& a, const dt_orbit_sampler& S, int64_t first, hipStream_t s,
-                                  bool probe = false);
+hipError_t launch_stack_generated(const StackArgs& a, const dt_orbit_sampler& S, int64_t first, hipStream_t s);
 // Per-sample walk of every generated orbit (no checkpoint kernel, no list).
 hipError_t launch_stack_generated_walk(const StackArgs& a, const dt_orbit_sampler& S, int64_t first, hipStream_t s);
 

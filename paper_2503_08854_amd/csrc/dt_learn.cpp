@@ -128,7 +128,7 @@ dt_status dt_stack_generated(dt_patch* p, const dt_orbit_sampler* S, int64_t fir
   // picks the walk for the rest.
   StackArgs a1 = a;
   a1.n = GEN_PROBE;
-  hipError_t e = launch_stack_generated(a1, *S, first, p->ctx->stream, true);
+  hipError_t e = launch_stack_generated(a1, *S, first, p->ctx->stream);
   unsigned int deferred = 0;
   if (e == hipSuccess)
     e = hipMemcpyAsync(&deferred, a.defer_count, sizeof(deferred), hipMemcpyDeviceToHost, p->ctx->stream);

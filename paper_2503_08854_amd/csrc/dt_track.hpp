@@ -31,7 +31,7 @@
 // per-sample walk.
 //
 // The prediction pays while most samples miss.  A wavefront whose orbits land
-// often (more than a fixed share of its lane-exposures queued, once
+// often (more than 1 / TRACK_SWITCH_DEN of its lane-exposures queued, once
 // TRACK_SWITCH_MIN exposures are tested or its queue is full, e.g. distant
 // objects the field follows for months) gives its orbits up when the launch
 // allows it:
@@ -48,25 +48,15 @@ constexpr float PRED_SLACK = 1e-9f;  // AU: rounding of the checkpoint state and
 constexpr int TQ_CAP = 128;          // queued samples per wavefront (< 64 held + 64 pushed)
 constexpr int TQ_LIST = 8;           // queued samples per lane between flushes
 constexpr int CK_ANCHOR = 8;         // checkpoints between full sincos re-anchors of sin E, cos E
-// A wavefront defers above 2/7 of its lane-exposures queued, in a probe
-// (PROBE: the first orbits of a call whose others follow the probe's majority)
-// above 1/5.  With a tenth of the samples landing (10^6
-// generated orbits on 48 exposures of one field) the search takes 1.41 ms at
-// 1/8, 1.31 at 1/5, 1.27 at 1/4, 1.195 at 2/7, 1.19 at 1/3 and 1.20 at 1/2.
-// With a third (distant orbits, probed) the line decides whether all of the
-// probe's wavefronts are seen to defer: 78 ms, and 81 at 1/3 and 108 at 1/2.
-// 4 10^6 stored ones on 60 exposures: 3.25 ms at 1/5, 2.59 at 2/7.  (The line
-// is a constant of the kernel: as an argument it cost the survey stack a
-// spilled scalar in the dense step, 3.81 -> 4.63 ms.)
+constexpr int TRACK_SWITCH_DEN = 5;  // a wavefront defers above 1/5 of its lane-exposures queued
 constexpr int TRACK_SWITCH_MIN = 3;  // exposures tested before the fraction is trusted
 
-// More than the fraction of the 64 n_tested lane-exposures queued: for an
-// integer count, q > x exactly when q > floor(x).  Plain 32-bit arithmetic on
-// wave-uniform counts, so scalar instructions only (the walk runs with fewer
-// than 2^25 exposures, so 128 n_tested < 2^32).
-__device__ __forceinline__ bool over_switch(int queued, int n_tested, bool probe) {
-  const unsigned n = 64u * (unsigned)n_tested;
-  return queued > (int)(probe ? n / 5u : 2u * n / 7u);
+// More than 1 / TRACK_SWITCH_DEN of the 64 n_tested lane-exposures queued:
+// for an integer count, q > 64 n / 5 exactly when q > floor(64 n / 5).  Plain
+// 32-bit arithmetic on wave-uniform counts, so scalar instructions only (the
+// walk runs with fewer than 2^25 exposures, so 64 n_tested < 2^31).
+__device__ __forceinline__ bool over_switch(int queued, int n_tested) {
+  return queued > (int)(((unsigned)n_tested << 6) / (unsigned)TRACK_SWITCH_DEN);
 }
 
 // One wavefront's state in LDS: the queue, and each lane's prepared orbit and
@@ -121,7 +111,7 @@ __device__ __forceinline__ void track_bound(double a, double e, const Orbit& o, 
 // checkpoint epoch in a vector register, so that D = t - tc is one
 // instruction per exposure rather than a copy and a subtraction (~1 % on the
 // stacks that fit it without spilling; the cell and id-list kernels do not).
-template <bool REC = false, bool DEFER = true, bool TCV = false, bool PROBE = false>
+template <bool REC = false, bool DEFER = true, bool TCV = false>
 __device__ __forceinline__ void track_walk(const StackArgs& A, const Orbit& o, const TrackBound& bd, bool live,
                                            TrackQueue& Qm, StackPart& P, bool& deferred,
                                            const DebugArgs* dbg = nullptr, int64_t rowbase = 0) {
@@ -188,9 +178,9 @@ __device__ __forceinline__ void track_walk(const StackArgs& A, const Orbit& o, c
       const bool ck = ex >= ck_at;
       const bool fl = count > 0;
       // a wavefront due to serve its queue whose queued fraction is already
-      // above the switch defers now rather than solve samples the
+      // above 1 / TRACK_SWITCH_DEN defers now rather than solve samples the
       // per-sample walk repeats
-      tail = may_defer && fl && !last && over_switch(queued + count, n_tested, PROBE);
+      tail = may_defer && fl && !last && over_switch(queued + count, n_tested);
       if (tail) break;
       const int nb = fl ? (count + 63) >> 6 : 0;
       float tg_ck = 0.f;  // a Newton start only
@@ -389,7 +379,7 @@ __device__ __forceinline__ void track_walk(const StackArgs& A, const Orbit& o, c
       // (nothing queued is served).  A queue that fills before
       // TRACK_SWITCH_MIN exposures decides at once, rather than serving
       // solves the per-sample walk would repeat.
-      tail = may_defer && (n_tested >= TRACK_SWITCH_MIN || full) && over_switch(queued + count, n_tested, PROBE);
+      tail = may_defer && (n_tested >= TRACK_SWITCH_MIN || full) && over_switch(queued + count, n_tested);
       if (tail) break;
     }
   }
@@ -410,7 +400,7 @@ __device__ __forceinline__ void track_walk(const StackArgs& A, const Orbit& o, c
 // per-sample stack (NaN, NaN, -1 for an orbit that is not live), or nothing
 // when the wavefront deferred its orbits (returns true).  All 64 lanes of the
 // wavefront call it together; Q is the wavefront's LDS queue.
-template <bool REC = false, bool DEFER = true, bool TCV = false, bool PROBE = false>
+template <bool REC = false, bool DEFER = true, bool TCV = false>
 __device__ __forceinline__ bool track_stack_lane(const StackArgs& A, const double el[6], bool live, TrackQueue& Q,
                                                  float& snr, float& flux, int& nv, const DebugArgs* dbg = nullptr,
                                                  int64_t rowbase = 0) {
@@ -425,7 +415,7 @@ __device__ __forceinline__ bool track_stack_lane(const StackArgs& A, const doubl
   track_bound(a, e, ob, A.vobs, bd);
   StackPart P;
   bool deferred = false;
-  track_walk<REC, DEFER, TCV, PROBE>(A, ob, bd, live, Q, P, deferred, dbg, rowbase);
+  track_walk<REC, DEFER, TCV>(A, ob, bd, live, Q, P, deferred, dbg, rowbase);
   snr = flux = __builtin_nanf("");
   nv = -1;
   if (deferred) return true;

@@ -116,7 +116,6 @@ __global__ __launch_bounds__(256) void k_stack_generated(StackArgs A, dt_orbit_s
 }
 
 // The same by checkpoint prediction (one wavefront per 64 generated orbits).
-template <bool PROBE>
 __global__ __launch_bounds__(64, 4) void k_stack_generated_track(StackArgs A, dt_orbit_sampler S, int64_t first) {
   __shared__ TrackQueue tq[1];
   if (wave_base() >= A.n) return;  // the whole wavefront is past the end
@@ -129,7 +128,7 @@ __global__ __launch_bounds__(64, 4) void k_stack_generated_track(StackArgs A, dt
     double el[6] = {0.0, 0.0, 0.0, 0.0, 0.0, 0.0};
     const bool live = in && gen_orbit(S, (uint64_t)(first + i), el) &&
                       orbit_ok(el[0], el[1], el[2], el[3], el[4], el[5]);
-    if (track_stack_lane<false, true, true, PROBE>(A, el, live, tq[threadIdx.x >> 6], snr, flux, nv)) {
+    if (track_stack_lane<false, true, true>(A, el, live, tq[threadIdx.x >> 6], snr, flux, nv)) {
       defer_wave(A, wave_base());
       return;
     }
@@ -225,7 +224,7 @@ hipError_t launch_stack_generated_walk(const StackArgs& a, const dt_orbit_sample
   return hipGetLastError();
 }
 
-hipError_t launch_stack_generated(const StackArgs& a, const dt_orbit_sampler& S, int64_t first, hipStream_t s, bool probe) {
+hipError_t launch_stack_generated(const StackArgs& a, const dt_orbit_sampler& S, int64_t first, hipStream_t s) {
   if (a.n <= 0) return hipSuccess;
   const int split = stack_split(a);
   if (split) {
@@ -243,9 +242,7 @@ hipError_t launch_stack_generated(const StackArgs& a, const dt_orbit_sampler& S,
       hipError_t e = launch_zero_u32(a.defer_count, s);
       if (e != hipSuccess) return e;
     }
-    const dim3 g((unsigned)((a.n + 63) / 64));
-    if (probe) hipLaunchKernelGGL(k_stack_generated_track<true>, g, dim3(64), 0, s, a, S, first);
-    else hipLaunchKernelGGL(k_stack_generated_track<false>, g, dim3(64), 0, s, a, S, first);
+    hipLaunchKernelGGL(k_stack_generated_track, dim3((unsigned)((a.n + 63) / 64)), dim3(64), 0, s, a, S, first);
     if (a.defer_list)
       hipLaunchKernelGGL(k_stack_generated_deferred, dim3((unsigned)((a.n + 255) / 256)), dim3(256), 0, s, a, S,
                          first);
