@@ -75,6 +75,7 @@ struct NoiseImage {
   int32_t whole;    // one bin, every value listed
   int32_t n_sample; // finite values of the sample
   int32_t todo;     // the plan missed: solve from the pixels
+  uint32_t n_todo;  // first image: images with todo
   uint32_t role, done;       // workgroups that came to it, pieces done
   uint32_t call;             // number of the pass; 0: none yet, ~0: done
   uint32_t taken[NZ_PIECES]; // pass in which a piece was taken last
@@ -253,6 +254,7 @@ __global__ __launch_bounds__(NZ_TX) void k_noise_sample(const void* const* imgs,
     S.whole = n <= NZ_WHOLE;
     S.n_sample = 0;
     S.role = 0;
+    S.n_todo = 0;
     S.call = 0;
   }
   if (n <= NZ_WHOLE) {  // every value is listed: one bin
@@ -798,7 +800,10 @@ __global__ __launch_bounds__(NZ_TX) void k_noise_solve(NoiseImage* st, double ka
     }
   }
   // (every thread computed the same `good` and R)
-  if (tid == 0) S.todo = !good;
+  if (tid == 0) {
+    S.todo = !good;
+    if (!good) atomicAdd(&st[0].n_todo, 1u);
+  }
   if (good) noise_result(R, img, n_img, sigma, n_used, iters, meta);
 }
 
@@ -946,13 +951,8 @@ __global__ __launch_bounds__(NZ_TX) void k_noise_pixels(const void* const* imgs,
   __shared__ uint64_t sh[2];
   __shared__ NoiseTask task;
   __shared__ uint32_t sh_i[3];
-  __shared__ uint32_t n_todo;
   const int tid = threadIdx.x;
-  if (tid == 0) n_todo = 0u;
-  __syncthreads();
-  for (int i = tid; i < n_img; i += NZ_TX)
-    if (st[i].todo) atomicAdd(&n_todo, 1u);
-  __syncthreads();
+  const uint32_t n_todo = st[0].n_todo;
   if (n_todo == 0u) return;
   // pieces: two for each workgroup that an image gets (a piece costs its histogram of 4096 words)
   const int most = (int)std::min<uint32_t>(NZ_PIECES, std::max<uint32_t>(16u, 2u * gridDim.x / n_todo));
