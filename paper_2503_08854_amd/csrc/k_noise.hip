@@ -24,6 +24,8 @@
 //            checked to fall in a marked bin (or a gap without pixels); if
 //            one does not, the image is solved by radix selection over its
 //            pixels (pixels, a kernel that ends at once if there is none).
+// The counts of the histogram route are 32-bit: an image of 2^32 pixels or
+// more goes straight to the radix selection, whose counts are 64-bit.
 // All comparisons that decide the result are the FP64 ones of the definition,
 // so the result is exact on either route.
 //
@@ -50,6 +52,7 @@ constexpr int NZ_WAVES = NZ_TX / 64;
 constexpr int NZ_SAMPLE = 4096;       // sample size
 constexpr int NZ_SAMPLE_STEPS = 6;    // clip steps followed on the sample
 constexpr int64_t NZ_WHOLE = 16384;   // images up to this size are listed whole
+constexpr int64_t NZ_MOST = 0xffffffffll;  // images beyond it are solved from their pixels
 constexpr int NZ_LIST = 32768;        // listed values per image
 constexpr int NZ_TAB = 512;           // marked bins per image
 constexpr int NZ_STAGE = 2048;        // values a collecting workgroup stages in LDS
@@ -84,7 +87,7 @@ struct NoiseImage {
   uint32_t bin[NZ_TAB], below[NZ_TAB], cnt[NZ_TAB];  // marked bins: index, pixels below, pixels in
   uint32_t heavy[NZ_TAB];                            // key of the value that is not listed (0: none)
   uint16_t mode[NZ_BINS];                            // 0 not listed, 0xffff listed, else 1 + table entry (heavy value)
-  uint32_t hist[NZ_BINS];
+  alignas(8) uint32_t hist[NZ_BINS];  // in the radix selection: 64-bit sums of a pass
   uint32_t sample[NZ_SAMPLE];  // sorted keys
   uint32_t list[NZ_LIST];      // keys
 };
@@ -142,19 +145,20 @@ __device__ __forceinline__ void for_pixels(const void* img, int64_t n, int block
 }
 
 // Exclusive prefix sum over the workgroup; *total is the sum.  tmp: NZ_WAVES
-// words of LDS.
-__device__ __forceinline__ uint32_t block_scan(uint32_t v, uint32_t* tmp, uint32_t* total) {
+// values in LDS.
+template <typename C>
+__device__ __forceinline__ C block_scan(C v, C* tmp, C* total) {
   const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
-  uint32_t inc = v;
+  C inc = v;
 #pragma unroll
   for (int o = 1; o < 64; o <<= 1) {
-    const uint32_t u = (uint32_t)__shfl_up((int)inc, o, 64);
+    const C u = __shfl_up(inc, o, 64);
     if (lane >= o) inc += u;
   }
   __syncthreads();  // earlier readers of tmp
   if (lane == 63) tmp[w] = inc;
   __syncthreads();
-  uint32_t base = 0, sum = 0;
+  C base = 0, sum = 0;
   for (int i = 0; i < NZ_WAVES; ++i) {
     if (i < w) base += tmp[i];
     sum += tmp[i];
@@ -261,6 +265,10 @@ __global__ __launch_bounds__(NZ_TX) void k_noise_sample(const void* const* imgs,
     if (tid == 0) S.map = NoiseMap{0.f, 1.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
     return;
   }
+  if (n > NZ_MOST) {
+    if (tid == 0) S.n_tab = -1;
+    return;
+  }
   const auto* p = global_ptr(static_cast<const T*>(imgs[img]));
   uint32_t mine = 0;
   for (int i = tid; i < NZ_SAMPLE; i += NZ_TX) {
@@ -355,9 +363,10 @@ __global__ __launch_bounds__(NZ_TX) void k_noise_sample(const void* const* imgs,
 template <typename T>
 __global__ __launch_bounds__(NZ_TX) void k_noise_bins(const void* const* imgs, const int64_t* npix, NoiseImage* st) {
   const int img = blockIdx.y;
+  NoiseImage& S = st[img];
+  if (S.n_tab < 0) return;
   __shared__ uint32_t h[NZ_BINS];
   for (int b = threadIdx.x; b < NZ_BINS; b += NZ_TX) h[b] = 0u;
-  NoiseImage& S = st[img];
   const NoiseMap M = S.map;
   __syncthreads();
   for_pixels<T>(imgs[img], npix[img], blockIdx.x, gridDim.x, [&](float x) {
@@ -374,6 +383,7 @@ __global__ __launch_bounds__(NZ_TX) void k_noise_bins(const void* const* imgs, c
 __global__ __launch_bounds__(NZ_TX) void k_noise_plan(NoiseImage* st, double kappa, int max_iter) {
   const int tid = threadIdx.x, lane = tid & 63;
   NoiseImage& S = st[blockIdx.x];
+  if (S.n_tab < 0) return;
   __shared__ uint32_t C[NZ_BINS + 1];
   __shared__ uint32_t mark[NZ_BINS / 32];
   __shared__ uint32_t tmp[NZ_WAVES];
@@ -903,8 +913,11 @@ __device__ __forceinline__ int noise_take(NoiseImage& S, int pieces, int r, uint
 }
 
 constexpr int NZ_DIGITS = 2048;
+static_assert(2 * NZ_DIGITS * 2 <= NZ_BINS, "64-bit sums in the histogram's place");
+typedef unsigned long long NoiseSum;
+__device__ __forceinline__ NoiseSum* noise_sums(NoiseImage& S) { return reinterpret_cast<NoiseSum*>(S.hist); }
 
-// One piece: its histogram (or count) added to the image's.
+// One piece (fewer than 2^32 pixels): its histogram (or count) added to the image's.
 template <typename T>
 __device__ __forceinline__ void noise_piece(const void* img, int64_t n, int piece, int pieces, NoiseImage& S,
                                             const NoiseTask& t, uint32_t* h, uint32_t* tmp) {
@@ -918,7 +931,7 @@ __device__ __forceinline__ void noise_piece(const void* img, int64_t n, int piec
       c += (changed ? in != (fabs((double)x - mn) <= tn) : in) ? 1u : 0u;
     });
     (void)block_scan(c, tmp, &total);
-    if (threadIdx.x == 0 && total) atomicAdd(&S.hist[0], total);
+    if (threadIdx.x == 0 && total) atomicAdd(&noise_sums(S)[0], (NoiseSum)total);
   } else {
     const bool dev = t.pass == NZ_DEV_DIGIT, two = t.pre[0] != t.pre[1];
     const int hi = t.hi, lo = t.lo;
@@ -935,7 +948,7 @@ __device__ __forceinline__ void noise_piece(const void* img, int64_t n, int piec
     });
     __syncthreads();
     for (int b = threadIdx.x; b < 2 * NZ_DIGITS; b += NZ_TX)
-      if (h[b]) atomicAdd(&S.hist[b], h[b]);
+      if (h[b]) atomicAdd(&noise_sums(S)[b], (NoiseSum)h[b]);
   }
   settle();
   __syncthreads();
@@ -947,7 +960,9 @@ __global__ __launch_bounds__(NZ_TX) void k_noise_pixels(const void* const* imgs,
                                                         double kappa, int max_iter, int n_img, double* sigma,
                                                         int64_t* n_used, int32_t* iters, ExpMeta* meta) {
   __shared__ uint32_t h[2 * NZ_DIGITS];
+  __shared__ NoiseSum sums[2 * NZ_DIGITS];
   __shared__ uint32_t tmp[NZ_WAVES];
+  __shared__ NoiseSum tmp_sum[NZ_WAVES];
   __shared__ uint64_t sh[2];
   __shared__ NoiseTask task;
   __shared__ uint32_t sh_i[3];
@@ -962,7 +977,9 @@ __global__ __launch_bounds__(NZ_TX) void k_noise_pixels(const void* const* imgs,
     if (!S.todo) continue;
     const void* p = imgs[img];
     const int64_t n_pix = npix[img];
-    const int pieces = (int)std::min<int64_t>(most, (n_pix + NZ_TX * 16 - 1) / (NZ_TX * 16));
+    // (of fewer than 2^32 pixels each: memory ends before the most pieces of that size)
+    const int pieces = (int)std::min<int64_t>(std::max<int64_t>(most, std::min<int64_t>(NZ_PIECES, (n_pix >> 31) + 1)),
+                                              (n_pix + NZ_TX * 16 - 1) / (NZ_TX * 16));
     __syncthreads();  // sh_i is read
     if (tid == 0) sh_i[0] = __hip_atomic_fetch_add(&S.role, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     __syncthreads();
@@ -975,11 +992,11 @@ __global__ __launch_bounds__(NZ_TX) void k_noise_pixels(const void* const* imgs,
       continue;
     }
     uint32_t seq = 0;
-    // one pass with the workgroups that are here; its sums are in h afterwards, and the image's are clear again
+    // one pass with the workgroups that are here; its sums are in `sums` afterwards
     double m = 0.0, thr = __builtin_inf(), mn = 0.0, tn = 0.0;
     auto run = [&](NoisePass pass, int hi, int lo, uint64_t pre0, uint64_t pre1) {
       for (int b = tid; b < 2 * NZ_DIGITS; b += NZ_TX)
-        __hip_atomic_store(&S.hist[b], 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        __hip_atomic_store(&noise_sums(S)[b], (NoiseSum)0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
       settle();
       __syncthreads();
       ++seq;
@@ -1003,12 +1020,12 @@ __global__ __launch_bounds__(NZ_TX) void k_noise_pixels(const void* const* imgs,
       settle();
       __syncthreads();
       for (int b = tid; b < 2 * NZ_DIGITS; b += NZ_TX)
-        h[b] = __hip_atomic_load(&S.hist[b], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        sums[b] = __hip_atomic_load(&noise_sums(S)[b], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
       __syncthreads();
     };
     auto count = [&](NoisePass pass) {
       run(pass, 0, 0, 0, 0);
-      return (int64_t)h[0];
+      return (int64_t)sums[0];
     };
     // mean of the two middle values of the set: of x, or of |x - mn|
     auto middle = [&](int64_t n, bool dev) {
@@ -1018,23 +1035,23 @@ __global__ __launch_bounds__(NZ_TX) void k_noise_pixels(const void* const* imgs,
         const int lo = max(hi - 11, 0);
         const bool two = pre0 != pre1;
         run(dev ? NZ_DEV_DIGIT : NZ_DIGIT, hi, lo, pre0, pre1);
-        auto digit = [&](const uint32_t* H, uint64_t& pre, int64_t& rank) {
-          const uint32_t c0 = H[2 * tid], c1 = H[2 * tid + 1];
-          uint32_t total;
-          const uint32_t e = block_scan(c0 + c1, tmp, &total);
-          const uint32_t r = (uint32_t)rank;
+        auto digit = [&](const NoiseSum* H, uint64_t& pre, int64_t& rank) {
+          const NoiseSum c0 = H[2 * tid], c1 = H[2 * tid + 1];
+          NoiseSum total;
+          const NoiseSum e = block_scan(c0 + c1, tmp_sum, &total);
+          const NoiseSum r = (NoiseSum)rank;
           if (r >= e && r < e + c0 + c1) {
             const bool second = r >= e + c0;
             sh[0] = (uint64_t)(2 * tid + (second ? 1 : 0));
-            sh[1] = e + (second ? c0 : 0u);
+            sh[1] = e + (second ? c0 : 0);
           }
           __syncthreads();
           pre |= sh[0] << lo;
           rank -= (int64_t)sh[1];
           __syncthreads();
         };
-        digit(h, pre0, rank0);
-        digit(two ? h + NZ_DIGITS : h, pre1, rank1);
+        digit(sums, pre0, rank0);
+        digit(two ? sums + NZ_DIGITS : sums, pre1, rank1);
         hi = lo;
       }
       if (dev) return 0.5 * (__longlong_as_double((long long)pre0) + __longlong_as_double((long long)pre1));
