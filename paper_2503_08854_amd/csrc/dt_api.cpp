@@ -327,14 +327,17 @@ dt_status dt_patch_create(dt_ctx* c, const dt_exposure* exps, int32_t n_exp, con
   // 32; 30 of 700^2: 105 and 48), while large patches lose the 2R halo rows
   // that each strip reads again (60 FP16 2048^2 at R = 10: 1.06 ms at 128
   // rows, 1.51 at 32).
-  auto strips = [](const dt_exposure& x, int ty) { return std::max(1, (x.height + ty / 2) / ty); };
+  // (64-bit: an image one column wide may have 2^31 - 1 rows)
+  auto strips = [](const dt_exposure& x, int ty) {
+    return std::max<int64_t>(1, ((int64_t)x.height + ty / 2) / ty);
+  };
   auto tile_R = [&](int s) { return sorted[s].width == 1 ? 0 : rad[s]; };
   auto tile_w = [&](int s) { return tile_R(s) ? prep_width(tile_R(s)) : 1; };
   int ty = PREP_TY;
   for (; ty > PREP_TY_MIN; ty /= 2) {
     int64_t n = 0;
     for (int s = 0; s < n_exp; ++s)
-      n += (int64_t)strips(sorted[s], ty) * ((sorted[s].width + tile_w(s) - 1) / tile_w(s));
+      n += strips(sorted[s], ty) * (((int64_t)sorted[s].width + tile_w(s) - 1) / tile_w(s));
     if (n >= PREP_TILES) break;
   }
   for (int R = 0; R <= PREP_RMAX; ++R) {
@@ -342,10 +345,10 @@ dt_status dt_patch_create(dt_ctx* c, const dt_exposure* exps, int32_t n_exp, con
     for (int s = 0; s < n_exp; ++s) {
       if (tile_R(s) != R) continue;
       const dt_exposure& x = sorted[s];
-      const int h = (x.height + strips(x, ty) - 1) / strips(x, ty);
-      for (int y0 = 0; y0 < x.height; y0 += h)
-        for (int x0 = 0; x0 < x.width; x0 += tile_w(s))
-          tiles.push_back(PrepTile{s, x0, y0, std::min(h, x.height - y0)});
+      const int64_t h = (x.height + strips(x, ty) - 1) / strips(x, ty);
+      for (int64_t y0 = 0; y0 < x.height; y0 += h)
+        for (int64_t x0 = 0; x0 < x.width; x0 += tile_w(s))
+          tiles.push_back(PrepTile{s, (int32_t)x0, (int32_t)y0, (int32_t)std::min(h, x.height - y0)});
     }
     if (tiles.size() > before) {
       p->group_off.push_back((int64_t)before);

@@ -421,7 +421,7 @@ __global__ __launch_bounds__(256) void k_prepass_column(const ExpMeta* __restric
   double zs = 0.0;
   for (int j = -m.R; j <= m.R; ++j) zs += tap(j);
   const double z = zs * zs;
-  for (int y = tl.y0 + (int)threadIdx.x; y < tl.y0 + tl.ny; y += 256) {
+  for (int64_t y = (int64_t)tl.y0 + threadIdx.x; y < (int64_t)tl.y0 + tl.ny; y += 256) {  // (past 2^31 in the tallest)
     float a = 0.f, b = 0.f;
     for (int j = -m.R; j <= m.R; ++j) {
       if (y + j < 0 || y + j >= m.H) continue;
