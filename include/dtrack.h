@@ -35,7 +35,7 @@
  *   learned cell proposer: dt_cell_stamps, dt_scorer_*, dt_cell_members_near,
  *                          dt_stack_ids, dt_stack_cells
  *   checking only: dt_debug_samples, dt_debug_stack_samples, dt_record_gathers,
- *                  dt_gather_replay, dt_ctx_count_work
+ *                  dt_gather_replay, dt_ctx_count_work, dt_debug_noise_pixels
  */
 #ifndef DTRACK_H
 #define DTRACK_H
@@ -488,6 +488,11 @@ dt_status dt_debug_samples(dt_patch *p, const dt_orbits *orbits, const int64_t *
 dt_status dt_debug_stack_samples(dt_patch *p, const dt_orbits *orbits, const int64_t *d_ids, int64_t m,
                                  double *d_px, double *d_py, int32_t *d_ix, int32_t *d_iy,
                                  int32_t *d_flags, float *d_psi, float *d_phi, double *d_tau);
+
+/* Checking only: how many images of the context's last dt_image_noise call
+ * were solved by selection over their pixels (the histogram route did not hold
+ * every place that their iteration visits); 0 before any call.  Synchronises. */
+dt_status dt_debug_noise_pixels(dt_ctx *ctx, int32_t *out);
 
 #ifdef __cplusplus
 }

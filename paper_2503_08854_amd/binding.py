@@ -92,6 +92,7 @@ def lib():
         "dt_cell_stamps": ([_P, C.POINTER(DtOrbits), C.c_double, C.c_double, _P, _P, _P, _P], C.c_int),
         "dt_image_noise": ([_P, C.c_int32, _P, _P, C.c_int, C.c_double, C.c_int32, _P, _P, _P], C.c_int),
         "dt_patch_noise": ([_P, _P], C.c_int),
+        "dt_debug_noise_pixels": ([_P, C.POINTER(C.c_int32)], C.c_int),
         "dt_record_gathers": ([_P, C.POINTER(DtOrbits), _P, _P, C.POINTER(C.c_int64), C.POINTER(C.c_int64)],
                               C.c_int),
         "dt_gather_replay": ([_P, _P, _P, C.c_int64, _P], C.c_int),
@@ -487,6 +488,13 @@ def image_noise(ctx: Context, images, kappa: float = 3.0, max_iter: int = 10):
     _check(lib().dt_image_noise(ctx.handle, n, ptrs, npx, DT_F32 if dt == torch.float32 else DT_F16, float(kappa),
                                 int(max_iter), _ptr(sig), _ptr(used), _ptr(it)))
     return sig, used, it
+
+
+def debug_noise_pixels(ctx: Context) -> int:
+    """Images of the last image_noise call that were solved from their pixels."""
+    out = C.c_int32()
+    _check(lib().dt_debug_noise_pixels(ctx.handle, C.byref(out)))
+    return out.value
 
 
 def orbit_sampler(field: dict, epoch: float, a_range, e_range, inc_deg_range, seed: int):

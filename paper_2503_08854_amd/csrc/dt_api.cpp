@@ -469,6 +469,7 @@ dt_status dt_image_noise(dt_ctx* c, int32_t n_img, const void* const* d_images, 
     (void)hipStreamSynchronize(c->stream);
     ctx_free(c, c->noise_ws, c->noise_bytes);
     c->noise_ws = nullptr;
+    c->noise_state = nullptr;
     c->noise_bytes = 0;
     dt_status st = ctx_alloc(c, &c->noise_ws, need, "noise scratch");
     if (st != DT_OK) return st;
@@ -485,7 +486,19 @@ dt_status dt_image_noise(dt_ctx* c, int32_t n_img, const void* const* d_images, 
   if (e == hipSuccess)
     e = launch_noise(d_ptrs, d_npix, max_pix, n_img, dtype, kappa, max_iter, ws + stage, d_sigma, d_n_used, d_iters,
                      nullptr, c->stream);
+  c->noise_state = e == hipSuccess ? ws + stage : nullptr;
   return e == hipSuccess ? DT_OK : hip_fail(e, "noise estimate");
+}
+
+dt_status dt_debug_noise_pixels(dt_ctx* c, int32_t* out) {
+  if (!c || !c->alive || !out) return fail(DT_E_ARG, "invalid context or NULL out");
+  *out = 0;
+  if (!c->noise_state) return DT_OK;
+  DeviceGuard g(c->device);
+  hipError_t e = hipMemcpyAsync(out, c->noise_state + noise_pixels_offset(), sizeof(int32_t), hipMemcpyDeviceToHost,
+                                c->stream);
+  if (e == hipSuccess) e = hipStreamSynchronize(c->stream);
+  return e == hipSuccess ? DT_OK : hip_fail(e, "noise count read");
 }
 
 dt_status dt_patch_release_images(dt_patch* p) {

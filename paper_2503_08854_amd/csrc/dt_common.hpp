@@ -323,6 +323,8 @@ hipError_t launch_gather_replay(const float2* planes, const int64_t* gstart, con
 constexpr double NOISE_KAPPA = 3.0;   // clip half-width in sigma (patches without variance planes)
 constexpr int NOISE_MAX_ITER = 10;
 size_t noise_scratch_bytes(int n_img);
+// Where the scratch holds the number (uint32) of images solved from their pixels.
+size_t noise_pixels_offset();
 hipError_t launch_noise(const void* const* d_imgs, const int64_t* d_npix, int64_t max_pix, int n_img, dt_dtype dtype,
                         double kappa, int max_iter, void* scratch, double* d_sigma, int64_t* d_used, int32_t* d_iters,
                         ExpMeta* d_meta, hipStream_t s);

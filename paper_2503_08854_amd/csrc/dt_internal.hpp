@@ -27,6 +27,7 @@ struct dt_ctx {
   unsigned long long* d_counter = nullptr;
   void* noise_ws = nullptr;  // staging + selection state of dt_image_noise
   size_t noise_bytes = 0;
+  const char* noise_state = nullptr;  // in it, of the last call (dt_debug_noise_pixels)
   dtk::BatchGraph* graph = nullptr;  // last captured batched launch
   hipStream_t capture_stream = nullptr;
   unsigned long long* d_work = nullptr;  // work counters (dt_ctx_count_work), WORK_SLOTS x WORK_N

@@ -38,6 +38,7 @@
 // values sorted by their deviation on either side; with every value trying
 // itself and one atomic minimum they took 0.39 ms instead of 0.19.)
 #include <algorithm>
+#include <cstddef>
 #include <type_traits>
 
 #include "dt_common.hpp"
@@ -89,7 +90,7 @@ struct NoiseImage {
   uint16_t mode[NZ_BINS];                            // 0 not listed, 0xffff listed, else 1 + table entry (heavy value)
   alignas(8) uint32_t hist[NZ_BINS];  // in the radix selection: 64-bit sums of a pass
   uint32_t sample[NZ_SAMPLE];  // sorted keys
-  uint32_t list[NZ_LIST];      // keys
+  alignas(8) uint32_t list[NZ_LIST];  // keys; in the radix selection: 64-bit ones
 };
 
 typedef float nz_f4 __attribute__((ext_vector_type(4)));
@@ -499,22 +500,22 @@ __global__ __launch_bounds__(NZ_TX) void k_noise_plan(NoiseImage* st, double kap
         uint32_t heavy = 0;
         mode = 0xffffu;
         if (!all && h[j] > (uint32_t)NZ_LIST / 64) {
-          // too full to list: the most frequent sample value in it is left
-          // out; a bin without a value that fills most of it stays unlisted
-          int lo = 0, hi = ns;
-          while (lo < hi) {
-            const int q = (lo + hi) >> 1;
-            if (map_bin(M, fkey_value(S.sample[q])) < b) lo = q + 1;
-            else hi = q;
-          }
-          int run = 0, most = 0, n_in = 0;
-          for (int q = lo; q < ns && map_bin(M, fkey_value(S.sample[q])) == b; ++q, ++n_in) {
-            run = q > lo && S.sample[q] == S.sample[q - 1] ? run + 1 : 1;
-            if (run > most) {
-              most = run;
-              heavy = S.sample[q];
+          // too full to list: the sample value that fills nine tenths of it (of
+          // its sorted sample values, then, the middle one) is left out; a bin
+          // without such a value stays unlisted
+          auto first = [&](auto&& from) {  // first sample key from which on from(key)
+            int lo = 0, hi = ns;
+            while (lo < hi) {
+              const int q = (lo + hi) >> 1;
+              if (from(S.sample[q])) hi = q;
+              else lo = q + 1;
             }
-          }
+            return lo;
+          };
+          const int lo = first([&](uint32_t key) { return map_bin(M, fkey_value(key)) >= b; });
+          const int n_in = first([&](uint32_t key) { return map_bin(M, fkey_value(key)) > b; }) - lo;
+          if (n_in > 0) heavy = S.sample[lo + n_in / 2];
+          const int most = first([&](uint32_t key) { return key > heavy; }) - first([&](uint32_t key) { return key >= heavy; });
           const bool use = 10 * most >= 9 * n_in && n_in > 0;
           mode = use ? (uint16_t)(k + 1) : (uint16_t)0;
           if (!use) heavy = 0;
@@ -829,14 +830,25 @@ __global__ __launch_bounds__(NZ_TX) void k_noise_solve(NoiseImage* st, double ka
 // relaxed device-scope atomics, ordered by waiting for them (settle): a
 // release or acquire of the whole device would write back or drop the L2 each
 // time (100 images at once 844 ms instead of 69, before the rest below).
-// Latency bounds a pass of one image (20 to 50 us: the call, one piece of
+// A step takes at most six passes while the values do not repeat: two digits
+// of the median, two of the deviation, the deviations that share these two
+// digits as a list (the leader finds the rest there; as soon as few enough are
+// left, for the median too), and the clip, which counts the change of the set
+// and is the first digit of the next median.
+//
+// Latency bounds a pass of one image (20 to 35 us: the call, one piece of
 // 16384 pixels a workgroup, the sums' atomics), the LDS atomics of equal digits
-// many.  2048^2 pixels, half of them 10^6 times narrower than the others (five
-// steps of eleven passes): one image 1.5 ms, 16 images 5.6, 100 images 23; two
-// far groups (one step) 0.85, 2.1 and 9.2; 31, 37 and 33 (14, 14 and 15) when
-// one workgroup made an image's passes.  Where every image is solved before,
-// the kernel costs its launch (200 images: within the noise of 1.5 ms).
-enum NoisePass { NZ_DIGIT, NZ_DEV_DIGIT, NZ_COUNT, NZ_CHANGED };
+// many.  Against a launch per pass over every image (26 reads and up to 110
+// launches, an image the plan holds among them): 2048^2 FP32 pixels, half of
+// them 10^6 times narrower than the others (five steps): one image 1.09 ms ->
+// 0.77, 16 images 3.2 -> 2.65, 100 images 19.8 -> 12.0; two far groups (one
+// step) 1.36, 3.1 and 15.4 -> 0.37, 1.43 and 8.6; log-normal values (ten steps)
+// 1.85, 5.8 and 36.6 -> 1.72, 4.7 and 28.0.  (With a pass of its own for the
+// size of a set and no list, eleven passes a step: 1.54, 5.2 and 24.3 in the
+// first; with every workgroup calling at every image in turn 64 images of 512^2
+// in two groups took 1.57 ms instead of 0.55.)  Where every image is solved
+// before, the kernel costs its launch (200 images: within the noise of 1.5 ms).
+enum NoisePass { NZ_DIGIT, NZ_DEV_DIGIT, NZ_KEYS, NZ_DEV_KEYS, NZ_CLIP };
 struct NoiseTask {
   double m, thr, mn, tn;  // the set |x - m| <= thr; center of the deviations; the next set
   uint64_t pre[2];        // digits found above bit `hi`
@@ -913,41 +925,79 @@ __device__ __forceinline__ int noise_take(NoiseImage& S, int pieces, int r, uint
 }
 
 constexpr int NZ_DIGITS = 2048;
+constexpr int NZ_CHANGED = NZ_DIGITS;  // clip: the pixels in one of the two sets only, after the digits
+constexpr int NZ_MOST_KEYS = NZ_LIST / 2;
 static_assert(2 * NZ_DIGITS * 2 <= NZ_BINS, "64-bit sums in the histogram's place");
 typedef unsigned long long NoiseSum;
 __device__ __forceinline__ NoiseSum* noise_sums(NoiseImage& S) { return reinterpret_cast<NoiseSum*>(S.hist); }
 
-// One piece (fewer than 2^32 pixels): its histogram (or count) added to the image's.
+__device__ __forceinline__ int noise_bins(const NoiseTask& t) {  // of them, in use by a pass
+  return t.pass == NZ_CLIP ? NZ_CHANGED + 1
+         : t.pass == NZ_KEYS || t.pass == NZ_DEV_KEYS ? 0 : t.pre[0] != t.pre[1] ? 2 * NZ_DIGITS : NZ_DIGITS;
+}
+
+// One piece (fewer than 2^32 pixels): its histogram added to the image's, or
+// its keys to the list.
 template <typename T>
 __device__ __forceinline__ void noise_piece(const void* img, int64_t n, int piece, int pieces, NoiseImage& S,
-                                            const NoiseTask& t, uint32_t* h, uint32_t* tmp) {
+                                            const NoiseTask& t, uint32_t* h, uint32_t* tmp, uint32_t* cnt) {
   const double m = t.m, thr = t.thr, mn = t.mn, tn = t.tn;
-  if (t.pass >= NZ_COUNT) {
-    const bool changed = t.pass == NZ_CHANGED;  // pixels in one of the two sets only
-    uint32_t c = 0, total;
-    for_pixels<T, 2>(img, n, piece, pieces, [&](float x) {
-      if (!__builtin_isfinite(x)) return;
-      const bool in = fabs((double)x - m) <= thr;
-      c += (changed ? in != (fabs((double)x - mn) <= tn) : in) ? 1u : 0u;
-    });
-    (void)block_scan(c, tmp, &total);
-    if (threadIdx.x == 0 && total) atomicAdd(&noise_sums(S)[0], (NoiseSum)total);
-  } else {
-    const bool dev = t.pass == NZ_DEV_DIGIT, two = t.pre[0] != t.pre[1];
-    const int hi = t.hi, lo = t.lo;
-    const uint32_t mask = (1u << (hi - lo)) - 1u;
-    const uint64_t p0 = t.pre[0] >> hi, p1 = t.pre[1] >> hi;
-    for (int b = threadIdx.x; b < 2 * NZ_DIGITS; b += NZ_TX) h[b] = 0u;
+  const bool two = t.pre[0] != t.pre[1], dev = t.pass == NZ_DEV_DIGIT || t.pass == NZ_DEV_KEYS;
+  const int hi = t.hi, lo = t.lo;
+  const uint64_t p0 = t.pre[0] >> hi, p1 = t.pre[1] >> hi;
+  auto key_of = [&](float x) {
+    return dev ? (uint64_t)__double_as_longlong(fabs((double)x - mn)) : (uint64_t)fkey(x);
+  };
+  if (t.pass == NZ_KEYS || t.pass == NZ_DEV_KEYS) {
+    uint64_t* stage = reinterpret_cast<uint64_t*>(h);
+    uint64_t* list = reinterpret_cast<uint64_t*>(S.list);
+    if (threadIdx.x == 0) *cnt = 0u;
     __syncthreads();
     for_pixels<T, 2>(img, n, piece, pieces, [&](float x) {
       if (!(__builtin_isfinite(x) && fabs((double)x - m) <= thr)) return;
-      const uint64_t key = dev ? (uint64_t)__double_as_longlong(fabs((double)x - mn)) : (uint64_t)fkey(x);
-      const uint32_t d = (uint32_t)(key >> lo) & mask;
-      if (key >> hi == p0) atomicAdd(&h[d], 1u);
-      if (two && key >> hi == p1) atomicAdd(&h[NZ_DIGITS + d], 1u);
+      const uint64_t key = key_of(x);
+      if (key >> hi != p0 && !(two && key >> hi == p1)) return;
+      const uint32_t i = atomicAdd(cnt, 1u);
+      if (i < (uint32_t)NZ_DIGITS) {
+        stage[i] = key;
+      } else {  // staging full: append directly
+        const uint32_t g = atomicAdd(&S.n_list, 1u);
+        if (g < (uint32_t)NZ_MOST_KEYS) shared_set(list + g, key);
+      }
     });
     __syncthreads();
-    for (int b = threadIdx.x; b < 2 * NZ_DIGITS; b += NZ_TX)
+    const uint32_t c = min(*cnt, (uint32_t)NZ_DIGITS);
+    if (threadIdx.x == 0) tmp[0] = c ? atomicAdd(&S.n_list, c) : 0u;
+    __syncthreads();
+    const uint32_t base = tmp[0];
+    for (uint32_t i = threadIdx.x; i < c; i += NZ_TX)
+      if (base + i < (uint32_t)NZ_MOST_KEYS) shared_set(list + base + i, stage[i]);
+  } else {
+    const int bins = two ? 2 * NZ_DIGITS : NZ_DIGITS;
+    for (int b = threadIdx.x; b < bins; b += NZ_TX) h[b] = 0u;
+    __syncthreads();
+    if (t.pass == NZ_CLIP) {
+      uint32_t c = 0, total;
+      for_pixels<T, 2>(img, n, piece, pieces, [&](float x) {
+        if (!__builtin_isfinite(x)) return;
+        const bool in = fabs((double)x - mn) <= tn;
+        c += in != (fabs((double)x - m) <= thr) ? 1u : 0u;
+        if (in) atomicAdd(&h[fkey(x) >> 21], 1u);
+      });
+      (void)block_scan(c, tmp, &total);
+      if (threadIdx.x == 0 && total) atomicAdd(&noise_sums(S)[NZ_CHANGED], (NoiseSum)total);
+    } else {
+      const uint32_t mask = (1u << (hi - lo)) - 1u;
+      for_pixels<T, 2>(img, n, piece, pieces, [&](float x) {
+        if (!(__builtin_isfinite(x) && fabs((double)x - m) <= thr)) return;
+        const uint64_t key = key_of(x);
+        const uint32_t d = (uint32_t)(key >> lo) & mask;
+        if (key >> hi == p0) atomicAdd(&h[d], 1u);
+        if (two && key >> hi == p1) atomicAdd(&h[NZ_DIGITS + d], 1u);
+      });
+    }
+    __syncthreads();
+    for (int b = threadIdx.x; b < bins; b += NZ_TX)
       if (h[b]) atomicAdd(&noise_sums(S)[b], (NoiseSum)h[b]);
   }
   settle();
@@ -955,126 +1005,234 @@ __device__ __forceinline__ void noise_piece(const void* img, int64_t n, int piec
   if (threadIdx.x == 0) __hip_atomic_fetch_add(&S.done, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
+// Where the leader of an image stands (in LDS, so that nothing of it is live
+// through the pixels of a pass): the pass that was published, and the
+// selection it belongs to.
+struct NoiseLead {
+  NoiseTask task;
+  int64_t n, rank[2], left;  // size of the set; ranks among the keys with the digits found; those keys
+  double sigma;
+  uint32_t seq;  // passes so far
+  int iter, dev;  // steps so far; the selection is of deviations
+};
+
+// The pass in L.task, open for all workgroups: its sums and keys cleared.
+__device__ __forceinline__ void noise_publish(NoiseImage& S, NoiseLead& L) {
+  const int tid = threadIdx.x;
+  for (int b = tid; b < noise_bins(L.task); b += NZ_TX)
+    __hip_atomic_store(&noise_sums(S)[b], (NoiseSum)0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  settle();
+  __syncthreads();
+  if (tid == 0) {
+    const NoiseTask& t = L.task;
+    shared_set(&S.task[0], (uint64_t)__double_as_longlong(t.m));
+    shared_set(&S.task[1], (uint64_t)__double_as_longlong(t.thr));
+    shared_set(&S.task[2], (uint64_t)__double_as_longlong(t.mn));
+    shared_set(&S.task[3], (uint64_t)__double_as_longlong(t.tn));
+    shared_set(&S.task[4], t.pre[0]);
+    shared_set(&S.task[5], t.pre[1]);
+    shared_set(&S.task[6], (uint64_t)(t.pass | t.hi << 8 | t.lo << 16));
+    __hip_atomic_store(&S.n_list, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    __hip_atomic_store(&S.done, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    settle();
+    __hip_atomic_store(&S.call, ++L.seq, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  }
+}
+
+// Reads the sums of the pass that has ended and sets the next one; false when
+// the result is final.
+__device__ __forceinline__ bool noise_advance(NoiseImage& S, NoiseLead& L, NoiseSum* sums, NoiseSum* tmp, uint64_t* sh,
+                                              double kappa, int max_iter) {
+  const int tid = threadIdx.x;
+  NoiseTask t = L.task;
+  int64_t n = L.n, rank0 = L.rank[0], rank1 = L.rank[1], left = L.left;
+  double sigma = L.sigma;
+  int iter = L.iter, dev = L.dev;
+  bool more = true;
+  for (int b = tid; b < noise_bins(t); b += NZ_TX)
+    sums[b] = __hip_atomic_load(&noise_sums(S)[b], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  __syncthreads();  // (L is read, too)
+  // the digit (at bit lo) that holds the rank among the keys H counts; the keys that have it
+  auto digit = [&](const NoiseSum* H, int lo, uint64_t& pre, int64_t& rank) {
+    const NoiseSum c0 = H[2 * tid], c1 = H[2 * tid + 1];
+    NoiseSum total;
+    const NoiseSum e = block_scan(c0 + c1, tmp, &total);
+    const NoiseSum r = (NoiseSum)rank;
+    if (r >= e && r < e + c0 + c1) {
+      const bool second = r >= e + c0;
+      sh[0] = (uint64_t)(2 * tid + (second ? 1 : 0));
+      sh[1] = e + (second ? c0 : 0);
+      sh[2] = second ? c1 : c0;
+    }
+    __syncthreads();
+    pre |= sh[0] << lo;
+    rank -= (int64_t)sh[1];
+    const int64_t c = (int64_t)sh[2];
+    __syncthreads();
+    return c;
+  };
+  auto digits = [&](int lo) {
+    const bool two = t.pre[0] != t.pre[1];
+    const int64_t c0 = digit(sums, lo, t.pre[0], rank0);
+    const int64_t c1 = digit(two ? sums + NZ_DIGITS : sums, lo, t.pre[1], rank1);
+    left = t.pre[0] != t.pre[1] ? c0 + c1 : c0;
+    t.hi = lo;
+  };
+  auto begin = [&](int bits) {
+    t.pre[0] = t.pre[1] = 0;
+    rank0 = (n - 1) / 2;
+    rank1 = n / 2;
+    left = n;
+    t.hi = bits;
+  };
+  if (t.pass == NZ_CLIP) {
+    const bool changed = sums[NZ_CHANGED] != 0;
+    NoiseSum total;
+    (void)block_scan(sums[2 * tid] + sums[2 * tid + 1], tmp, &total);
+    n = (int64_t)total;
+    t.m = t.mn;
+    t.thr = t.tn;
+    more = n > 0 && (iter == 0 || (changed && iter < max_iter));
+    begin(32);
+    dev = 0;
+    if (more) digits(21);  // the clip's digits are the first ones of the values
+  } else if (t.pass == NZ_DIGIT || t.pass == NZ_DEV_DIGIT) {
+    digits(t.lo);
+  } else {
+    // the rest of the digits among the listed keys
+    const uint64_t* list = reinterpret_cast<const uint64_t*>(S.list);
+    const int n_keys = (int)left;
+    while (t.hi > 0) {
+      const int lo = max(t.hi - 11, 0);
+      const bool two = t.pre[0] != t.pre[1];
+      for (int b = tid; b < 2 * NZ_DIGITS; b += NZ_TX) sums[b] = 0;
+      __syncthreads();
+      for (int i = tid; i < n_keys; i += NZ_TX) {
+        const uint64_t key = shared_get(list + i);
+        const uint32_t d = (uint32_t)(key >> lo) & ((1u << (t.hi - lo)) - 1u);
+        if (key >> t.hi == t.pre[0] >> t.hi) atomicAdd(&sums[d], (NoiseSum)1);
+        if (two && key >> t.hi == t.pre[1] >> t.hi) atomicAdd(&sums[NZ_DIGITS + d], (NoiseSum)1);
+      }
+      __syncthreads();
+      digits(lo);
+    }
+  }
+  if (more && t.hi == 0) {  // both middle values
+    if (!dev) {
+      t.mn = 0.5 * ((double)fkey_value((uint32_t)t.pre[0]) + (double)fkey_value((uint32_t)t.pre[1]));
+      begin(63);
+      dev = 1;
+    } else {
+      sigma = 1.4826 *
+              (0.5 * (__longlong_as_double((long long)t.pre[0]) + __longlong_as_double((long long)t.pre[1])));
+      t.tn = kappa * sigma;
+      iter++;
+      t.pre[0] = t.pre[1] = 0;
+    }
+  }
+  if (t.hi == 0) {
+    t.pass = NZ_CLIP;
+  } else {
+    t.pass = left <= NZ_MOST_KEYS ? (dev ? NZ_DEV_KEYS : NZ_KEYS) : (dev ? NZ_DEV_DIGIT : NZ_DIGIT);
+    t.lo = max(t.hi - 11, 0);
+  }
+  if (tid == 0) {
+    L.task = t;
+    if (more) L.n = n;  // (what a last clip finds is not a set that was used)
+    L.rank[0] = rank0;
+    L.rank[1] = rank1;
+    L.left = left;
+    L.sigma = sigma;
+    L.iter = iter;
+    L.dev = dev;
+  }
+  __syncthreads();
+  return more;
+}
+
+// Pieces of a pass over an image of n pixels: one for each workgroup that an
+// image gets (a piece costs its histogram of up to 4096 words), of 16 pixels a
+// thread or more and of fewer than 2^32 pixels (memory ends before the most
+// pieces of that size).
+__device__ __forceinline__ int noise_pieces(int64_t n, uint32_t n_todo) {
+  const int64_t most = std::min<uint32_t>(NZ_PIECES, std::max<uint32_t>(8u, gridDim.x / n_todo));
+  return (int)std::min<int64_t>(std::max<int64_t>(most, std::min<int64_t>(NZ_PIECES, (n >> 31) + 1)),
+                                (n + NZ_TX * 16 - 1) / (NZ_TX * 16));
+}
+
 template <typename T>
 __global__ __launch_bounds__(NZ_TX) void k_noise_pixels(const void* const* imgs, const int64_t* npix, NoiseImage* st,
                                                         double kappa, int max_iter, int n_img, double* sigma,
                                                         int64_t* n_used, int32_t* iters, ExpMeta* meta) {
-  __shared__ uint32_t h[2 * NZ_DIGITS];
+  __shared__ alignas(8) uint32_t h[2 * NZ_DIGITS];
   __shared__ NoiseSum sums[2 * NZ_DIGITS];
   __shared__ uint32_t tmp[NZ_WAVES];
   __shared__ NoiseSum tmp_sum[NZ_WAVES];
-  __shared__ uint64_t sh[2];
+  __shared__ uint64_t sh[3];
   __shared__ NoiseTask task;
-  __shared__ uint32_t sh_i[3];
+  __shared__ NoiseLead L;
+  __shared__ uint32_t sh_i[3], sh_n;
   const int tid = threadIdx.x;
   const uint32_t n_todo = st[0].n_todo;
   if (n_todo == 0u) return;
-  // pieces: two for each workgroup that an image gets (a piece costs its histogram of 4096 words)
-  const int most = (int)std::min<uint32_t>(NZ_PIECES, std::max<uint32_t>(16u, 2u * gridDim.x / n_todo));
-  for (int v = 0; v < n_img; ++v) {
-    const int img = (int)(((int64_t)blockIdx.x + v) % n_img);
+  for (;;) {
+    // the next image, from this workgroup's own one on, that is not done and has fewer workgroups than pieces (all
+    // images are looked at together: one after another took 2 us each)
+    if (tid == 0) sh_n = ~0u;
+    __syncthreads();
+    for (int v = tid; v < n_img; v += NZ_TX) {
+      const int i = (int)(((int64_t)blockIdx.x + v) % n_img);
+      NoiseImage& S = st[i];
+      if (S.todo && shared_get(&S.role) < (uint32_t)noise_pieces(npix[i], n_todo) && shared_get(&S.call) != ~0u)
+        atomicMin(&sh_n, (uint32_t)v);
+    }
+    __syncthreads();
+    if (sh_n == ~0u) return;
+    const int img = (int)(((int64_t)blockIdx.x + sh_n) % n_img);
     NoiseImage& S = st[img];
-    if (!S.todo) continue;
-    const void* p = imgs[img];
     const int64_t n_pix = npix[img];
-    // (of fewer than 2^32 pixels each: memory ends before the most pieces of that size)
-    const int pieces = (int)std::min<int64_t>(std::max<int64_t>(most, std::min<int64_t>(NZ_PIECES, (n_pix >> 31) + 1)),
-                                              (n_pix + NZ_TX * 16 - 1) / (NZ_TX * 16));
-    __syncthreads();  // sh_i is read
+    const int pieces = noise_pieces(n_pix, n_todo);
     if (tid == 0) sh_i[0] = __hip_atomic_fetch_add(&S.role, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     __syncthreads();
     const int role = (int)sh_i[0];
-    uint32_t last = 0;
-    if (role > 0) {
-      if (role >= pieces) continue;
-      for (int i; (i = noise_take(S, pieces, role, last, &task, sh_i)) >= 0;)
-        noise_piece<T>(p, n_pix, i, pieces, S, task, h, tmp);
-      continue;
-    }
-    uint32_t seq = 0;
-    // one pass with the workgroups that are here; its sums are in `sums` afterwards
-    double m = 0.0, thr = __builtin_inf(), mn = 0.0, tn = 0.0;
-    auto run = [&](NoisePass pass, int hi, int lo, uint64_t pre0, uint64_t pre1) {
-      for (int b = tid; b < 2 * NZ_DIGITS; b += NZ_TX)
-        __hip_atomic_store(&noise_sums(S)[b], (NoiseSum)0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-      settle();
-      __syncthreads();
-      ++seq;
+    if (role >= pieces) continue;  // others came first
+    if (role == 0) {
       if (tid == 0) {
-        shared_set(&S.task[0], (uint64_t)__double_as_longlong(m));
-        shared_set(&S.task[1], (uint64_t)__double_as_longlong(thr));
-        shared_set(&S.task[2], (uint64_t)__double_as_longlong(mn));
-        shared_set(&S.task[3], (uint64_t)__double_as_longlong(tn));
-        shared_set(&S.task[4], pre0);
-        shared_set(&S.task[5], pre1);
-        shared_set(&S.task[6], (uint64_t)(pass | hi << 8 | lo << 16));
-        __hip_atomic_store(&S.done, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        settle();
-        __hip_atomic_store(&S.call, seq, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        L.task = NoiseTask{0.0, __builtin_inf(), 0.0, __builtin_inf(), {0, 0}, NZ_CLIP, 0, 0};
+        L.n = 0;
+        L.sigma = __builtin_nan("");
+        L.seq = 0;
+        L.iter = L.dev = 0;
       }
-      for (int i; (i = noise_take(S, pieces, 0, last, &task, sh_i)) >= 0;)
-        noise_piece<T>(p, n_pix, i, pieces, S, task, h, tmp);
+      __syncthreads();
+      noise_publish(S, L);
+    }
+    uint32_t last = 0;
+    for (;;) {
+      const int i = noise_take(S, pieces, role, last, &task, sh_i);
+      if (i >= 0) {
+        noise_piece<T>(imgs[img], n_pix, i, pieces, S, task, h, tmp, &sh_n);
+        continue;
+      }
+      if (role > 0) break;
       if (tid == 0)
         while (__hip_atomic_load(&S.done, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) < (uint32_t)pieces)
           __builtin_amdgcn_s_sleep(2);
       settle();
       __syncthreads();
-      for (int b = tid; b < 2 * NZ_DIGITS; b += NZ_TX)
-        sums[b] = __hip_atomic_load(&noise_sums(S)[b], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-      __syncthreads();
-    };
-    auto count = [&](NoisePass pass) {
-      run(pass, 0, 0, 0, 0);
-      return (int64_t)sums[0];
-    };
-    // mean of the two middle values of the set: of x, or of |x - mn|
-    auto middle = [&](int64_t n, bool dev) {
-      uint64_t pre0 = 0, pre1 = 0;
-      int64_t rank0 = (n - 1) / 2, rank1 = n / 2;
-      for (int hi = dev ? 63 : 32; hi > 0;) {
-        const int lo = max(hi - 11, 0);
-        const bool two = pre0 != pre1;
-        run(dev ? NZ_DEV_DIGIT : NZ_DIGIT, hi, lo, pre0, pre1);
-        auto digit = [&](const NoiseSum* H, uint64_t& pre, int64_t& rank) {
-          const NoiseSum c0 = H[2 * tid], c1 = H[2 * tid + 1];
-          NoiseSum total;
-          const NoiseSum e = block_scan(c0 + c1, tmp_sum, &total);
-          const NoiseSum r = (NoiseSum)rank;
-          if (r >= e && r < e + c0 + c1) {
-            const bool second = r >= e + c0;
-            sh[0] = (uint64_t)(2 * tid + (second ? 1 : 0));
-            sh[1] = e + (second ? c0 : 0);
-          }
-          __syncthreads();
-          pre |= sh[0] << lo;
-          rank -= (int64_t)sh[1];
-          __syncthreads();
-        };
-        digit(sums, pre0, rank0);
-        digit(two ? sums + NZ_DIGITS : sums, pre1, rank1);
-        hi = lo;
+      if (noise_advance(S, L, sums, tmp_sum, sh, kappa, max_iter)) {
+        noise_publish(S, L);
+        continue;
       }
-      if (dev) return 0.5 * (__longlong_as_double((long long)pre0) + __longlong_as_double((long long)pre1));
-      return 0.5 * ((double)fkey_value((uint32_t)pre0) + (double)fkey_value((uint32_t)pre1));
-    };
-    NoiseResult R{__builtin_nan(""), 0, 0};
-    int64_t n = count(NZ_COUNT);
-    while (n > 0) {
-      mn = middle(n, false);
-      R.sigma = 1.4826 * middle(n, true);
-      R.used = n;
-      R.iter++;
-      tn = kappa * R.sigma;
-      const bool changed = count(NZ_CHANGED) != 0;
-      m = mn;
-      thr = tn;
-      if (!changed || R.iter >= max_iter) break;
-      n = count(NZ_COUNT);
+      if (tid == 0) __hip_atomic_store(&S.call, ~0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      noise_result(NoiseResult{L.sigma, L.n, L.iter}, img, n_img, sigma, n_used, iters, meta);
+      break;
     }
-    if (tid == 0) __hip_atomic_store(&S.call, ~0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    noise_result(R, img, n_img, sigma, n_used, iters, meta);
+    __syncthreads();  // L and sh_n are read
   }
 }
+
+size_t noise_pixels_offset() { return offsetof(NoiseImage, n_todo); }
 
 size_t noise_scratch_bytes(int n_img) { return sizeof(NoiseImage) * (size_t)n_img; }
 
