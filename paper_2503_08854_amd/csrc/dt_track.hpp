@@ -20,10 +20,16 @@
 // (ExpMeta: two linear inequalities), widened by m, then either proves the
 // sample cannot land or queues it.  Prediction and test run in FP32, m widened
 // by what their roundings can add, so that they drop no more than the exact
-// walk does; everything that reaches a result is FP64 as before.  10^7 orbits x
-// 200 survey exposures: 4.37 -> 3.81 ms from an FP64 prediction and a test
-// against the cone around the image (half as many vector cycles per sample, and
-// the rectangle queues two thirds of what the cone does).
+// walk does; everything that reaches a result is FP64 as before.  5 x 10^6
+// orbits x 200 survey exposures: 2.00 ms with an FP64 prediction and a test
+// against the cone around the image, 2.02 with this rectangle in FP64, 1.70 in
+// FP32 (as many vector instructions, which issue at one rate, but half the
+// registers and half the record: 32 instead of 58 scalar registers spilled, and
+// less waiting).  What rounding is allowed for matters to objects a few
+// hundredths of an AU away: 4 x 10^5 of them on five 64^2 images within a
+// hundredth of a day queue 4986 samples for the 1995 that land (89 184 when
+// 2^-18 of all sizes was allowed for), and 3 x 10^6 on 100 images of 1024^2 over
+// ten days take 1.49 ms as with the FP64 cone (1.72).
 // Queued samples are solved exactly, as the per-sample walk solves them
 // (Kepler from the checkpoint state, light time to LT_LINEAR_MAX, projection,
 // nearest pixel), by whichever lanes are free, 64 at a time, and each orbit
@@ -326,24 +332,29 @@ __device__ __forceinline__ void track_walk(const StackArgs& A, const Orbit& o, c
         n_ck++;
         D = 0.f;
       }
-      // what FP32 adds, as a displacement of the exact position: each of the
-      // ~24 roundings on the way to |X.p| - kx Z.p is at most 2^-24 of the sum
-      // of the sizes that enter, up to CK_SPAN days on; 64 of them.  A state
-      // too large for FP32 is zeroed and never pruned.
-      {
-        constexpr float T = (float)CK_SPAN;
-        const float size = fabsf(r0) + fabsf(r1) + fabsf(r2) + T * (fabsf(v0) + fabsf(v1) + fabsf(v2)) +
-                           T * T * (fabsf(h0) + fabsf(h1) + fabsf(h2)) + fabsf(y.fo[0]) + fabsf(y.fo[1]) +
-                           fabsf(y.fo[2]) + T * (float)A.vobs;
-        s1 = fmaf(size, 0x1p-18f, s0);
-        if (!(size < 1e15f)) {
-          r0 = r1 = r2 = v0 = v1 = v2 = h0 = h1 = h2 = 0.f;
-          s1 = s0 < 0.f ? s0 : __builtin_inff();
-        }
-      }
       p0 = fmaf(fmaf(h0, D, v0), D, r0) - y.fo[0];
       p1 = fmaf(fmaf(h1, D, v1), D, r1) - y.fo[1];
       p2 = fmaf(fmaf(h2, D, v2), D, r2) - y.fo[2];
+      // What FP32 adds, as a displacement of the exact position, in units of
+      // 2^-24.  State, D and observer as FP32, the two fused multiply-adds and
+      // the difference: at most 2 |r| + 4 |v D| + 7 |h D^2| + |o| + |p|; the
+      // two sides of the test (a vector of length <= 1 and its dot product, a
+      // half size, the sum with m): 6 |p| more.  |o| and |p| move by at most
+      // T vobs and T (|v| + vobs) + T^2 |h| until the next checkpoint.  Twice
+      // that, with the norms as sums of sizes, also holds the rounding of this
+      // estimate.  A state too large for FP32 is zeroed and never pruned.
+      {
+        constexpr float T = (float)CK_SPAN;
+        const float mv = T * (fabsf(v0) + fabsf(v1) + fabsf(v2)) + T * T * (fabsf(h0) + fabsf(h1) + fabsf(h2));
+        const float size = 2.f * (fabsf(r0) + fabsf(r1) + fabsf(r2)) + fabsf(y.fo[0]) + fabsf(y.fo[1]) +
+                           fabsf(y.fo[2]) + 7.f * (fabsf(p0) + fabsf(p1) + fabsf(p2)) + 13.f * mv +
+                           8.f * T * (float)A.vobs;
+        s1 = fmaf(size, 0x1p-23f, s0);
+        if (!(size < 1e15f)) {
+          r0 = r1 = r2 = v0 = v1 = v2 = h0 = h1 = h2 = p0 = p1 = p2 = 0.f;
+          s1 = s0 < 0.f ? s0 : __builtin_inff();
+        }
+      }
       // the test again too: nothing of the first read stays live across the solves
       X0 = y.fX[0];
       X1 = y.fX[1];
