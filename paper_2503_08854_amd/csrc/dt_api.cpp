@@ -118,6 +118,7 @@ StackArgs stack_args(const dt_patch* p, const dt_orbits* o) {
   a.nvalid = nullptr;
   a.vobs = p->vobs;
   a.work = p->ctx->count_work ? p->ctx->d_work : nullptr;
+  a.plane_bytes = (int64_t)(sizeof(float2) * p->plane_elems);
   return a;
 }
 

@@ -4,6 +4,8 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include <type_traits>
+
 #include "dtrack.h"
 
 namespace dtk {
@@ -135,7 +137,41 @@ struct StackArgs {
   // deferred-walk kernel then stacks those orbits per sample.
   int64_t* defer_list = nullptr;
   unsigned int* defer_count = nullptr;
+  int64_t plane_bytes = 0;  // of all planes (the launch's choice of where wavefronts defer)
 };
+
+// 1 / stack_switch(a): the share of its samples queued above which a wavefront
+// of a launch that allows it defers.  The queue saves the arithmetic of samples
+// that miss, but its gathers are waited for, which the per-sample walk's are
+// not, so the larger the planes (the further beyond the 256 MiB Infinity Cache),
+// the sooner a wavefront gives up.  Measured at 1/4, 1/5, 1/6, 1/7 and, last,
+// with the FP64 cone at 1/5, whose queue is up to half as large again (ms;
+// 2 x 10^6 to 10^7 orbits):
+//   0.13 GB 0.05 AU away 0.75 0.86 0.84 0.87   0.78
+//   0.25 GB main belt    0.35 0.45 0.80 0.80   0.79
+//   0.25 GB near Earth   0.37 0.39 0.70 0.80   0.64
+//   0.84 GB 0.05 AU away 1.47 1.50 1.68 1.75   1.49
+//   0.84 GB 0.015 AU     1.90 1.61 1.52 1.49   1.63
+//   1.0 GB distant       2.67 2.49 2.37 2.36   2.41
+//   2.0 GB main belt     0.60 0.65 0.65 0.88   0.81
+//   2.0 GB near Earth    0.62 0.66 0.68 0.94   0.75
+//   4.0 GB distant       3.18 4.06 4.06 3.69   3.70
+//   16 GB main belt      2.39 2.18 2.06 1.98   2.05
+//   53 GB distant        44.0 36.4 33.3 32.2   32.2
+constexpr int64_t SWITCH_TINY = 256ll << 20, SWITCH_SMALL = 1000000000, SWITCH_LARGE = 3000000000;  // bytes of planes
+inline int stack_switch(const StackArgs& a) {
+  return a.plane_bytes < SWITCH_TINY ? 4 : a.plane_bytes < SWITCH_SMALL ? 5 : a.plane_bytes < SWITCH_LARGE ? 6 : 7;
+}
+// f(std::integral_constant<int, stack_switch(a)>): picks a kernel instance.
+template <typename F>
+inline void with_switch(const StackArgs& a, F&& f) {
+  switch (stack_switch(a)) {
+    case 4: f(std::integral_constant<int, 4>{}); break;
+    case 5: f(std::integral_constant<int, 5>{}); break;
+    case 6: f(std::integral_constant<int, 6>{}); break;
+    default: f(std::integral_constant<int, 7>{}); break;
+  }
+}
 
 // Work counters (one slot; see dt_ctx_count_work): samples tested by
 // prediction, queued exact solves, checkpoint solves, samples walked by the

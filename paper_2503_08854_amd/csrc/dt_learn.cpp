@@ -111,6 +111,7 @@ dt_status dt_stack_generated(dt_patch* p, const dt_orbit_sampler* S, int64_t fir
   a.epoch = S->epoch;
   a.vobs = p->vobs;
   a.work = p->ctx->count_work ? p->ctx->d_work : nullptr;
+  a.plane_bytes = (int64_t)(sizeof(float2) * p->plane_elems);
   a.snr = d_snr;
   a.flux = d_flux;
   a.nvalid = d_nvalid;

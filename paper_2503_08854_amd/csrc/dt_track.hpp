@@ -37,8 +37,8 @@
 // per-sample walk.
 //
 // The prediction pays while most samples miss.  A wavefront whose orbits land
-// often (more than 1 / TRACK_SWITCH_DEN of its lane-exposures queued, once
-// TRACK_SWITCH_MIN exposures are tested or its queue is full, e.g. distant
+// often (more than 1 / DEN of its lane-exposures queued, DEN from stack_switch,
+// once TRACK_SWITCH_MIN exposures are tested or its queue is full, e.g. distant
 // objects the field follows for months) gives its orbits up when the launch
 // allows it:
 // it appends its first orbit index to the deferral list and writes nothing;
@@ -54,22 +54,15 @@ constexpr float PRED_SLACK = 1e-9f;  // AU: rounding of the checkpoint state and
 constexpr int TQ_CAP = 128;          // queued samples per wavefront (< 64 held + 64 pushed)
 constexpr int TQ_LIST = 8;           // queued samples per lane between flushes
 constexpr int CK_ANCHOR = 8;         // checkpoints between full sincos re-anchors of sin E, cos E
-constexpr int TRACK_SWITCH_DEN = 6;  // a wavefront defers above 1/6 of its lane-exposures queued
 constexpr int TRACK_SWITCH_MIN = 3;  // exposures tested before the fraction is trusted
 
-// Where wavefronts give up, measured at 2/7, 1/5, 1/6 and 1/8: a generated search
-// on small planes where a tenth of the samples lands takes 1.20, 1.33, 1.35
-// and 1.40 ms (the queue saves the samples that miss); the stack of 10^7
-// distant orbits on 400 4096^2 images, where a third lands, 45.2, 33.4, 32.0
-// and 32.0 ms (the queue's gathers are waited for, the per-sample walk's are
-// not, and there they replay in 31.8).
-
-// More than 1 / TRACK_SWITCH_DEN of the 64 n_tested lane-exposures queued:
-// for an integer count, q > 64 n / d exactly when q > floor(64 n / d).  Plain
-// 32-bit arithmetic on wave-uniform counts, so scalar instructions only (the
-// walk runs with fewer than 2^25 exposures, so 64 n_tested < 2^31).
+// More than 1 / DEN of the 64 n_tested lane-exposures queued: for an integer
+// count, q > 64 n / d exactly when q > floor(64 n / d).  Plain 32-bit
+// arithmetic on wave-uniform counts, so scalar instructions only (the walk
+// runs with fewer than 2^25 exposures, so 64 n_tested < 2^31).
+template <int DEN>
 __device__ __forceinline__ bool over_switch(int queued, int n_tested) {
-  return queued > (int)(((unsigned)n_tested << 6) / (unsigned)TRACK_SWITCH_DEN);
+  return queued > (int)(((unsigned)n_tested << 6) / (unsigned)DEN);
 }
 
 // One wavefront's state in LDS: the queue, and each lane's prepared orbit and
@@ -119,12 +112,12 @@ __device__ __forceinline__ void track_bound(double a, double e, const Orbit& o, 
 // meaningless), see the file comment.
 //
 // REC (debug kernels only): every sample the walk solves exactly is written
-// to row rowbase + lane of dbg (the owner's row for queued samples).  DEFER
-// false compiles the deferral out (launches that never defer).  TCV keeps the
+// to row rowbase + lane of dbg (the owner's row for queued samples).  DEN
+// 0 compiles the deferral out (launches that never defer).  TCV keeps the
 // checkpoint epoch in a vector register, so that D = t - tc is one
 // instruction per exposure rather than a copy and a subtraction (~1 % on the
 // stacks that fit it without spilling; the cell and id-list kernels do not).
-template <bool REC = false, bool DEFER = true, bool TCV = false>
+template <bool REC = false, int DEN = 0, bool TCV = false>
 __device__ __forceinline__ void track_walk(const StackArgs& A, const Orbit& o, const TrackBound& bd, bool live,
                                            TrackQueue& Qm, StackPart& P, bool& deferred,
                                            const DebugArgs* dbg = nullptr, int64_t rowbase = 0) {
@@ -169,7 +162,7 @@ __device__ __forceinline__ void track_walk(const StackArgs& A, const Orbit& o, c
   int ex = 0;
   int n_tested = 0;  // exposures tested by prediction (wave-uniform)
   bool tail = false; // give the orbits up for the per-sample walk
-  const bool may_defer = DEFER && A.defer_list != nullptr;
+  const bool may_defer = DEN > 0 && A.defer_list != nullptr;
 
   for (;; ++ex) {
     // the step after the last exposure only serves the queue; the record
@@ -191,9 +184,9 @@ __device__ __forceinline__ void track_walk(const StackArgs& A, const Orbit& o, c
       const bool ck = ex >= ck_at;
       const bool fl = count > 0;
       // a wavefront due to serve its queue whose queued fraction is already
-      // above 1 / TRACK_SWITCH_DEN defers now rather than solve samples the
+      // above 1 / DEN defers now rather than solve samples the
       // per-sample walk repeats
-      tail = may_defer && fl && !last && over_switch(queued + count, n_tested);
+      tail = may_defer && fl && !last && over_switch<DEN ? DEN : 1>(queued + count, n_tested);
       if (tail) break;
       const int nb = fl ? (count + 63) >> 6 : 0;
       float tg_ck = 0.f;  // a Newton start only
@@ -397,7 +390,7 @@ __device__ __forceinline__ void track_walk(const StackArgs& A, const Orbit& o, c
       // (nothing queued is served).  A queue that fills before
       // TRACK_SWITCH_MIN exposures decides at once, rather than serving
       // solves the per-sample walk would repeat.
-      tail = may_defer && (n_tested >= TRACK_SWITCH_MIN || full) && over_switch(queued + count, n_tested);
+      tail = may_defer && (n_tested >= TRACK_SWITCH_MIN || full) && over_switch<DEN ? DEN : 1>(queued + count, n_tested);
       if (tail) break;
     }
   }
@@ -418,7 +411,7 @@ __device__ __forceinline__ void track_walk(const StackArgs& A, const Orbit& o, c
 // per-sample stack (NaN, NaN, -1 for an orbit that is not live), or nothing
 // when the wavefront deferred its orbits (returns true).  All 64 lanes of the
 // wavefront call it together; Q is the wavefront's LDS queue.
-template <bool REC = false, bool DEFER = true, bool TCV = false>
+template <bool REC = false, int DEN = 0, bool TCV = false>
 __device__ __forceinline__ bool track_stack_lane(const StackArgs& A, const double el[6], bool live, TrackQueue& Q,
                                                  float& snr, float& flux, int& nv, const DebugArgs* dbg = nullptr,
                                                  int64_t rowbase = 0) {
@@ -433,7 +426,7 @@ __device__ __forceinline__ bool track_stack_lane(const StackArgs& A, const doubl
   track_bound(a, e, ob, A.vobs, bd);
   StackPart P;
   bool deferred = false;
-  track_walk<REC, DEFER, TCV>(A, ob, bd, live, Q, P, deferred, dbg, rowbase);
+  track_walk<REC, DEN, TCV>(A, ob, bd, live, Q, P, deferred, dbg, rowbase);
   snr = flux = __builtin_nanf("");
   nv = -1;
   if (deferred) return true;

@@ -116,6 +116,7 @@ __global__ __launch_bounds__(256) void k_stack_generated(StackArgs A, dt_orbit_s
 }
 
 // The same by checkpoint prediction (one wavefront per 64 generated orbits).
+template <int DEN>
 __global__ __launch_bounds__(64, 4) void k_stack_generated_track(StackArgs A, dt_orbit_sampler S, int64_t first) {
   __shared__ TrackQueue tq[1];
   if (wave_base() >= A.n) return;  // the whole wavefront is past the end
@@ -128,7 +129,7 @@ __global__ __launch_bounds__(64, 4) void k_stack_generated_track(StackArgs A, dt
     double el[6] = {0.0, 0.0, 0.0, 0.0, 0.0, 0.0};
     const bool live = in && gen_orbit(S, (uint64_t)(first + i), el) &&
                       orbit_ok(el[0], el[1], el[2], el[3], el[4], el[5]);
-    if (track_stack_lane<false, true, true>(A, el, live, tq[threadIdx.x >> 6], snr, flux, nv)) {
+    if (track_stack_lane<false, DEN, true>(A, el, live, tq[threadIdx.x >> 6], snr, flux, nv)) {
       defer_wave(A, wave_base());
       return;
     }
@@ -242,7 +243,10 @@ hipError_t launch_stack_generated(const StackArgs& a, const dt_orbit_sampler& S,
       hipError_t e = launch_zero_u32(a.defer_count, s);
       if (e != hipSuccess) return e;
     }
-    hipLaunchKernelGGL(k_stack_generated_track, dim3((unsigned)((a.n + 63) / 64)), dim3(64), 0, s, a, S, first);
+    with_switch(a, [&](auto den) {
+      hipLaunchKernelGGL(k_stack_generated_track<decltype(den)::value>, dim3((unsigned)((a.n + 63) / 64)), dim3(64), 0,
+                         s, a, S, first);
+    });
     if (a.defer_list)
       hipLaunchKernelGGL(k_stack_generated_deferred, dim3((unsigned)((a.n + 255) / 256)), dim3(256), 0, s, a, S,
                          first);

@@ -32,6 +32,7 @@ __global__ __launch_bounds__(256) void k_stack(StackArgs A) {
 // together; used when the patch has a finite observer speed bound).  One
 // wavefront per workgroup: the wavefronts are independent, and single-wave
 // workgroups measured 3 % faster than four-wave ones on the survey set.
+template <int DEN>
 __global__ __launch_bounds__(64, 4) void k_stack_track(StackArgs A) {
   __shared__ TrackQueue tq[1];
   if (wave_base() >= A.n) return;  // the whole wavefront is past the end
@@ -45,7 +46,7 @@ __global__ __launch_bounds__(64, 4) void k_stack_track(StackArgs A) {
     if (in) {
       el[0] = A.a[o]; el[1] = A.e[o]; el[2] = A.inc[o]; el[3] = A.node[o]; el[4] = A.peri[o]; el[5] = A.m0[o];
     }
-    if (track_stack_lane<false, true, true>(A, el, in && orbit_ok(el[0], el[1], el[2], el[3], el[4], el[5]),
+    if (track_stack_lane<false, DEN, true>(A, el, in && orbit_ok(el[0], el[1], el[2], el[3], el[4], el[5]),
                                            tq[threadIdx.x >> 6], snr, flux, nv)) {
       defer_wave(A, wave_base());
       return;
@@ -277,7 +278,9 @@ hipError_t launch_stack(const StackArgs& a, hipStream_t s) {
   }
   if (a.vobs < __builtin_inf()) {
     if (a.defer_list) hipLaunchKernelGGL(k_zero_u32, dim3(1), dim3(1), 0, s, a.defer_count);
-    hipLaunchKernelGGL(k_stack_track, dim3(grid_for(a.n, 64)), dim3(64), 0, s, a);
+    with_switch(a, [&](auto den) {
+      hipLaunchKernelGGL(k_stack_track<decltype(den)::value>, dim3(grid_for(a.n, 64)), dim3(64), 0, s, a);
+    });
     if (a.defer_list) hipLaunchKernelGGL(k_stack_deferred, dim3(grid_for(a.n, 256)), dim3(256), 0, s, a);
   } else {
     hipLaunchKernelGGL(k_stack, dim3(grid_for(a.n, 256)), dim3(256), 0, s, a);

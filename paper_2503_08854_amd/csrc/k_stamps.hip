@@ -415,6 +415,7 @@ __global__ void k_zero_i64(int64_t* p) { *p = 0; }
 // The plain stack on a device list of orbit ids (the first *count of them;
 // outputs at the orbits' own indices), by checkpoint prediction with deferral
 // of wavefronts whose samples land often (list index of their first lane).
+template <int DEN>
 __global__ __launch_bounds__(256, 4) void k_stack_ids_track(StackArgs A, const int64_t* __restrict__ ids,
                                                             const int64_t* __restrict__ count) {
   __shared__ TrackQueue tq[4];
@@ -432,8 +433,8 @@ __global__ __launch_bounds__(256, 4) void k_stack_ids_track(StackArgs A, const i
     if (ok) {
       el[0] = A.a[o]; el[1] = A.e[o]; el[2] = A.inc[o]; el[3] = A.node[o]; el[4] = A.peri[o]; el[5] = A.m0[o];
     }
-    if (track_stack_lane(A, el, ok && orbit_ok(el[0], el[1], el[2], el[3], el[4], el[5]), tq[threadIdx.x >> 6], snr,
-                         flux, nv)) {
+    if (track_stack_lane<false, DEN>(A, el, ok && orbit_ok(el[0], el[1], el[2], el[3], el[4], el[5]),
+                                     tq[threadIdx.x >> 6], snr, flux, nv)) {
       defer_wave(A, wave_base());
       return;
     }
@@ -579,7 +580,9 @@ hipError_t launch_stack_ids(const StackArgs& a, const int64_t* d_ids, const int6
   if (m_max > STACK_IDS_SHORT) {  // the count may be long: the kernels for long lists too
     if (a.vobs < __builtin_inf()) {
       // (the deferral counter was zeroed by k_stack_ids_split)
-      hipLaunchKernelGGL(k_stack_ids_track, dim3(grid), dim3(256), 0, s, a, d_ids, d_count);
+      with_switch(a, [&](auto den) {
+        hipLaunchKernelGGL(k_stack_ids_track<decltype(den)::value>, dim3(grid), dim3(256), 0, s, a, d_ids, d_count);
+      });
       if (a.defer_list) hipLaunchKernelGGL(k_stack_ids_deferred, dim3(grid), dim3(256), 0, s, a, d_ids, d_count);
     } else {
       hipLaunchKernelGGL(k_stack_ids, dim3(grid), dim3(256), 0, s, a, d_ids, d_count);
