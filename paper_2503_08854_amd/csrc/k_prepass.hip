@@ -172,11 +172,15 @@ hipError_t launch_exposure_prep(const dt_exposure* d_in, const int64_t* d_plane_
 //
 // HBM bounds it: 57 vector instructions per pixel at R = 4 (120 with one
 // column per thread, of them 18 moves of the row window and 12 of rows in
-// flight, each of which waited for the newest row).  120 FP16 4096^2 images
-// (24 GB): 4.6-5.5 ms by where the buffers lie (4.4-5.3 TB/s; a device copy
-// reaches 4.8), 9.6 ms before; 57 of 1031 x 773: 0.15 ms (3.7 TB/s), 0.38
-// before; 200 FP32 2048^2 (13.4 GB): 2.55-3.0 ms, 2.95 before.  Four rows in
-// flight measured as six and three do.
+// flight, each of which waited for the newest row).  Images are read with
+// ordinary loads: neighbouring strips share halo rows and the cache lines at
+// their edges, which the non-temporal hint drops (100 FP32 2048^2 images at
+// R = 4 1.49 ms with it, 1.42 without; 40 FP16 4096^2 1.84 and 1.69; 60 FP16
+// 1000^2 at R = 1 0.170 and 0.116).  One column per thread: 1.45, 3.09 and
+// 0.255 ms; 57 FP16 of 1031 x 773 0.29 -> 0.136.  A device copy reaches 4.8
+// TB/s (6.7 GB of the first in 1.40 ms, 8.1 GB of the second in 1.68); where
+// the buffers lie moves a time by up to 8 %.  Four rows in flight measured as
+// six and three do.
 // ----------------------------------------------------------------------------
 // The image pointers come from a device array, so they are generic to the
 // compiler; reading through global pointers keeps these loads off the LDS
@@ -194,7 +198,7 @@ struct Pair<float> {
   typedef uint32_t vec __attribute__((ext_vector_type(2), aligned(4)));
   vec v;
   __device__ __forceinline__ void load(const float* p, int c) {
-    v = __builtin_nontemporal_load((const __attribute__((address_space(1))) vec*)(global_ptr(p) + c));
+    v = *(const __attribute__((address_space(1))) vec*)(global_ptr(p) + c);
   }
   // {pixel 0, pixel 1}
   __device__ __forceinline__ float2 use(bool second, uint32_t kill0, uint32_t kill1) const {
@@ -206,7 +210,7 @@ struct Pair<_Float16> {
   typedef uint32_t word __attribute__((aligned(2)));
   uint32_t v;
   __device__ __forceinline__ void load(const _Float16* p, int c) {
-    v = __builtin_nontemporal_load((const __attribute__((address_space(1))) word*)(global_ptr(p) + c));
+    v = *(const __attribute__((address_space(1))) word*)(global_ptr(p) + c);
   }
   __device__ __forceinline__ float2 use(bool second, uint32_t kill0, uint32_t kill1) const {
     const uint32_t u = (second ? v >> 16 : v) | (kill0 & 0xffffu) | (kill1 << 16);
