@@ -319,7 +319,7 @@ dt_status dt_patch_create(dt_ctx* c, const dt_exposure* exps, int32_t n_exp, con
     return fail(DT_E_DOMAIN, "stamp half-width %d exceeds %d", p->rmax, PREP_RMAX);
   }
   // Pre-pass tiles, grouped by stamp half-width (one kernel instance per R;
-  // group 0: images one column wide).  A tile is a strip of prep_width(R)
+  // group 0: images one column wide).  A tile is a strip of up to prep_width(R)
   // columns and about PREP_TY rows, strips of an image of equal height (a
   // fixed height leaves most images a short or nearly empty last strip).
   // Patches of few tiles take lower ones, down to PREP_TY_MIN rows, until
@@ -333,7 +333,7 @@ dt_status dt_patch_create(dt_ctx* c, const dt_exposure* exps, int32_t n_exp, con
     return std::max<int64_t>(1, ((int64_t)x.height + ty / 2) / ty);
   };
   auto tile_R = [&](int s) { return sorted[s].width == 1 ? 0 : rad[s]; };
-  auto tile_w = [&](int s) { return tile_R(s) ? prep_width(tile_R(s)) : 1; };
+  auto tile_w = [&](int s) -> int64_t { return tile_R(s) ? prep_strip(tile_R(s), sorted[s].width) : 1; };
   int ty = PREP_TY;
   for (; ty > PREP_TY_MIN; ty /= 2) {
     int64_t n = 0;
@@ -346,9 +346,9 @@ dt_status dt_patch_create(dt_ctx* c, const dt_exposure* exps, int32_t n_exp, con
     for (int s = 0; s < n_exp; ++s) {
       if (tile_R(s) != R) continue;
       const dt_exposure& x = sorted[s];
-      const int64_t h = (x.height + strips(x, ty) - 1) / strips(x, ty);
+      const int64_t h = (x.height + strips(x, ty) - 1) / strips(x, ty), w = tile_w(s);
       for (int64_t y0 = 0; y0 < x.height; y0 += h)
-        for (int64_t x0 = 0; x0 < x.width; x0 += tile_w(s))
+        for (int64_t x0 = 0; x0 < x.width; x0 += w)
           tiles.push_back(PrepTile{s, (int32_t)x0, (int32_t)y0, (int32_t)std::min(h, x.height - y0)});
     }
     if (tiles.size() > before) {

@@ -53,6 +53,7 @@ struct alignas(16) ExpMeta {
   int32_t R;                // stamp half-width ceil(3 sigma)
   float vs;                 // scalar pixel variance when the patch has no variance planes
   int32_t ck_next;          // first exposure (epoch order) more than CK_SPAN days after this one (n + 1 when none)
+  int32_t strip;            // columns of a pre-pass tile (prep_strip)
 };
 // A patch holds n + 1 records: the last exposure's record is repeated once
 // (the checkpoint walk's final queue-serving step reads it, uses nothing of it).
@@ -96,6 +97,19 @@ constexpr int PREP_DEPTH = 4; // input rows each lane keeps in flight
 constexpr int prep_groups(int R) { return R <= 6 ? 2 : 1; }
 constexpr int prep_lead(int R) { return (R + 1) & ~1; }
 constexpr int prep_width(int R) { return (128 * prep_groups(R) - prep_lead(R) - R) & ~1; }
+// Columns of the tiles of an image W wide.  Strips are as wide as can be.  The
+// narrowest stamps leave nothing but memory to wait for: where the image's rows
+// are whole 128-byte lines of the plane, their strips are as many of equal width
+// in whole lines if that still fits, so that no line is written by two (100 FP32
+// 2048^2 images at R = 1: 1.48 ms in strips of 252 columns, 1.37 of 240; 1.41 and
+// 1.39 at R = 4).  More strips for the sake of whole lines gain nothing (40 of
+// 4096^2: 2.38 and 2.39).
+constexpr int PREP_EVEN_R = 2;
+__host__ __device__ inline int prep_strip(int R, int W) {
+  const int most = prep_width(R), n = (int)(((int64_t)W + most - 1) / most);
+  const int w = (int)(((int64_t)W + n - 1) / n + 15) / 16 * 16;
+  return R <= PREP_EVEN_R && W % 16 == 0 && w <= most ? w : most;
+}
 constexpr int PREP_RMAX = 12; // largest stamp half-width supported (FWHM <= 8 px gives R = 11)
 
 // Launchers (defined in the .hip files; all enqueue on `s`).

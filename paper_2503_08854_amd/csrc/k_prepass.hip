@@ -89,6 +89,7 @@ __global__ void k_exposure_prep(const dt_exposure* __restrict__ in, const int64_
     else lo = mid + 1;
   }
   m.ck_next = lo < n ? lo : n + 1;
+  m.strip = prep_strip(m.R, m.W);
   // Sky cone of the image.  The pixel (x, y) is the direction
   // c + xi e + eta n with (xi, eta) = CD (x - px0, y - py0) in radians; the
   // axis is the centre pixel's direction and the half-angle is the largest
@@ -157,7 +158,7 @@ hipError_t launch_exposure_prep(const dt_exposure* d_in, const int64_t* d_plane_
 }
 
 // ----------------------------------------------------------------------------
-// Matched-filter planes.  One wavefront per strip of prep_width(R) output
+// Matched-filter planes.  One wavefront per strip of up to prep_width(R) output
 // columns and up to a few hundred output rows; wavefronts share nothing, so
 // there is no barrier.  It streams the input rows y0 - R .. y0 + ny + R - 1:
 // each lane holds two adjacent columns (two groups of them up to R = 6, so
@@ -333,7 +334,7 @@ __global__ __launch_bounds__(64) void k_prepass(const ExpMeta* __restrict__ meta
   // this strip (nothing for the rows before the first one and past the last
   // one): the hardware drops the lanes past it.  The pair that an odd width
   // cuts is stored on its own.
-  const int n_out = min(W - tl.x0, prep_width(R));
+  const int n_out = min(W - tl.x0, R <= PREP_EVEN_R ? m.strip : prep_width(R));
   const bool odd = (n_out & 1) != 0;
   float2* out = planes + m.plane_off + (int64_t)(tl.y0 - 2 * R) * W + tl.x0;
 #pragma unroll 1
