@@ -110,7 +110,7 @@ __host__ __device__ inline int prep_strip(int R, int W) {
   const int w = (int)(((int64_t)W + n - 1) / n + 15) / 16 * 16;
   return R <= PREP_EVEN_R && W % 16 == 0 && w <= most ? w : most;
 }
-constexpr int PREP_RMAX = 12; // largest stamp half-width supported (FWHM <= 8 px gives R = 11)
+constexpr int PREP_RMAX = 11; // largest stamp half-width supported (FWHM <= 8 px gives R = 11)
 
 // Launchers (defined in the .hip files; all enqueue on `s`).
 hipError_t launch_exposure_prep(const dt_exposure* d_in, const int64_t* d_plane_off, const int32_t* d_src,
@@ -248,8 +248,7 @@ hipError_t launch_validate(const StackArgs& a, unsigned long long* d_bad, hipStr
 
 // BF16 GEMM C = op(A) op(B) (+ bias, ReLU) with FP32 accumulation; op(A) is
 // M x K (A stored [K x M] when transA), op(B) is K x N (B stored [N x K] when
-// transB).  Outputs FP32 (Cf) and/or BF16 (Cb), each with its own leading
-// dimension; d_part is split-K scratch of part_elems floats.
+// transB).  d_part is split-K scratch of part_elems floats.
 struct GemmArgs {
   const uint16_t* A;
   int lda, transA;
@@ -260,8 +259,6 @@ struct GemmArgs {
   int relu;
   float* Cf;
   int ldcf;
-  uint16_t* Cb;
-  int ldcb;
 };
 hipError_t launch_gemm_bf16(const GemmArgs& g, float* d_part, size_t part_elems, hipStream_t s);
 hipError_t launch_init_params(float* w, int64_t off, int64_t n, int fan_in, uint64_t seed, int is_bias,

@@ -33,7 +33,7 @@ dt_status dt_gemm_bf16(dt_ctx* c, const uint16_t* d_A, int32_t lda, int32_t tran
   float* part = nullptr;
   dt_status st = ctx_alloc(c, (void**)&part, sizeof(float) * part_elems, "GEMM split-K scratch");
   if (st != DT_OK) return st;
-  GemmArgs g{d_A, lda, transA ? 1 : 0, d_B, ldb, transB ? 1 : 0, M, N, K, d_bias, relu ? 1 : 0, d_C, ldc, nullptr, 0};
+  GemmArgs g{d_A, lda, transA ? 1 : 0, d_B, ldb, transB ? 1 : 0, M, N, K, d_bias, relu ? 1 : 0, d_C, ldc};
   hipError_t e = launch_gemm_bf16(g, part, part_elems, c->stream);
   if (e == hipSuccess) e = hipStreamSynchronize(c->stream);
   ctx_free(c, part, sizeof(float) * part_elems);

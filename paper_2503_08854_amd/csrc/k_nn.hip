@@ -17,22 +17,15 @@ namespace dtk {
 typedef __bf16 bf16x8_t __attribute__((ext_vector_type(8)));
 typedef float float4_t __attribute__((ext_vector_type(4)));
 
-__device__ __forceinline__ uint16_t f2bf(float f) {  // round to nearest even (NaN kept quiet)
-  uint32_t u = __float_as_uint(f);
-  if ((u & 0x7fffffffu) > 0x7f800000u) return (uint16_t)((u >> 16) | 0x40u);
-  u += 0x7fffu + ((u >> 16) & 1u);
-  return (uint16_t)(u >> 16);
-}
-
 constexpr int GT_M = 64, GT_N = 64, GT_K = 32;
 
 // Partial GEMM over k in [k0, k1).  Output: if part != null, raw FP32 tile to
-// part (ldc = N); otherwise the epilogue (bias, ReLU, FP32 and/or BF16 out).
+// part (ldc = N); otherwise the epilogue (bias, ReLU).
 __global__ __launch_bounds__(256) void k_gemm_bf16(const uint16_t* __restrict__ A, int lda, int transA,
                                                    const uint16_t* __restrict__ B, int ldb, int transB, int M,
                                                    int N, int K, int k_per_split, float* __restrict__ part,
                                                    const float* __restrict__ bias, int relu, float* __restrict__ Cf,
-                                                   int ldcf, uint16_t* __restrict__ Cb, int ldcb) {
+                                                   int ldcf) {
   // [m][k] and [n][k]; rows of 80 bytes keep every 8-element operand 16-byte aligned
   __shared__ __attribute__((aligned(16))) uint16_t sA[GT_M][GT_K + 8];
   __shared__ __attribute__((aligned(16))) uint16_t sB[GT_N][GT_K + 8];
@@ -97,14 +90,12 @@ __global__ __launch_bounds__(256) void k_gemm_bf16(const uint16_t* __restrict__ 
         }
         if (bias) v += bias[gn];
         if (relu) v = fmaxf(v, 0.f);
-        if (Cf) Cf[(int64_t)gm * ldcf + gn] = v;
-        if (Cb) Cb[(int64_t)gm * ldcb + gn] = f2bf(v);
+        Cf[(int64_t)gm * ldcf + gn] = v;
       }
 }
 
 __global__ void k_splitk_reduce(const float* __restrict__ part, int splits, int M, int N,
-                                const float* __restrict__ bias, int relu, float* __restrict__ Cf, int ldcf,
-                                uint16_t* __restrict__ Cb, int ldcb) {
+                                const float* __restrict__ bias, int relu, float* __restrict__ Cf, int ldcf) {
   const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (i >= (int64_t)M * N) return;
   const int gm = (int)(i / N), gn = (int)(i % N);
@@ -112,8 +103,7 @@ __global__ void k_splitk_reduce(const float* __restrict__ part, int splits, int 
   for (int s = 0; s < splits; ++s) v += part[(int64_t)s * M * N + i];
   if (bias) v += bias[gn];
   if (relu) v = fmaxf(v, 0.f);
-  if (Cf) Cf[(int64_t)gm * ldcf + gn] = v;
-  if (Cb) Cb[(int64_t)gm * ldcb + gn] = f2bf(v);
+  Cf[(int64_t)gm * ldcf + gn] = v;
 }
 
 hipError_t launch_gemm_bf16(const GemmArgs& g, float* d_part, size_t part_elems, hipStream_t s) {
@@ -129,14 +119,14 @@ hipError_t launch_gemm_bf16(const GemmArgs& g, float* d_part, size_t part_elems,
   if (splits == 1) {
     hipLaunchKernelGGL(k_gemm_bf16, dim3(gm, gn, 1), dim3(256), 0, s, g.A, g.lda, g.transA, g.B, g.ldb, g.transB,
                        g.M, g.N, g.K, g.K > 0 ? ((g.K + GT_K - 1) / GT_K) * GT_K : GT_K, nullptr, g.bias, g.relu,
-                       g.Cf, g.ldcf, g.Cb, g.ldcb);
+                       g.Cf, g.ldcf);
     return hipGetLastError();
   }
   hipLaunchKernelGGL(k_gemm_bf16, dim3(gm, gn, splits), dim3(256), 0, s, g.A, g.lda, g.transA, g.B, g.ldb,
-                     g.transB, g.M, g.N, g.K, kps, d_part, nullptr, 0, nullptr, 0, nullptr, 0);
+                     g.transB, g.M, g.N, g.K, kps, d_part, nullptr, 0, nullptr, 0);
   const int64_t mn = (int64_t)g.M * g.N;
   hipLaunchKernelGGL(k_splitk_reduce, dim3((unsigned)((mn + 255) / 256)), dim3(256), 0, s, d_part, splits, g.M, g.N,
-                     g.bias, g.relu, g.Cf, g.ldcf, g.Cb, g.ldcb);
+                     g.bias, g.relu, g.Cf, g.ldcf);
   return hipGetLastError();
 }
 

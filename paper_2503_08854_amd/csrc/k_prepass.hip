@@ -453,7 +453,7 @@ static hipError_t launch_prepass_t(int R, const ExpMeta* d_meta, const PrepTile*
                        d_planes);                                                                          \
     break;
     DT_CASE(1) DT_CASE(2) DT_CASE(3) DT_CASE(4) DT_CASE(5) DT_CASE(6)
-    DT_CASE(7) DT_CASE(8) DT_CASE(9) DT_CASE(10) DT_CASE(11) DT_CASE(12)
+    DT_CASE(7) DT_CASE(8) DT_CASE(9) DT_CASE(10) DT_CASE(11)
 #undef DT_CASE
     default:
       return hipErrorInvalidValue;
