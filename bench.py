@@ -25,9 +25,10 @@ import numpy as np
 ROOT = os.path.dirname(os.path.abspath(__file__))
 sys.path.insert(0, ROOT)
 
-# Operations of the stack kernel's path as written, in FP64 operations (an FMA
-# counts 2; add / mul / hardware reciprocal or rsqrt estimate 1; an FP32
-# operation counts half, as the vector peaks do).  Every dense sample, in FP32:
+# Operations of the stack kernel's path as written (an FMA counts 2; add / mul
+# / hardware reciprocal or rsqrt estimate 1; an FP32 operation counts as an
+# FP64 one: the kernels are built without packed FP32 instructions, so both
+# issue at the same rate).  Every dense sample, in FP32:
 # the prediction p = r + D (v + D h) - obs 15 and its test against the image
 # rectangle 26 (three projections 15, bound 5, widened half sizes 4, test 2).
 # Every exact solve (each orbit at each checkpoint, and each sample that lands
@@ -36,7 +37,7 @@ sys.path.insert(0, ROOT)
 # with a tiny rotation 12), position and distance 25, velocity and light-time
 # correction 23, corrected position 6, light time 1, projection with one-
 # refinement reciprocal 24, rounding 2.
-FLOPS_PER_SAMPLE = 20.5
+FLOPS_PER_SAMPLE = 41
 FLOPS_PER_SOLVE = 125
 # A wavefront whose samples land often leaves the prediction for the
 # per-sample walk: per sample 82 (mean anomaly with the predicted light time

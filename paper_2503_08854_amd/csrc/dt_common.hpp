@@ -27,8 +27,8 @@ constexpr double CK_SPAN = 12.0;
 // Everything is expressed in the heliocentric ecliptic frame so no rotation
 // is needed per sample: the TAN basis is rotated once per exposure instead.
 struct alignas(16) ExpMeta {
-  // The fields every step of the checkpoint walk reads come first (64 bytes,
-  // one scalar load).  A position q (AU from the observer) projects into the
+  // The fields every step of the checkpoint walk reads come first (64 bytes:
+  // four scalar loads issued together, one wait).  A position q (AU from the observer) projects into the
   // pixel rectangle only if c.q > 0, |A0'.q| <= (W / 2) c.q and likewise for y,
   // with A0' = a0 + (px0 - (W - 1) / 2) c; kx X = A0' and so on are those scaled
   // so that a displacement of q by d changes |X.q| - kx c.q by at most d.
