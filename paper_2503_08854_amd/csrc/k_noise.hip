@@ -29,9 +29,10 @@
 // All comparisons that decide the result are the FP64 ones of the definition,
 // so the result is exact on either route.
 //
-// Two image reads bound it.  200 FP32 2048^2 images (3.36 GB): bins 0.71 ms
-// (4.7 TB/s, the copy rate), collect 0.66 ms, sample + plan + solve 0.23 ms
-// (one workgroup per image, latency); 1.55 ms together, 32.2 ms before, when
+// Two image reads bound it.  200 FP32 2048^2 images (3.36 GB), one kernel
+// trace: bins 0.71 ms (4.7 TB/s, the copy rate), collect 0.66 ms, sample +
+// plan + solve 0.055 + 0.047 + 0.131 ms (one workgroup per image, latency),
+// 1.60 ms together; 1.53 ms a call without the trace, 32.2 ms before, when
 // every 11-bit digit of every median and deviation of every step read the
 // images again (26 reads).  48 FP32 2048 x 1536 images: 0.43 ms, 6.9 before.
 // (In sample and solve the middle deviation is found by wavefronts over the
